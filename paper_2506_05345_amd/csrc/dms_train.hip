@@ -8,22 +8,30 @@
 // classified per block of queries as entirely old (bias per key), entirely
 // inside the window (no bias) or mixed (per-element select).
 //
-// Passes (all MFMA v_mfma_f32_16x16x32_bf16, fp32 accumulation):
-//   tile   -- every input tensor [B, T, H, d] becomes 32-token tiles holding
-//             a row part (keys-as-rows MFMA operand order) and a transposed
-//             part (dims-as-rows order), so every kernel stages tiles with
-//             contiguous 16-byte copies and reads operands conflict-free;
+// Passes (all MFMA v_mfma_f32_32x32x16_bf16, fp32 accumulation):
+//   bias   -- log2(1 - alpha) per key, token order per head;
 //   fwd    -- query-major online softmax, as in the masked prefill: out, lse;
-//   rowsum -- D_t = sum_d dout * out per query row;
-//   dq     -- query-major: recompute P, dP = dO V^T, dS = P (dP - D),
-//             dQ = scale dS K;
-//   dkv    -- key-major: each wave keeps 16 keys' K and V operands in
+//   dq     -- query-major: D_t = sum_d dout * out, recompute P, dP = dO V^T,
+//             dS = P (dP - D), dQ = scale dS K;
+//   dkv    -- key-major: each wave keeps 32 keys' K and V operands in
 //             registers and walks the query tiles of every query head of the
 //             group: dV = P^T dO, dK = scale dS^T Q and
 //             dalpha_j = -sum_t exp(s_tj - lse_t) (dP_tj - D_t) over t >= j + w
 //             (the probability without the (1 - alpha_j) factor, so the
 //             gradient stays finite where alpha_j = 1).
+// What bounds them: instruction issue and operand latency beside the matrix
+// core (about half busy in each).  32x32 products take half the MFMA and LDS
+// read instructions per key of 16x16 ones.  One layer of 8 x 5 heads, 2 x
+// 8192 tokens, w = 256, before (16x16 products on tiles re-laid in memory by a
+// pass of their own) and now: forward 1836 -> 1430 us (960 TFLOP/s), dQ 4005
+// -> 1850 us (1110 of its three products), dK / dV 5160 -> 2590 us (1060 of
+// its four), tiling and row sums 380 us -> none.  Pairing each tile's weights
+// with the next tile's scores and the last tile's value products in one
+// scheduled stretch ran 1540 to 1700 us forward: the second wave of a SIMD
+// already fills the gaps, and the tile-by-tile barriers cost more.
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "dms_common.h"
 #include "dms_train.h"
@@ -33,41 +41,44 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+
+#define DMS_LDS __attribute__((address_space(3)))
 
 constexpr int kThreads = 256;
 constexpr int kTrainD = kTrainHeadDim;
+constexpr int kRowB = kTrainD * 2;    // bytes of one bf16 row
+constexpr int kUnit = 32 * kRowB;     // one 32-token tile of one tensor in LDS (8 KB)
+constexpr int kStage = 4 * kUnit;     // one staged step: two tensors x two tiles
+constexpr int kKS = kTrainD / 16;     // k-steps of a product over the head dimension
+constexpr int kDB = kTrainD / 32;     // 32-dim blocks of a head
 constexpr float kRescale = 8.0f;      // lazy rescale threshold, log2 units
 constexpr float kMInit = -1.0e30f;    // running max before the first visible key
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-__device__ inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+__device__ inline f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 __device__ inline u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
-__device__ inline void st16(void* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
-// max / sum over the four lanes r, r + 16, r + 32, r + 48
+// max / sum over the two lanes of one column (l and l + 32)
 __device__ inline float col_max(float x) {
   const uint32_t u = __float_as_uint(x);
   const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 __device__ inline float col_sum(float x) {
   const uint32_t u = __float_as_uint(x);
   const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
 // The dispatcher deals workgroups to the 8 XCDs round-robin by linear id, and
@@ -97,49 +108,144 @@ __device__ inline u32x4 pack_bf16(const float* e) {
 }
 
 // ---------------------------------------------------------------------------
-// Tile layout (one 32-token tile of one head: D * 128 bytes)
-//   row part, bytes [0, D*64): 16-byte slot P holds dims 32 (P / 128) +
-//     8 ((P / 16) % 4) .. + 7 of tile row (r % 4) + 8 (r / 4) + 4 ((P / 64) % 2),
-//     r = P % 16 -- the order in which MFMA A-operand loads of "rows" (two
-//     16-row blocks whose rows are tokens 8 (r / 4) + r % 4 and that + 4)
-//     read it: lane L of the load for dims [32 s, 32 s + 32) reads slot
-//     128 s + L (first block) or 128 s + 64 + L (second block);
-//   transposed part, bytes [D*64, D*128): slot P holds tokens 8 ((P / 16) % 4)
-//     .. + 7 of dim 16 (P / 64) + P % 16 -- the A operand of a product over
-//     the tile's tokens, dims 16 b .. + 15 at slots 64 b + L.
+// LDS tiles.  A 32-token tile of one head is staged row-major (256 bytes a
+// token) straight from the [B, T, heads, D] input by global -> LDS copies,
+// its 16-byte pieces permuted inside each row: piece dg of token t lies at
+// t * 256 + 16 (dg ^ x(t)), x(t) = 4 (t % 4) + (t / 4) % 4.  Both operand
+// reads then spread over all 64 banks:
+//   rows (a product over dims): lane l of k-step s takes dims 16 s + 8 (l / 32)
+//     .. + 7 of token row_token(l % 32) with one 16-byte read;
+//   columns (a product over tokens): lane l of (dim block b, half s) takes
+//     tokens 16 s + 8 (l / 32) .. + 7 of dim 32 b + l % 32 with two LDS
+//     transpose reads (ds_read_b64_tr_b16: in a 16-lane group, lane 4 j + q
+//     passes the address of dims 4 q .. of token j and lane i receives dim i).
+// Measured with eight waves reading: 4.0 cycles per wave read for both (256
+// bytes a cycle for rows), 7.6 or more for the transpose reads of the
+// unpermuted or t % 16-permuted rows.  Against tiles re-laid in memory by a
+// pass of their own (row part and transposed part) this halves the staged
+// bytes of the key-major pass and saves the pass.
+// row_token orders the rows of a score MFMA so that accumulator registers
+// 8 s .. 8 s + 7 of a lane are tokens 16 s + 8 (l / 32) .. + 7: exactly the B
+// operand of half s of the next product.
 // ---------------------------------------------------------------------------
-struct TileArgs {
-  const uint16_t* x;   // [B, T, H, D]
-  char* tiles;         // [B, H, nt] tiles
-  int T, H, nt;
+__device__ inline int row_token(int r) {
+  return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
+}
+
+// Per-lane byte offsets; the others follow by an exclusive or (offsets of
+// rows are multiples of 256, so it stays inside a row).
+struct LaneOffsets {
+  uint32_t row;   // row operand of k-step 0; k-step s: ^ 32 s
+  uint32_t col;   // column operand of dim block 0, tokens 0-3 of the eight; block b: ^ 64 b,
+                  // tokens 4-7: ^ 16, + 1024
+  uint32_t src;   // source of copy 0 (rows 0 .. 3); copy m (rows 4 m ..): ^ 16 (m % 4)
 };
 
-template <int D>
-__global__ __launch_bounds__(kThreads) void train_tile_kernel(TileArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t rows[32][D + 8];
-  const int k = blockIdx.x, bh = blockIdx.y;
-  const int b = bh / a.H, h = bh % a.H;
-  const int tid = threadIdx.x;
-  for (int q = tid; q < 32 * D / 8; q += kThreads) {
-    const int row = q / (D / 8), e0 = 8 * (q % (D / 8));
-    const int t = 32 * k + row;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (t < a.T) v = ld16(a.x + ((static_cast<size_t>(b) * a.T + t) * a.H + h) * D + e0);
-    st16(&rows[row][e0], v);
-  }
-  __syncthreads();
-  char* tile = a.tiles + (static_cast<size_t>(bh) * a.nt + k) * (D * 128);
-  for (int P = tid; P < D * 4; P += kThreads) {
-    const int r = P & 15, c = (P >> 4) & 3, hh = (P >> 6) & 1, s = P >> 7;
-    const int j = (r & 3) + 8 * (r >> 2) + 4 * hh;
-    st16(tile + P * 16, ld16(&rows[j][32 * s + 8 * c]));
-    const int G = c, e = 16 * (P >> 6) + r;
-    u32x4 v;
+__device__ inline LaneOffsets lane_offsets(int lane, uint32_t row_stride) {
+  LaneOffsets o;
+  const int hf = lane >> 5;
+  const int t = row_token(lane & 31);
+  o.row = t * kRowB + 16 * (hf ^ (4 * (t & 3) + ((t >> 2) & 3)));
+  const int blk = (lane >> 4) & 1, j = (lane & 15) >> 2, q = lane & 3;
+  o.col = (8 * hf + j) * kRowB + 16 * ((2 * blk + (q >> 1)) ^ (4 * j + 2 * hf)) + 8 * (q & 1);
+  const int tr = lane >> 4, c = lane & 15;
+  o.src = tr * row_stride + 16 * (c ^ (4 * tr));
+  return o;
+}
+
+__device__ inline uint32_t lds_addr(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DMS_LDS const char*)p));
+}
+// 64 lanes x 16 bytes (4 bytes) from base + off (per lane) to LDS m0 + 16 (4) lane.  The LDS
+// destination goes in M0, written by the same statement; nothing else in this
+// file reads M0.  The compiler does not count these loads: the kernels wait
+// for them (vmcnt) before the barrier that publishes a stage.
+__device__ inline void lds_copy16(const void* base, uint32_t off, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ inline void lds_copy4(const void* base, uint32_t off, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(m0), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ inline void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// keeps the compiler from forming what follows from x ahead of a loop and holding it
+__device__ inline int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// One wave copies rows t0 .. t0 + 31 of one head (row t at base + t * stride
+// bytes) to the LDS tile `dst`; rows past the last token repeat it.
+__device__ inline void copy_tile(const char* base, int t0, int T, uint32_t stride, const LaneOffsets& o,
+                                 int lane, uint32_t dst) {
+  if (t0 + 32 <= T) {
+    const char* src = base + static_cast<size_t>(t0) * stride;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      v[i] = static_cast<uint32_t>(rows[8 * G + 2 * i][e]) |
-             (static_cast<uint32_t>(rows[8 * G + 2 * i + 1][e]) << 16);
-    st16(tile + D * 64 + P * 16, v);
+    for (int m = 0; m < 8; ++m) lds_copy16(src + static_cast<size_t>(4 * m) * stride, o.src ^ (16 * (m & 3)), dst + 1024 * m);
+  } else {
+    const int ln = fresh(lane);   // formed here, not held ahead of the loop
+    const int tr = ln >> 4, c = ln & 15;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int r0 = min(t0 + 4 * m, T - 1);                    // first row of the copy
+      const uint32_t d = min(tr, T - 1 - r0);
+      lds_copy16(base + static_cast<size_t>(r0) * stride, d * stride + 16 * (c ^ (4 * tr + (m & 3))), dst + 1024 * m);
+    }
+  }
+}
+
+// Operand reads of the LDS tile at byte address `t` (a multiple of 256).
+__device__ inline u32x4 row_operand(uint32_t t, const LaneOffsets& o, int s) {
+  return *reinterpret_cast<DMS_LDS const u32x4*>((t + o.row) ^ (32 * s));
+}
+__device__ inline u32x2 tr_read16(uint32_t p) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<DMS_LDS v4i16*>(p)));
+}
+// column operand of dim block b, token half s
+__device__ inline u32x4 col_operand(uint32_t t, const LaneOffsets& o, int b, int s) {
+  const u32x2 lo = tr_read16(((t + o.col) ^ (64 * b)) + 16 * s * kRowB);
+  const u32x2 hi = tr_read16(((t + o.col) ^ (64 * b) ^ 16) + 16 * s * kRowB + 1024);
+  return u32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+// Every operand address of a lane in the tile at LDS byte address 0: passes
+// with registers to spare hold them, so that a read is one instruction with
+// the tile as its immediate offset (formed per read they were a sixth of the
+// forward's VALU instructions).
+struct LaneAddresses {
+  uint32_t row[kKS], col[kDB][2];
+};
+__device__ inline LaneAddresses lane_addresses(uint32_t t, const LaneOffsets& o) {
+  LaneAddresses r;
+#pragma unroll
+  for (int s = 0; s < kKS; ++s) r.row[s] = (t + o.row) ^ (32 * s);
+#pragma unroll
+  for (int b = 0; b < kDB; ++b) {
+    r.col[b][0] = (t + o.col) ^ (64 * b);
+    r.col[b][1] = ((t + o.col) ^ (64 * b) ^ 16) + 1024;
+  }
+  return r;
+}
+__device__ inline u32x4 row_operand(int tile, const LaneAddresses& r, int s) {
+  return *reinterpret_cast<DMS_LDS const u32x4*>(r.row[s] + tile);
+}
+__device__ inline u32x4 col_operand(int tile, const LaneAddresses& r, int b, int s) {
+  const u32x2 lo = tr_read16(r.col[b][0] + tile + 16 * s * kRowB);
+  const u32x2 hi = tr_read16(r.col[b][1] + tile + 16 * s * kRowB);
+  return u32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+// keeps the compiler from forming (and holding) every operand address ahead of the loop
+__device__ inline void refresh(LaneOffsets& o) { asm volatile("" : "+v"(o.row), "+v"(o.col), "+v"(o.src)); }
+
+// Scheduling order of a stretch of M MFMAs: P LDS reads ahead, then R reads
+// beside each (bounds the operands in flight, so that the accumulators and the
+// resident operands fit without spills).
+template <int P, int M, int R>
+__device__ __forceinline__ void paced() {
+  __builtin_amdgcn_sched_group_barrier(0x100, P, 0);
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
   }
 }
 
@@ -154,21 +260,39 @@ struct TrainArgs {
   const float* alpha;      // [B, T, H]
   const float* out;        // [B, T, Hq, D]
   const float* lse;        // [B, Hq, T]
-  const float* dsum;       // [B, Hq, T]
-  const char* ktiles;      // [B, H, nt]
-  const char* vtiles;
-  const char* qtiles;      // [B, Hq, nt]
-  const char* dotiles;
+  float* bias;             // [B, H, 64 nst]: key biases in raw score units
+  float* nlse;             // [B, Hq, 32 nt]: -lse / scale (raw score units), -inf past the last token
+  float* nsum;             // [B, Hq, 32 nt]: -sum_d dout * out, 0 past the last token
+  float* part;             // [splits - 1] sets of (dk, dv [B, T, H, D], dalpha [B, T, H])
   float* o_out;
   float* lse_out;
-  float* dsum_out;
   float* dq;
   float* dk;
   float* dv;
   float* dalpha;
-  int B, T, H, g, w, nt, PB;
+  size_t part_stride;      // floats of one set
+  int B, T, H, g, w, nt, nst, PB, splits;
   float scale_log2;        // softmax scale * log2(e)
 };
+
+// Key bias log2(1 - alpha) / (scale * log2 e): in raw score units, so that
+// adding it to q.k and scaling gives log2 of the weight (-inf at alpha = 1).
+// Written per (sequence, head) in token order, 0 past the last token.
+__global__ __launch_bounds__(kThreads) void train_bias_kernel(TrainArgs a, bool backward) {
+  const int n = 64 * a.nst;
+  const int j = blockIdx.x * kThreads + threadIdx.x;
+  if (j >= n) return;
+  const int b = blockIdx.y / a.H, h = blockIdx.y % a.H;
+  float x = 0.f;
+  if (j < a.T) x = __log2f(1.0f - a.alpha[(static_cast<size_t>(b) * a.T + j) * a.H + h]) / a.scale_log2;
+  a.bias[static_cast<size_t>(blockIdx.y) * n + j] = x;
+  if (backward && j >= a.T && j < 32 * a.nt)   // rows past the last token weigh nothing
+    for (int i = 0; i < a.g; ++i) {
+      const size_t ni = (static_cast<size_t>(blockIdx.y) * a.g + i) * 32 * a.nt + j;
+      a.nlse[ni] = -INFINITY;
+      a.nsum[ni] = 0.f;
+    }
+}
 
 // Mask class of keys [j0, j1) for queries [q0, q1): 0 = every key older
 // than every query's window (bias log(1 - alpha)), 1 = every key inside every
@@ -179,25 +303,48 @@ __device__ inline int mask_class(int j0, int j1, int q0, int q1, int w, int T) {
   return 2;
 }
 
-// Key bias log2(1 - alpha) / (scale * log2 e): in raw score units, so that
-// adding it to q.k and scaling gives log2 of the weight (-inf at alpha = 1).
-__device__ inline float key_bias_raw(const TrainArgs& a, int b, int h, int j) {
-  if (j >= a.T) return 0.f;
-  const float al = a.alpha[(static_cast<size_t>(b) * a.T + j) * a.H + h];
-  return __log2f(1.0f - al) / a.scale_log2;
+// Scores of one 32-key tile for a wave's 32 columns, masked: register i of a
+// lane is key jt + 16 (i / 8) + 8 (lane / 32) + i % 8.  The bias of old keys
+// starts the accumulation (class 0; zeros otherwise); t < 0 (unused column)
+// hides every key of a mixed tile.
+__device__ inline f32x16 score_tile(int ktile, const float* bias, const float* zeros, const LaneAddresses& ad,
+                                    const u32x4 (&qf)[kKS], int cls, int jt, int t, int w, int hf) {
+  const float* c = (cls == 0 ? bias : zeros) + 8 * hf;
+  f32x16 s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(c + 16 * (i >> 1) + 4 * (i & 1));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[4 * i + e] = x[e];
+  }
+#pragma unroll
+  for (int x = 0; x < kKS; ++x) s = mfma(row_operand(ktile, ad, x), qf[x], s);
+  if (cls == 2) {
+    const int d = t - jt - 8 * hf;
+    f32x4 bv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      bv[i] = *reinterpret_cast<const f32x4*>(bias + 16 * (i >> 1) + 8 * hf + 4 * (i & 1));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int k = 16 * (i >> 3) + (i & 7);
+      s[i] = k > d ? -INFINITY : (k > d - w ? s[i] : s[i] + bv[i >> 2][i & 3]);
+    }
+  }
+  return s;
 }
 
 // ---------------------------------------------------------------------------
 // Forward.  Workgroup = (sequence b, KV head h, block of PB query positions);
 // columns are (position, query head) pairs, the g heads of a position
-// consecutive, 16 per MFMA column block (a position's heads may straddle two
-// blocks), NQ blocks per wave.  Key tiles 0 .. ceil(t1 / 32) - 1
-// (causal) are staged through LDS: K row part, V transposed part.
+// consecutive, 32 per wave (a position's heads may straddle two waves).  Key
+// tiles 0 .. ceil(t1 / 32) - 1 (causal) go through LDS two at a time, the next
+// two being copied while these are attended: one barrier per 64 keys.
 // ---------------------------------------------------------------------------
-template <int D, int NQ>
 __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
-  __shared__ __attribute__((aligned(16))) char tile_lds[2][D * 128];
-  __shared__ float bias_lds[2][32];
+  __shared__ __attribute__((aligned(256))) char tile_lds[2][kStage];   // [K tile | V tile] x 2
+  __shared__ __attribute__((aligned(16))) float bias_lds[2][64], zero_lds[32];
+  if (threadIdx.x < 32) zero_lds[threadIdx.x] = 0.f;
   const int2 wg = xcd_order();               // latest (longest) query blocks first
   const int bh = wg.y;
   const int b = bh / a.H, h = bh % a.H;
@@ -207,194 +354,120 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
   const int ntiles = (t1 + 31) >> 5;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, G = lane >> 4;
+  const int hf = lane >> 5;
   const int Hq = a.H * a.g;
 
-  int tcol[NQ];
-  u32x4 qf[NQ][D / 32];
+  const int col = wave * 32 + (lane & 31);
+  const int pl = col / a.g, qh = col % a.g;
+  const bool ok = pl < a.PB && t0 + pl < t1;
+  const int t = ok ? t0 + pl : -1;
+  const size_t row = (static_cast<size_t>(b) * a.T + (ok ? t : 0)) * Hq + h * a.g + qh;
+  u32x4 qf[kKS];
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const int col = (wave * NQ + qb) * 16 + r;
-    const int pl = col / a.g, qh = col % a.g;
-    const int t = t0 + pl;
-    const bool ok = (pl < a.PB) && (t < t1);
-    tcol[qb] = ok ? t : -1;
-    const uint16_t* qrow = a.q + ((static_cast<size_t>(b) * a.T + (ok ? t : 0)) * Hq + h * a.g + qh) * D;
-#pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2)
-      qf[qb][s2] = ok ? ld16(qrow + 32 * s2 + 8 * G) : u32x4{0u, 0u, 0u, 0u};
-  }
+  for (int x = 0; x < kKS; ++x)
+    qf[x] = ok ? ld16(a.q + row * kTrainD + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
 
-  constexpr int KP = D * 4 / kThreads;   // 16-byte slots per thread per part
-  const char* kt = a.ktiles + static_cast<size_t>(bh) * a.nt * (D * 128);
-  const char* vt = a.vtiles + static_cast<size_t>(bh) * a.nt * (D * 128) + D * 64;
-  u32x4 sk[KP], sv[KP];
-  float sb = 0.f;
-  auto stage_load = [&](int k) {
-#pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-      sk[m] = ld16(kt + static_cast<size_t>(k) * (D * 128) + P * 16);
-      sv[m] = ld16(vt + static_cast<size_t>(k) * (D * 128) + P * 16);
-    }
-    if (tid < 32) sb = key_bias_raw(a, b, h, 32 * k + tid);
-  };
-  auto stage_store = [&](int buf) {
-#pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-      st16(tile_lds[buf] + P * 16, sk[m]);
-      st16(tile_lds[buf] + D * 64 + P * 16, sv[m]);
-    }
-    if (tid < 32) bias_lds[buf][tid] = sb;
+  const uint32_t stride = a.H * kRowB;
+  LaneOffsets lo = lane_offsets(lane, stride);
+  const uint32_t tiles = lds_addr(tile_lds);
+  const LaneAddresses ad = lane_addresses(tiles, lo);
+  const char* kv = reinterpret_cast<const char*>((wave >> 1 ? a.v : a.k) + (static_cast<size_t>(b) * a.T * a.H + h) * kTrainD);
+  const float* bias = a.bias + static_cast<size_t>(bh) * 64 * a.nst;
+  auto issue = [&](int st, int buf) {
+    copy_tile(kv, 64 * st + 32 * (wave & 1), a.T, stride, lo, lane,
+              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+    if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
   };
 
-  f32x4 o[NQ][D / 16];
-  float m_ref[NQ], l_run[NQ];
+  f32x16 o[kDB];
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
+  for (int x = 0; x < kDB; ++x)
 #pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) o[qb][bb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_ref[qb] = kMInit;
-    l_run[qb] = 0.f;
-  }
+    for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
+  float m_ref = kMInit, l_run = 0.f;
   const float thr = kRescale / a.scale_log2;
   const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
 
-  stage_load(0);
-  stage_store(0);
-  __syncthreads();
-  for (int k = 0; k < ntiles; ++k) {
-    const int buf = k & 1;
-    if (k + 1 < ntiles) stage_load(k + 1);
-    const char* tl = tile_lds[buf];
-    u32x4 ka[D / 32], kb[D / 32], vt2[D / 16];
+  issue(0, 0);
+  auto attend = [&](int st, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    wait_copies();
+    __syncthreads();
+    if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
+    // 64 keys at a time: both tiles' scores, one maximum and (rare) rescale, the weights, both
+    // tiles' products (a second tile past the last is hidden: every key is after t)
+    constexpr int tl = buf * kStage;
+    f32x16 s[2];
 #pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2) {
-      ka[s2] = ld16(tl + s2 * 2048 + lane * 16);
-      kb[s2] = ld16(tl + s2 * 2048 + 1024 + lane * 16);
+    for (int sub = 0; sub < 2; ++sub) {
+      const int jt = 64 * st + 32 * sub;
+      s[sub] = score_tile(tl + 2 * kUnit * sub, &bias_lds[buf][32 * sub], zero_lds, ad, qf,
+                          mask_class(jt, jt + 32, t0, t1, a.w, a.T), jt, t, a.w, hf);
     }
+    float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) vt2[bb] = ld16(tl + D * 64 + bb * 1024 + lane * 16);
-    const int jt = 32 * k;
-    const int cls = mask_class(jt, jt + 32, t0, t1, a.w, a.T);
-    float kbias[8];
+    for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
+    mx = col_max(mx);
+    const bool raise = mx > m_ref + thr;
+    if (__builtin_amdgcn_ballot_w64(raise)) {
+      const float m_new = raise ? mx : m_ref;
+      const float alpha_s = __builtin_amdgcn_exp2f((m_ref - m_new) * a.scale_log2);
+      l_run *= alpha_s;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) kbias[j] = bias_lds[buf][8 * G + j];
+      for (int x = 0; x < kDB; ++x) o[x] *= alpha_s;
+      m_ref = m_new;
+    }
+    const float mb = m_ref * a.scale_log2;
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s2 = 0; s2 < D / 32; ++s2) {
-        s0 = mfma_bf16(ka[s2], qf[qb][s2], s0);
-        s1 = mfma_bf16(kb[s2], qf[qb][s2], s1);
-      }
-      float sc[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        sc[j] = s0[j];
-        sc[j + 4] = s1[j];
-      }
-      if (cls == 0) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sc[j] += kbias[j];
-      } else if (cls == 2) {
-        const int t = tcol[qb];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int key = jt + 8 * G + j;
-          sc[j] = key > t ? -INFINITY : (key > t - a.w ? sc[j] : sc[j] + kbias[j]);
-        }
-      }
-      float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])),
-                       fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-      mx = col_max(mx);
-      const bool raise = mx > m_ref[qb] + thr;
-      if (__builtin_amdgcn_ballot_w64(raise)) {
-        const float m_new = raise ? mx : m_ref[qb];
-        const float alpha_s = __builtin_amdgcn_exp2f((m_ref[qb] - m_new) * a.scale_log2);
-        l_run[qb] *= alpha_s;
-#pragma unroll
-        for (int bb = 0; bb < D / 16; ++bb) o[qb][bb] *= alpha_s;
-        m_ref[qb] = m_new;
-      }
-      const float mb = m_ref[qb] * a.scale_log2;
-      float e[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) e[j] = __builtin_amdgcn_exp2f(fmaf(sc[j], a.scale_log2, -mb));
+    for (int sub = 0; sub < 2; ++sub) {
       // the denominator adds the bf16-rounded weights the MFMA uses (dot
       // with (1, 1) on each packed pair as it is made)
-      u32x4 pu;
+      u32x4 pu[2];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x2 pr = {e[2 * j], e[2 * j + 1]};
+      for (int j = 0; j < 8; ++j) {
+        const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[sub][2 * j], a.scale_log2, -mb)),
+                          __builtin_amdgcn_exp2f(fmaf(s[sub][2 * j + 1], a.scale_log2, -mb))};
         const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
-        pu[j] = __builtin_bit_cast(uint32_t, pb);
-        l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run[qb], false);
+        pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
+        l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
       }
 #pragma unroll
-      for (int bb = 0; bb < D / 16; ++bb) o[qb][bb] = mfma_bf16(vt2[bb], pu, o[qb][bb]);
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int x = 0; x < kDB; ++x) o[x] = mfma(col_operand(tl + 2 * kUnit * sub + kUnit, ad, x, y), pu[y], o[x]);
     }
-    if (k + 1 < ntiles) stage_store(buf ^ 1);
-    __syncthreads();
+  };
+  for (int st = 0; 2 * st < ntiles; st += 2) {
+    attend(st, std::integral_constant<int, 0>{});
+    if (2 * st + 2 < ntiles) attend(st + 1, std::integral_constant<int, 1>{});
   }
 
+  const float l = col_sum(l_run);
+  if (ok) {
+    float* dst = a.o_out + row * kTrainD + 4 * hf;
+    const float inv = 1.0f / l;
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const float l = col_sum(l_run[qb]);
-    const int t = tcol[qb];
-    if (t >= 0) {
-      const int qh = ((wave * NQ + qb) * 16 + r) % a.g;
-      float* dst = a.o_out + ((static_cast<size_t>(b) * a.T + t) * Hq + h * a.g + qh) * D + 4 * G;
-      const float inv = 1.0f / l;
+    for (int x = 0; x < kDB; ++x)
 #pragma unroll
-      for (int bb = 0; bb < D / 16; ++bb) *reinterpret_cast<f32x4*>(dst + 16 * bb) = o[qb][bb] * inv;
-      if (G == 0)
-        a.lse_out[(static_cast<size_t>(b) * Hq + h * a.g + qh) * a.T + t] =
-            (m_ref[qb] * a.scale_log2 + __log2f(l)) * kLn2;
-    }
-  }
-}
-
-// D = sum_d dout * out for every (b, query head, t); 16 lanes per row.
-__global__ __launch_bounds__(kThreads) void train_rowsum_kernel(TrainArgs a, int D) {
-  const int Hq = a.H * a.g;
-  const int64_t rows = static_cast<int64_t>(a.B) * a.T * Hq;
-  const int64_t row = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) >> 4;
-  const int sub = threadIdx.x & 15;
-  float s = 0.f;
-  if (row < rows) {
-    for (int e = sub * 8; e < D; e += 128) {
-      const u32x4 d8 = ld16(a.dout + row * D + e);
-      const f32x4 o0 = *reinterpret_cast<const f32x4*>(a.out + row * D + e);
-      const f32x4 o1 = *reinterpret_cast<const f32x4*>(a.out + row * D + e + 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float lo = __uint_as_float(d8[i] << 16), hi = __uint_as_float(d8[i] & 0xFFFF0000u);
-        s += lo * (i < 2 ? o0[2 * i] : o1[2 * i - 4]) + hi * (i < 2 ? o0[2 * i + 1] : o1[2 * i - 3]);
-      }
-    }
-  }
-#pragma unroll
-  for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 16);
-  if (row < rows && sub == 0) {
-    // row = (b * T + t) * Hq + qh  ->  dsum[(b * Hq + qh) * T + t]
-    const int qh = static_cast<int>(row % Hq);
-    const int64_t bt = row / Hq;
-    const int t = static_cast<int>(bt % a.T), bb = static_cast<int>(bt / a.T);
-    a.dsum_out[(static_cast<size_t>(bb) * Hq + qh) * a.T + t] = s;
+      for (int y = 0; y < 4; ++y)
+        *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
+            f32x4{o[x][4 * y], o[x][4 * y + 1], o[x][4 * y + 2], o[x][4 * y + 3]} * inv;
+    if (hf == 0)
+      a.lse_out[(static_cast<size_t>(b) * Hq + h * a.g + qh) * a.T + t] =
+          (m_ref * a.scale_log2 + __log2f(l)) * kLn2;
   }
 }
 
 // ---------------------------------------------------------------------------
-// dQ pass.  Same workgroups and columns as the forward.  Per key tile: K row
-// part (S^T = K Q^T), V row part (dP^T = V dO^T), K transposed part
-// (dQ^T += K^T dS^T).
+// dQ pass.  Same workgroups and columns as the forward; it also forms each
+// row's sum of dout * out and hands that and lse, negated and in the units
+// that start the key-major pass's products, to that pass.  Per key tile:
+// S^T = K Q^T and dP^T = V dO^T over rows, dQ^T += K^T dS^T over columns.
 // ---------------------------------------------------------------------------
-template <int D, int NQ>
-__global__ __launch_bounds__(kThreads, 1) void train_dq_kernel(TrainArgs a) {
-  __shared__ __attribute__((aligned(16))) char tile_lds[2][D * 192];
-  __shared__ float bias_lds[2][32];
+__global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
+  __shared__ __attribute__((aligned(256))) char tile_lds[2][kStage];
+  __shared__ __attribute__((aligned(16))) float bias_lds[2][64], zero_lds[32];
+  if (threadIdx.x < 32) zero_lds[threadIdx.x] = 0.f;
   const int2 wg = xcd_order();
   const int bh = wg.y;
   const int b = bh / a.H, h = bh % a.H;
@@ -404,314 +477,350 @@ __global__ __launch_bounds__(kThreads, 1) void train_dq_kernel(TrainArgs a) {
   const int ntiles = (t1 + 31) >> 5;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, G = lane >> 4;
+  const int hf = lane >> 5;
   const int Hq = a.H * a.g;
 
-  int tcol[NQ];
-  u32x4 qf[NQ][D / 32], df[NQ][D / 32];
-  float lse2[NQ], dcol[NQ];
+  const int col = wave * 32 + (lane & 31);
+  const int pl = col / a.g, qh = col % a.g;
+  const bool ok = pl < a.PB && t0 + pl < t1;
+  const int t = ok ? t0 + pl : -1;
+  const size_t row = (static_cast<size_t>(b) * a.T + (ok ? t : 0)) * Hq + h * a.g + qh;
+
+  const uint32_t stride = a.H * kRowB;
+  LaneOffsets lo = lane_offsets(lane, stride);
+  const uint32_t tiles = lds_addr(tile_lds);
+  const LaneAddresses ad = lane_addresses(tiles, lo);
+  const char* kv = reinterpret_cast<const char*>((wave >> 1 ? a.v : a.k) + (static_cast<size_t>(b) * a.T * a.H + h) * kTrainD);
+  const float* bias = a.bias + static_cast<size_t>(bh) * 64 * a.nst;
+  auto issue = [&](int st, int buf) {
+    copy_tile(kv, 64 * st + 32 * (wave & 1), a.T, stride, lo, lane,
+              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+    if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
+  };
+  issue(0, 0);
+
+  u32x4 qf[kKS], df[kKS];
+  float dcol = 0.f;
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const int col = (wave * NQ + qb) * 16 + r;
-    const int pl = col / a.g, qh = col % a.g;
-    const int t = t0 + pl;
-    const bool ok = (pl < a.PB) && (t < t1);
-    tcol[qb] = ok ? t : -1;
-    const size_t row = (static_cast<size_t>(b) * a.T + (ok ? t : 0)) * Hq + h * a.g + qh;
+  for (int x = 0; x < kKS; ++x) {
+    qf[x] = ok ? ld16(a.q + row * kTrainD + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
+    df[x] = ok ? ld16(a.dout + row * kTrainD + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
+    if (ok) {
+      const f32x4 o0 = *reinterpret_cast<const f32x4*>(a.out + row * kTrainD + 16 * x + 8 * hf);
+      const f32x4 o1 = *reinterpret_cast<const f32x4*>(a.out + row * kTrainD + 16 * x + 8 * hf + 4);
 #pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2) {
-      qf[qb][s2] = ok ? ld16(a.q + row * D + 32 * s2 + 8 * G) : u32x4{0u, 0u, 0u, 0u};
-      df[qb][s2] = ok ? ld16(a.dout + row * D + 32 * s2 + 8 * G) : u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < 4; ++i) {
+        const float lof = __uint_as_float(df[x][i] << 16), hif = __uint_as_float(df[x][i] & 0xFFFF0000u);
+        dcol += lof * (i < 2 ? o0[2 * i] : o1[2 * i - 4]) + hif * (i < 2 ? o0[2 * i + 1] : o1[2 * i - 3]);
+      }
     }
-    const size_t li = (static_cast<size_t>(b) * Hq + h * a.g + qh) * a.T + (ok ? t : 0);
-    lse2[qb] = ok ? a.lse[li] * kLog2e : 0.f;
-    dcol[qb] = ok ? a.dsum[li] : 0.f;
+  }
+  dcol = col_sum(dcol);
+  float lse2 = 0.f;
+  if (ok) {
+    const size_t li = (static_cast<size_t>(b) * Hq + h * a.g + qh) * a.T + t;
+    lse2 = a.lse[li] * kLog2e;
+    if (hf == 0) {
+      const size_t ni = (static_cast<size_t>(b) * Hq + h * a.g + qh) * 32 * a.nt + t;
+      a.nlse[ni] = -lse2 / a.scale_log2;
+      a.nsum[ni] = -dcol;
+    }
   }
 
-  constexpr int KP = D * 4 / kThreads;
-  const char* kt = a.ktiles + static_cast<size_t>(bh) * a.nt * (D * 128);
-  const char* vt = a.vtiles + static_cast<size_t>(bh) * a.nt * (D * 128);
-  u32x4 sk[KP], sv[KP], skt[KP];
-  float sb = 0.f;
-  auto stage_load = [&](int k) {
-    const size_t off = static_cast<size_t>(k) * (D * 128);
+  f32x16 dqa[kDB];
 #pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-      sk[m] = ld16(kt + off + P * 16);
-      sv[m] = ld16(vt + off + P * 16);
-      skt[m] = ld16(kt + off + D * 64 + P * 16);
-    }
-    if (tid < 32) sb = key_bias_raw(a, b, h, 32 * k + tid);
-  };
-  auto stage_store = [&](int buf) {
+  for (int x = 0; x < kDB; ++x)
 #pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-      st16(tile_lds[buf] + P * 16, sk[m]);
-      st16(tile_lds[buf] + D * 64 + P * 16, sv[m]);
-      st16(tile_lds[buf] + D * 128 + P * 16, skt[m]);
-    }
-    if (tid < 32) bias_lds[buf][tid] = sb;
-  };
+    for (int i = 0; i < 16; ++i) dqa[x][i] = 0.f;
 
-  f32x4 dqa[NQ][D / 16];
+  // -D in every row starts the dP products
+  f32x16 neg_d;
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) dqa[qb][bb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  stage_load(0);
-  stage_store(0);
-  __syncthreads();
-  for (int k = 0; k < ntiles; ++k) {
-    const int buf = k & 1;
-    if (k + 1 < ntiles) stage_load(k + 1);
-    const char* tl = tile_lds[buf];
-    u32x4 ka[D / 32], kb[D / 32], va[D / 32], vb[D / 32], ktr[D / 16];
-#pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2) {
-      ka[s2] = ld16(tl + s2 * 2048 + lane * 16);
-      kb[s2] = ld16(tl + s2 * 2048 + 1024 + lane * 16);
-      va[s2] = ld16(tl + D * 64 + s2 * 2048 + lane * 16);
-      vb[s2] = ld16(tl + D * 64 + s2 * 2048 + 1024 + lane * 16);
-    }
-#pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) ktr[bb] = ld16(tl + D * 128 + bb * 1024 + lane * 16);
-    const int jt = 32 * k;
-    const int cls = mask_class(jt, jt + 32, t0, t1, a.w, a.T);
-    float kbias[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) kbias[j] = bias_lds[buf][8 * G + j];
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, p0 = s0, p1 = s0;
-#pragma unroll
-      for (int s2 = 0; s2 < D / 32; ++s2) {
-        s0 = mfma_bf16(ka[s2], qf[qb][s2], s0);
-        s1 = mfma_bf16(kb[s2], qf[qb][s2], s1);
-        p0 = mfma_bf16(va[s2], df[qb][s2], p0);
-        p1 = mfma_bf16(vb[s2], df[qb][s2], p1);
-      }
-      float sc[8], dp[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        sc[j] = s0[j];
-        sc[j + 4] = s1[j];
-        dp[j] = p0[j];
-        dp[j + 4] = p1[j];
-      }
-      if (cls == 0) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sc[j] += kbias[j];
-      } else if (cls == 2) {
-        const int t = tcol[qb];   // -1 for unused columns: every key is masked
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int key = jt + 8 * G + j;
-          sc[j] = key > t ? -INFINITY : (key > t - a.w ? sc[j] : sc[j] + kbias[j]);
-        }
-      }
-      float ds[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[j], a.scale_log2, -lse2[qb]));
-        ds[j] = p * (dp[j] - dcol[qb]);
-      }
-      const u32x4 du = pack_bf16(ds);
-#pragma unroll
-      for (int bb = 0; bb < D / 16; ++bb) dqa[qb][bb] = mfma_bf16(ktr[bb], du, dqa[qb][bb]);
-    }
-    if (k + 1 < ntiles) stage_store(buf ^ 1);
+  for (int i = 0; i < 16; ++i) neg_d[i] = -dcol;
+  auto attend = [&](int st, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    wait_copies();
     __syncthreads();
+    if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {   // a second tile past the last is hidden: every key is after t
+      const int jt = 64 * st + 32 * sub;
+      constexpr int t_buf = buf * kStage;
+      const int tl = t_buf + 2 * kUnit * sub;
+      f32x16 s = score_tile(tl, &bias_lds[buf][32 * sub], zero_lds, ad, qf,
+                            mask_class(jt, jt + 32, t0, t1, a.w, a.T), jt, t, a.w, hf);
+      f32x16 dp = mfma(row_operand(tl + kUnit, ad, 0), df[0], neg_d);
+#pragma unroll
+      for (int x = 1; x < kKS; ++x) dp = mfma(row_operand(tl + kUnit, ad, x), df[x], dp);
+      float ds[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(fmaf(s[i], a.scale_log2, -lse2)) * dp[i];
+      const u32x4 du[2] = {pack_bf16(ds), pack_bf16(ds + 8)};
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int x = 0; x < kDB; ++x) dqa[x] = mfma(col_operand(tl, ad, x, y), du[y], dqa[x]);
+    }
+  };
+  for (int st = 0; 2 * st < ntiles; st += 2) {
+    attend(st, std::integral_constant<int, 0>{});
+    if (2 * st + 2 < ntiles) attend(st + 1, std::integral_constant<int, 1>{});
   }
 
   const float scale = a.scale_log2 / kLog2e;
+  if (ok) {
+    float* dst = a.dq + row * kTrainD + 4 * hf;
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const int t = tcol[qb];
-    if (t >= 0) {
-      const int qh = ((wave * NQ + qb) * 16 + r) % a.g;
-      float* dst = a.dq + ((static_cast<size_t>(b) * a.T + t) * Hq + h * a.g + qh) * D + 4 * G;
+    for (int x = 0; x < kDB; ++x)
 #pragma unroll
-      for (int bb = 0; bb < D / 16; ++bb) *reinterpret_cast<f32x4*>(dst + 16 * bb) = dqa[qb][bb] * scale;
-    }
+      for (int y = 0; y < 4; ++y)
+        *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
+            f32x4{dqa[x][4 * y], dqa[x][4 * y + 1], dqa[x][4 * y + 2], dqa[x][4 * y + 3]} * scale;
   }
 }
 
 // ---------------------------------------------------------------------------
-// dK / dV / dalpha pass.  Workgroup = (b, KV head h, 64 keys); wave w owns
-// keys j0 + 16 w .. + 15 as the 16 columns of its MFMAs, with those keys' K
-// and V (B operands) in registers.  It walks every query head of the group
-// and every 32-position query tile from the block's first key on (the last
-// tile first); per tile the Q and dO tiles (row and transposed parts), lse and
-// D are staged.
+// dK / dV / dalpha pass.  Workgroup = (b, KV head h, 128 keys, share of the
+// steps); wave w owns keys j0 + 32 w .. + 31 as the 32 columns of its MFMAs,
+// with those keys' K and V (B operands) in registers: a row or column operand
+// read from LDS feeds 32 columns.  It walks every query head of the group and
+// every 32-position query tile from the block's first key on, the last tile
+// first (the blocks of one (sequence, head) that run together read the same
+// tile at about the same time); two (tile, head) steps are staged at a time.
+// Query tiles that are entirely past a key's window come first and add
+// without the factor 1 - alpha, which is applied once to the sums where the
+// walk leaves them; -lse and -sum dout out start the products' accumulators.
+// When the call has too few blocks to fill the chip, each block's steps are
+// split over `splits` workgroups whose sums train_sum_kernel adds in order:
+// 1777 tokens of 2 x 6 heads, 518 us with one workgroup of 64 keys per block,
+// 83 + 8 us with six of 128.  Both loops hold 256 registers without a spill
+// only when a step's products and its element-wise part are kept apart and not
+// unrolled over the two steps; a reload from scratch waits for every copy in
+// flight (4400 us against 2600 us).
 // ---------------------------------------------------------------------------
-template <int D>
 __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
-  __shared__ __attribute__((aligned(16))) char tile_lds[2][D * 256];
-  __shared__ __attribute__((aligned(16))) float row_lds[2][2][32];   // lse (log2 units), D per row
+  __shared__ __attribute__((aligned(256))) char tile_lds[2][kStage];                 // [Q tile | dO tile] x 2
+  __shared__ __attribute__((aligned(16))) float row_lds[2][2][2][32];   // [step][-lse / scale, -sum][row]
   const int2 wg = xcd_order();               // earliest (longest) key blocks first
   const int bh = wg.y;
   const int b = bh / a.H, h = bh % a.H;
-  const int j0 = wg.x * 64;
-  if (j0 >= a.T) return;
+  const int split = wg.x % a.splits;
+  const int j0 = wg.x / a.splits * 128;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, G = lane >> 4;
+  const int hf = lane >> 5;
   const int Hq = a.H * a.g;
-  const int j = j0 + 16 * wave + r;          // this lane's key
+  const int jw = j0 + 32 * wave;             // this wave's keys jw .. jw + 31
+  const int j = jw + (lane & 31);            // this lane's key
   const bool jok = j < a.T;
+  const size_t krow = (static_cast<size_t>(b) * a.T + (jok ? j : 0)) * a.H + h;
 
-  u32x4 kf[D / 32], vf[D / 32];
-  {
-    const size_t row = (static_cast<size_t>(b) * a.T + (jok ? j : 0)) * a.H + h;
-#pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2) {
-      kf[s2] = jok ? ld16(a.k + row * D + 32 * s2 + 8 * G) : u32x4{0u, 0u, 0u, 0u};
-      vf[s2] = jok ? ld16(a.v + row * D + 32 * s2 + 8 * G) : u32x4{0u, 0u, 0u, 0u};
+  // steps first .. last - 1 of the block's list: (query tile, query head) pairs
+  const int total = a.g * (a.nt - (j0 >> 5));
+  const int first = static_cast<int>(static_cast<int64_t>(total) * split / a.splits);
+  const int last = static_cast<int>(static_cast<int64_t>(total) * (split + 1) / a.splits);
+  const int nst = (last - first + 1) >> 1;
+
+  const uint32_t stride = Hq * kRowB;
+  LaneOffsets lo = lane_offsets(lane, stride);
+  const uint32_t tiles = lds_addr(tile_lds);
+  const uint16_t* src = wave >> 1 ? a.dout : a.q;
+  // this wave copies tensor wave / 2 of step 2 st + wave % 2
+  int ld_step = first + (wave & 1);
+  int ld_qh = ld_step % a.g, ld_tile = a.nt - 1 - ld_step / a.g;
+  auto issue = [&](int buf) {
+    if (ld_step < last) {
+      const size_t hq = h * a.g + ld_qh;
+      copy_tile(reinterpret_cast<const char*>(src + (static_cast<size_t>(b) * a.T * Hq + hq) * kTrainD), 32 * ld_tile,
+                a.T, stride, lo, lane, tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+      if (wave < 2) {
+        const int ln = fresh(lane);
+        const uint32_t off = 4 * (32 * ld_tile + (ln & 31));
+        const float* rows = a.nlse + (static_cast<size_t>(b) * Hq + hq) * 32 * a.nt;
+        lds_copy4(rows, off + (ln >= 32 ? static_cast<uint32_t>(reinterpret_cast<const char*>(a.nsum) -
+                                                          reinterpret_cast<const char*>(a.nlse)) : 0u),
+                  lds_addr(row_lds[buf][wave & 1]));
+      }
     }
-  }
-  const float al = jok ? a.alpha[(static_cast<size_t>(b) * a.T + j) * a.H + h] : 0.f;
-  const float keep = 1.0f - al;              // weight of the key outside the window
-  f32x4 dka[D / 16], dva[D / 16];
+    ld_step += 2;
+    ld_qh += 2;
+    while (ld_qh >= a.g) {
+      ld_qh -= a.g;
+      --ld_tile;
+    }
+  };
+  issue(0);
+
+  u32x4 kf[kKS], vf[kKS];
 #pragma unroll
-  for (int bb = 0; bb < D / 16; ++bb) {
-    dka[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    dva[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int x = 0; x < kKS; ++x) {
+    kf[x] = jok ? ld16(a.k + krow * kTrainD + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
+    vf[x] = jok ? ld16(a.v + krow * kTrainD + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
   }
+  const float keep = 1.0f - (jok ? a.alpha[krow] : 0.f);   // weight of the key outside the window
+  f32x16 dka[kDB], dva[kDB];
+#pragma unroll
+  for (int x = 0; x < kDB; ++x)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dka[x][i] = dva[x][i] = 0.f;
   float dal = 0.f;
 
-  const int pt0 = j0 >> 5;
-  const int nsteps = a.g * (a.nt - pt0);     // (query tile, query head) pairs
-  constexpr int KP = D * 4 / kThreads;
-  // Two register sets: the tiles of step s + 2 are loaded while step s is
-  // computed, and step s + 1's are written to LDS at its end.
-  u32x4 ra[4][KP], rb[4][KP];
-  float rowa = 0.f, rowb = 0.f;
-  // steps walk the query tiles from the last one down, every query head of
-  // the group per tile: the blocks of one (sequence, head) that run together
-  // read the same tile at about the same time
-  int ld_qh = 0, ld_pt = a.nt - 1;           // next step to load
-  auto stage_load = [&](u32x4 (&rg)[4][KP], float& row) {
-    const size_t tix = (static_cast<size_t>(b) * Hq + h * a.g + ld_qh) * a.nt + ld_pt;
-    const char* qt = a.qtiles + tix * (D * 128);
-    const char* dt = a.dotiles + tix * (D * 128);
+  // scores and dP of the step staged at `tl`, started from its rows' -lse and -sum
+  auto products = [&](uint32_t tl, const float* rows, f32x16& s, f32x16& dp) {
 #pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-      rg[0][m] = ld16(qt + P * 16);
-      rg[1][m] = ld16(qt + D * 64 + P * 16);
-      rg[2][m] = ld16(dt + P * 16);
-      rg[3][m] = ld16(dt + D * 64 + P * 16);
-    }
-    if (tid < 64) {
-      const int t = 32 * ld_pt + (tid & 31);
-      const size_t li = (static_cast<size_t>(b) * Hq + h * a.g + ld_qh) * a.T + t;
-      row = t < a.T ? (tid < 32 ? a.lse[li] * kLog2e : a.dsum[li]) : 0.f;
-    }
-    if (++ld_qh == a.g) {
-      ld_qh = 0;
-      --ld_pt;
-    }
-  };
-  auto stage_store = [&](int buf, const u32x4 (&rg)[4][KP], float row) {
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 l = *reinterpret_cast<const f32x4*>(rows + 16 * (i >> 1) + 8 * hf + 4 * (i & 1));
+      const f32x4 d = *reinterpret_cast<const f32x4*>(rows + 32 + 16 * (i >> 1) + 8 * hf + 4 * (i & 1));
 #pragma unroll
-    for (int m = 0; m < KP; ++m) {
-      const int P = tid + m * kThreads;
-#pragma unroll
-      for (int part = 0; part < 4; ++part) st16(tile_lds[buf] + part * (D * 64) + P * 16, rg[part][m]);
-    }
-    if (tid < 64) row_lds[buf][tid >> 5][tid & 31] = row;
-  };
-
-  int step_qh = 0, tq = 32 * (a.nt - 1);     // step being computed
-  auto compute = [&](int buf) {
-    const char* tl = tile_lds[buf];
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, p0 = s0, p1 = s0;
-#pragma unroll
-    for (int s2 = 0; s2 < D / 32; ++s2) {
-      const u32x4 qa = ld16(tl + s2 * 2048 + lane * 16);
-      const u32x4 qb = ld16(tl + s2 * 2048 + 1024 + lane * 16);
-      const u32x4 da = ld16(tl + D * 128 + s2 * 2048 + lane * 16);
-      const u32x4 db = ld16(tl + D * 128 + s2 * 2048 + 1024 + lane * 16);
-      s0 = mfma_bf16(qa, kf[s2], s0);
-      s1 = mfma_bf16(qb, kf[s2], s1);
-      p0 = mfma_bf16(da, vf[s2], p0);
-      p1 = mfma_bf16(db, vf[s2], p1);
-    }
-    // lane (key r, G) now holds rows (queries) tq + 8 G + i, i = 0..7
-    const f32x4 l2a = *reinterpret_cast<const f32x4*>(&row_lds[buf][0][8 * G]);
-    const f32x4 l2b = *reinterpret_cast<const f32x4*>(&row_lds[buf][0][8 * G + 4]);
-    const f32x4 dda = *reinterpret_cast<const f32x4*>(&row_lds[buf][1][8 * G]);
-    const f32x4 ddb = *reinterpret_cast<const f32x4*>(&row_lds[buf][1][8 * G + 4]);
-    const int cls = mask_class(j0, j0 + 64, tq, tq + 32, a.w, a.T);
-    float pr[8], ds[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float raw = i < 4 ? s0[i] : s1[i - 4];
-      const float dpd = (i < 4 ? p0[i] : p1[i - 4]) - (i < 4 ? dda[i] : ddb[i - 4]);
-      const float l2 = i < 4 ? l2a[i] : l2b[i - 4];
-      const float pu = __builtin_amdgcn_exp2f(fmaf(raw, a.scale_log2, -l2));   // exp(s - lse) w/o bias
-      float p;
-      bool old;
-      if (cls == 0) {
-        p = pu * keep;
-        old = true;
-      } else if (cls == 1) {
-        p = pu;
-        old = false;
-      } else {
-        const int t = tq + 8 * G + i;
-        const bool vis = j <= t && t < a.T && jok;
-        old = vis && j <= t - a.w;
-        p = vis ? (old ? pu * keep : pu) : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        s[4 * i + e] = l[e];
+        dp[4 * i + e] = d[e];
       }
-      pr[i] = p;
-      ds[i] = p * dpd;
-      if (old) dal = fmaf(pu, dpd, dal);
     }
-    const u32x4 pu8 = pack_bf16(pr);
-    const u32x4 du8 = pack_bf16(ds);
 #pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) {
-      dva[bb] = mfma_bf16(ld16(tl + D * 192 + bb * 1024 + lane * 16), pu8, dva[bb]);
-      dka[bb] = mfma_bf16(ld16(tl + D * 64 + bb * 1024 + lane * 16), du8, dka[bb]);
+    for (int x = 0; x < kKS; ++x) s = mfma(row_operand(tl, lo, x), kf[x], s);
+#pragma unroll
+    for (int x = 0; x < kKS; ++x) dp = mfma(row_operand(tl + kUnit, lo, x), vf[x], dp);
+    paced<10, 2 * kKS, 1>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // dV^T += dO^T P, dK^T += Q^T dS with P, dS rounded to bf16
+  auto sums = [&](uint32_t tl, const f32x16& s, const f32x16& dp) {
+    float p[16], ds[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      p[i] = s[i];
+      ds[i] = dp[i];
     }
-    if (++step_qh == a.g) {
-      step_qh = 0;
-      tq -= 32;
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const u32x4 pu = pack_bf16(p + 8 * y), du = pack_bf16(ds + 8 * y);
+#pragma unroll
+      for (int x = 0; x < kDB; ++x) {
+        dva[x] = mfma(col_operand(tl + kUnit, lo, x, y), pu, dva[x]);
+        dka[x] = mfma(col_operand(tl, lo, x, y), du, dka[x]);
+      }
     }
+    paced<4, 4 * kDB, 2>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto publish = [&](int st) {   // stage st is in LDS for every wave; copy the next one
+    wait_copies();
+    __syncthreads();
+    if (st + 1 < nst) issue((st & 1) ^ 1);
   };
 
-  stage_load(ra, rowa);
-  if (nsteps > 1) stage_load(rb, rowb);
-  stage_store(0, ra, rowa);
-  __syncthreads();
-  for (int step = 0; step < nsteps; step += 2) {
-    if (step + 2 < nsteps) stage_load(ra, rowa);
-    compute(0);
-    if (step + 1 < nsteps) stage_store(1, rb, rowb);
-    __syncthreads();
-    if (step + 1 >= nsteps) break;
-    if (step + 3 < nsteps) stage_load(rb, rowb);
-    compute(1);
-    if (step + 2 < nsteps) stage_store(0, ra, rowa);
-    __syncthreads();
+  int step_qh = first % a.g, tq = 32 * (a.nt - 1 - first / a.g);   // step being computed
+  int st = 0;
+  // ---- stages whose queries are all past the window of each of this wave's keys
+  for (; st < nst && tq - (step_qh + 1 >= a.g ? 32 : 0) - a.w >= jw + 31 && first + 2 * st + 1 < last; ++st) {
+    publish(st);
+#pragma unroll 1
+    for (int sub = 0; sub < 2; ++sub) {
+      const uint32_t tl = tiles + (st & 1) * kStage + 2 * kUnit * sub;
+      refresh(lo);
+      f32x16 s, dp;
+      products(tl, &row_lds[st & 1][sub][0][0], s, dp);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        s[i] = __builtin_amdgcn_exp2f(s[i] * a.scale_log2);   // exp(s - lse), no bias
+        dp[i] *= s[i];
+        dal += dp[i];
+      }
+      sums(tl, s, dp);
+      if (++step_qh == a.g) {
+        step_qh = 0;
+        tq -= 32;
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < kDB; ++x) {
+    dka[x] *= keep;
+    dva[x] *= keep;
+  }
+  // ---- the rest, masked per element
+  for (; st < nst; ++st) {
+    publish(st);
+#pragma unroll 1
+    for (int sub = 0; sub < 2; ++sub) {
+      if (first + 2 * st + sub >= last) break;
+      if (tq + 31 >= jw) {                   // else every query precedes every key
+        const uint32_t tl = tiles + (st & 1) * kStage + 2 * kUnit * sub;
+        refresh(lo);
+        f32x16 s, dp;
+        products(tl, &row_lds[st & 1][sub][0][0], s, dp);
+        // register i of the lane: query tq + 16 (i / 8) + 8 hf + i % 8; it sees the lane's key
+        // from c = d on and is past the key's window from c = d + w on
+        const int ln = fresh(lane);
+        const int d = jw + (ln & 31) - tq - 8 * (ln >> 5);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int c = 16 * (i >> 3) + (i & 7);
+          s[i] = d <= c ? __builtin_amdgcn_exp2f(s[i] * a.scale_log2) : 0.f;
+          dp[i] *= s[i];
+          const bool old = d <= c - a.w;
+          dal += old ? dp[i] : 0.f;
+          const float f = old ? keep : 1.0f;
+          s[i] *= f;
+          dp[i] *= f;
+        }
+        sums(tl, s, dp);
+      }
+      if (++step_qh == a.g) {
+        step_qh = 0;
+        tq -= 32;
+      }
+    }
   }
 
   dal = col_sum(dal);
-  if (jok) {
+  const int je = jw + (fresh(lane) & 31);
+  if (je < a.T) {
+    const size_t krow = (static_cast<size_t>(b) * a.T + je) * a.H + h;
     const float scale = a.scale_log2 / kLog2e;
-    const size_t row = (static_cast<size_t>(b) * a.T + j) * a.H + h;
-    float* dkd = a.dk + row * D + 4 * G;
-    float* dvd = a.dv + row * D + 4 * G;
-#pragma unroll
-    for (int bb = 0; bb < D / 16; ++bb) {
-      *reinterpret_cast<f32x4*>(dkd + 16 * bb) = dka[bb] * scale;
-      *reinterpret_cast<f32x4*>(dvd + 16 * bb) = dva[bb];
+    float *dk = a.dk, *dv = a.dv, *dal_out = a.dalpha;
+    if (split) {
+      const size_t kv = static_cast<size_t>(a.B) * a.T * a.H * kTrainD;
+      dk = a.part + (split - 1) * a.part_stride;
+      dv = dk + kv;
+      dal_out = dv + kv;
     }
-    if (G == 0) a.dalpha[row] = -dal;
+    dk += krow * kTrainD + 4 * hf;
+    dv += krow * kTrainD + 4 * hf;
+#pragma unroll
+    for (int x = 0; x < kDB; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        *reinterpret_cast<f32x4*>(dk + 32 * x + 8 * y) =
+            f32x4{dka[x][4 * y], dka[x][4 * y + 1], dka[x][4 * y + 2], dka[x][4 * y + 3]} * scale;
+        *reinterpret_cast<f32x4*>(dv + 32 * x + 8 * y) =
+            f32x4{dva[x][4 * y], dva[x][4 * y + 1], dva[x][4 * y + 2], dva[x][4 * y + 3]};
+      }
+    if (hf == 0) dal_out[krow] = -dal;
+  }
+}
+
+// Adds the other workgroups' sums of a split key-major pass to the outputs,
+// in split order.
+__global__ __launch_bounds__(kThreads) void train_sum_kernel(TrainArgs a) {
+  const size_t rows = static_cast<size_t>(a.B) * a.T * a.H, kv = rows * kTrainD;
+  const size_t i = (static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x) * 4;
+  if (i >= 2 * kv + rows) return;
+  auto add = [&](float* dst, int n) {
+    float x[4];
+    for (int e = 0; e < n; ++e) x[e] = dst[e];
+    for (int sp = 1; sp < a.splits; ++sp)
+      for (int e = 0; e < n; ++e) x[e] += a.part[(sp - 1) * a.part_stride + i + e];
+    for (int e = 0; e < n; ++e) dst[e] = x[e];
+  };
+  if (i < 2 * kv) {   // rows of 128 floats: four at a time never straddle the two tensors
+    float* dst = i < kv ? a.dk + i : a.dv + (i - kv);
+    f32x4 x = *reinterpret_cast<const f32x4*>(dst);
+    for (int sp = 1; sp < a.splits; ++sp) x += *reinterpret_cast<const f32x4*>(a.part + (sp - 1) * a.part_stride + i);
+    *reinterpret_cast<f32x4*>(dst) = x;
+  } else {
+    add(a.dalpha + (i - 2 * kv), static_cast<int>(min(static_cast<size_t>(4), 2 * kv + rows - i)));
   }
 }
 
@@ -732,11 +841,21 @@ __global__ __launch_bounds__(kThreads) void gumbel_bwd_kernel(int n, const float
   dx[i] = da[i] * al * (1.0f - al) * inv_tau;
 }
 
-constexpr int kNQ = 2;
+// Global -> LDS copies of 16 bytes a lane need their rows 16-byte aligned; an
+// input that is not (a view into a larger buffer) is copied to the workspace.
+__global__ __launch_bounds__(kThreads) void train_align_kernel(const uint16_t* src, uint16_t* dst, size_t n) {
+  for (size_t i = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
+       i += static_cast<size_t>(gridDim.x) * kThreads)
+    dst[i] = src[i];
+}
 
+// Workspace (2 (H + Hq) 16 KB per sequence and 32 positions, and 4 B Hq T):
+// key biases, the two per-row arrays, aligned copies of inputs that need one
+// and, for a split key-major pass, the further workgroups' sums in what is left.
 struct TrainLayout {
-  size_t ktiles, vtiles, qtiles, dotiles, dsum, bytes;
-  int nt;
+  size_t bias, nlse, nsum, part, bytes;
+  size_t part_stride;   // floats of one set of sums
+  int nt, nst;
 };
 
 TrainLayout train_layout(const dms_train_config& c) {
@@ -744,42 +863,55 @@ TrainLayout train_layout(const dms_train_config& c) {
   const size_t B = c.batch, T = c.seq_len, H = c.num_kv_heads, Hq = H * c.group_size;
   const size_t D = c.head_dim;
   l.nt = static_cast<int>((T + 31) / 32);
+  l.nst = (l.nt + 1) / 2;
   const size_t tile = D * 128;
+  l.bytes = 2 * align_up(B * H * l.nt * tile, kAlign) + 2 * align_up(B * Hq * l.nt * tile, kAlign) +
+            align_up(B * Hq * T * 4, kAlign);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
-  l.ktiles = take(B * H * l.nt * tile);
-  l.vtiles = take(B * H * l.nt * tile);
-  l.qtiles = take(B * Hq * l.nt * tile);
-  l.dotiles = take(B * Hq * l.nt * tile);
-  l.dsum = take(B * Hq * T * 4);
-  l.bytes = off;
+  l.bias = take(B * H * l.nst * 64 * 4);
+  l.nlse = take(B * Hq * l.nt * 32 * 4);
+  l.nsum = take(B * Hq * l.nt * 32 * 4);
+  l.part_stride = align_up((2 * B * T * H * D + B * T * H) * 4, kAlign) / 4;
+  l.part = off;
   return l;
+}
+
+// Sets `dst` to `src`, or to an aligned copy taken from the workspace's free part.
+hipError_t align_input(const uint16_t*& dst, const void* src, size_t rows, TrainLayout& l, char* ws, hipStream_t st) {
+  dst = static_cast<const uint16_t*>(src);
+  if (reinterpret_cast<uintptr_t>(src) % 16 == 0) return hipSuccess;
+  uint16_t* copy = reinterpret_cast<uint16_t*>(ws + l.part);
+  l.part = align_up(l.part + rows * kRowB, kAlign);
+  hipLaunchKernelGGL(train_align_kernel, dim3(1024), dim3(kThreads), 0, st, dst, copy, rows * kTrainD);
+  dst = copy;
+  return hipGetLastError();
 }
 
 TrainArgs train_args(const dms_train_config& c, const TrainLayout& l, void* ws) {
   TrainArgs a{};
   char* w = static_cast<char*>(ws);
-  a.ktiles = w + l.ktiles;
-  a.vtiles = w + l.vtiles;
-  a.qtiles = w + l.qtiles;
-  a.dotiles = w + l.dotiles;
-  a.dsum = reinterpret_cast<const float*>(w + l.dsum);
-  a.dsum_out = reinterpret_cast<float*>(w + l.dsum);
+  a.bias = reinterpret_cast<float*>(w + l.bias);
+  a.nlse = reinterpret_cast<float*>(w + l.nlse);
+  a.nsum = reinterpret_cast<float*>(w + l.nsum);
+  a.part_stride = l.part_stride;
   a.B = c.batch;
   a.T = c.seq_len;
   a.H = c.num_kv_heads;
   a.g = c.group_size;
   a.w = c.window;
   a.nt = l.nt;
-  a.PB = 4 * kNQ * 16 / c.group_size;   // (position, head) columns packed across column blocks
+  a.nst = l.nst;
+  a.PB = 4 * 32 / c.group_size;   // (position, head) columns packed across the waves' column blocks
+  a.splits = 1;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf(static_cast<float>(c.head_dim));
   a.scale_log2 = scale * kLog2e;
   return a;
 }
 
-hipError_t tile(const void* x, int B, int T, int H, int nt, char* tiles, hipStream_t st) {
-  TileArgs t{static_cast<const uint16_t*>(x), tiles, T, H, nt};
-  hipLaunchKernelGGL(train_tile_kernel<kTrainD>, dim3(nt, B * H), dim3(kThreads), 0, st, t);
+hipError_t launch_bias(const TrainArgs& a, bool backward, hipStream_t st) {
+  hipLaunchKernelGGL(train_bias_kernel, dim3((64 * a.nst + kThreads - 1) / kThreads, a.B * a.H), dim3(kThreads), 0,
+                     st, a, backward);
   return hipGetLastError();
 }
 
@@ -789,18 +921,20 @@ size_t train_workspace_bytes(const dms_train_config& c) { return train_layout(c)
 
 hipError_t launch_train_fwd(const dms_train_config& c, const void* q, const void* k, const void* v,
                             const float* alpha, float* out, float* lse, void* ws, hipStream_t st) {
-  const TrainLayout l = train_layout(c);
+  TrainLayout l = train_layout(c);
   TrainArgs a = train_args(c, l, ws);
   char* w = static_cast<char*>(ws);
-  hipError_t e = tile(k, c.batch, c.seq_len, c.num_kv_heads, l.nt, w + l.ktiles, st);
-  if (e == hipSuccess) e = tile(v, c.batch, c.seq_len, c.num_kv_heads, l.nt, w + l.vtiles, st);
-  if (e != hipSuccess) return e;
+  const size_t rows = static_cast<size_t>(c.batch) * c.seq_len * c.num_kv_heads;
   a.q = static_cast<const uint16_t*>(q);
   a.alpha = alpha;
   a.o_out = out;
   a.lse_out = lse;
+  hipError_t e = align_input(a.k, k, rows, l, w, st);
+  if (e == hipSuccess) e = align_input(a.v, v, rows, l, w, st);
+  if (e == hipSuccess) e = launch_bias(a, false, st);
+  if (e != hipSuccess) return e;
   dim3 grid((c.seq_len + a.PB - 1) / a.PB, c.batch * c.num_kv_heads);
-  hipLaunchKernelGGL((train_fwd_kernel<kTrainD, kNQ>), grid, dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL(train_fwd_kernel, grid, dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -808,19 +942,10 @@ hipError_t launch_train_bwd(const dms_train_config& c, const void* q, const void
                             const float* alpha, const float* out, const float* lse,
                             const void* dout, float* dq, float* dk, float* dv, float* dalpha,
                             void* ws, hipStream_t st) {
-  const TrainLayout l = train_layout(c);
+  TrainLayout l = train_layout(c);
   TrainArgs a = train_args(c, l, ws);
   char* w = static_cast<char*>(ws);
-  const int Hq = c.num_kv_heads * c.group_size;
-  hipError_t e = tile(k, c.batch, c.seq_len, c.num_kv_heads, l.nt, w + l.ktiles, st);
-  if (e == hipSuccess) e = tile(v, c.batch, c.seq_len, c.num_kv_heads, l.nt, w + l.vtiles, st);
-  if (e == hipSuccess) e = tile(q, c.batch, c.seq_len, Hq, l.nt, w + l.qtiles, st);
-  if (e == hipSuccess) e = tile(dout, c.batch, c.seq_len, Hq, l.nt, w + l.dotiles, st);
-  if (e != hipSuccess) return e;
-  a.q = static_cast<const uint16_t*>(q);
-  a.k = static_cast<const uint16_t*>(k);
-  a.v = static_cast<const uint16_t*>(v);
-  a.dout = static_cast<const uint16_t*>(dout);
+  const size_t rows = static_cast<size_t>(c.batch) * c.seq_len * c.num_kv_heads;
   a.alpha = alpha;
   a.out = out;
   a.lse = lse;
@@ -828,17 +953,29 @@ hipError_t launch_train_bwd(const dms_train_config& c, const void* q, const void
   a.dk = dk;
   a.dv = dv;
   a.dalpha = dalpha;
-  const int64_t rows = static_cast<int64_t>(c.batch) * c.seq_len * Hq;
-  hipLaunchKernelGGL(train_rowsum_kernel, dim3(static_cast<unsigned>((rows * 16 + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, st, a, c.head_dim);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(train_dkv_kernel<kTrainD>, dim3((c.seq_len + 63) / 64, c.batch * c.num_kv_heads),
-                     dim3(kThreads), 0, st, a);
-  e = hipGetLastError();
+  hipError_t e = align_input(a.k, k, rows, l, w, st);
+  if (e == hipSuccess) e = align_input(a.v, v, rows, l, w, st);
+  if (e == hipSuccess) e = align_input(a.q, q, rows * c.group_size, l, w, st);
+  if (e == hipSuccess) e = align_input(a.dout, dout, rows * c.group_size, l, w, st);
+  if (e == hipSuccess) e = launch_bias(a, true, st);
   if (e != hipSuccess) return e;
   dim3 grid((c.seq_len + a.PB - 1) / a.PB, c.batch * c.num_kv_heads);
-  hipLaunchKernelGGL((train_dq_kernel<kTrainD, kNQ>), grid, dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL(train_dq_kernel, grid, dim3(kThreads), 0, st, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // Key-major pass: about two workgroups per CU, the room left in the
+  // workspace permitting (always at least g sets of sums with aligned inputs)
+  a.part = reinterpret_cast<float*>(w + l.part);
+  const int blocks = (c.seq_len + 127) / 128;
+  const int64_t wgs = static_cast<int64_t>(blocks) * c.batch * c.num_kv_heads;
+  const int64_t room = l.bytes > l.part ? static_cast<int64_t>((l.bytes - l.part) / (l.part_stride * 4)) : 0;
+  a.splits = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({512 / wgs, 1 + room, c.group_size})));
+  hipLaunchKernelGGL(train_dkv_kernel, dim3(blocks * a.splits, c.batch * c.num_kv_heads), dim3(kThreads), 0, st, a);
+  e = hipGetLastError();
+  if (e != hipSuccess || a.splits == 1) return e;
+  const size_t n = (rows * (2 * kTrainD + 1) + 3) / 4;
+  hipLaunchKernelGGL(train_sum_kernel, dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                     st, a);
   return hipGetLastError();
 }
 
