@@ -538,7 +538,10 @@ int dms_append_chunk(dms_ctx* ctx, int layer, int n, const int32_t* seq_ids_dev,
   if (!k_dev || !(v_dev || mla(ctx)) || !flags_dev) return DMS_ERR_INVALID;
   const Ctx& c = ctx->c;
   hipStream_t st = as_stream(stream);
-  hipError_t e = dms::launch_chunk_commit(c.cfg, c.lo, c.meta, c.ws, c.pools[layer], layer, n,
+  hipError_t e = dms::launch_chunk_scan(c.cfg, c.lo, c.meta, c.ws, layer, n, seq_ids_dev, cu_seqlens_dev,
+                                        total_tokens, max_seqlen, flags_dev, false, as_stream(stream));
+  if (e == hipSuccess)
+    e = dms::launch_chunk_commit(c.cfg, c.lo, c.meta, c.ws, c.pools[layer], layer, n,
                                           seq_ids_dev, cu_seqlens_dev, total_tokens, max_seqlen,
                                           k_dev, v_dev, flags_dev, st);
   // page retrieval: a chunk may write into any page of a head (reused slots)

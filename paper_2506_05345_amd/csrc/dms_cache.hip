@@ -5,6 +5,8 @@
 // Every state change of one call is planned before it is applied, so a call
 // that would exhaust the page pool (or overflow a head's page table) changes
 // nothing and only records the error in the sticky status word.
+#include <algorithm>
+
 #include "dms_common.h"
 #include "dms_fp8.h"
 
@@ -100,6 +102,7 @@ struct ResetArgs {
 
 __global__ __launch_bounds__(kPlanThreads) void seq_reset_kernel(ResetArgs a) {
   __shared__ uint32_t seen[kMaxSeqs / 32];
+  __shared__ int2 head_pages[kPlanThreads];   // first stack entry, pages
   __shared__ int lds[17];
   __shared__ int s_abort;
   if (threadIdx.x == 0) s_abort = load_status(a.status) != 0;
@@ -118,24 +121,29 @@ __global__ __launch_bounds__(kPlanThreads) void seq_reset_kernel(ResetArgs a) {
   int32_t* top = reinterpret_cast<int32_t*>(b + a.top);
   const int NH = a.n * a.H;
   const int top0 = *top;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int run = 0;
   for (int base = 0; base < NH; base += blockDim.x) {
     const int hh = base + threadIdx.x;
-    int np = 0, sh = 0;
-    if (hh < NH) {
-      sh = a.seq_ids[hh / a.H] * a.H + hh % a.H;
-      np = (len[sh] + a.P - 1) / a.P;
-    }
+    int np = 0;
+    if (hh < NH) np = (len[a.seq_ids[hh / a.H] * a.H + hh % a.H] + a.P - 1) / a.P;
     int tot;
-    int off = block_exclusive_scan(np, lds, &tot);
-    if (hh < NH) {
-      for (int k = 0; k < np; ++k) {
-        stack[top0 + run + off + k] = pt[static_cast<size_t>(sh) * a.maxp + k];
-        pt[static_cast<size_t>(sh) * a.maxp + k] = -1;
+    const int off = block_exclusive_scan(np, lds, &tot);
+    head_pages[threadIdx.x] = make_int2(top0 + run + off, np);
+    __syncthreads();
+    // a wave per head, its lanes over the head's pages and ring entries (one
+    // thread per head: 15 us for 4 sequences of 8 heads, w = 256; 7 us so)
+    for (int x = wave; x < min(static_cast<int>(blockDim.x), NH - base); x += blockDim.x >> 6) {
+      const size_t sh = static_cast<size_t>(a.seq_ids[(base + x) / a.H]) * a.H + (base + x) % a.H;
+      const int2 hp = head_pages[x];
+      for (int k = lane; k < hp.y; k += 64) {
+        stack[hp.x + k] = pt[sh * a.maxp + k];
+        pt[sh * a.maxp + k] = -1;
       }
-      len[sh] = 0;
-      for (int e = 0; e < a.w; ++e) ring[static_cast<size_t>(sh) * a.w + e] = 0;
+      for (int e = lane; e < a.w; e += 64) ring[sh * a.w + e] = 0;
+      if (lane == 0) len[sh] = 0;
     }
+    __syncthreads();
     run += tot;
   }
   __syncthreads();
@@ -514,7 +522,8 @@ __global__ void retained_kernel(RetainedArgs a) {
 
 struct ChunkArgs {
   LayerState st;
-  int32_t* status;
+  const int32_t* status;
+  int32_t* status_w;
   const int32_t* seq_ids;
   const int32_t* cu;
   const uint8_t* flags;   // [T, H]
@@ -527,7 +536,13 @@ struct ChunkArgs {
   int32_t* base;          // [n*H] first pop index per head
   int32_t* pos0;          // [n] position of each sequence before the chunk
   int32_t* err;           // call-local error word, err[1] = stack height before the call
-  int32_t* slots;         // [T, H] slot of every chunk token
+  int32_t* slots;         // [T, H] slot of every fresh chunk token
+  // masked prefill (null otherwise): kept chunk tokens, see dms_prefill.hip
+  int32_t* list;          // [H][total]
+  int32_t* list_cnt;      // [n*H]
+  int32_t* kept_before;   // [H][tph]
+  int32_t* work_ctr;
+  int tph;
   int n, H, w, P, D, maxp, max_slots, max_seqs, total, max_len;
   int immediate;          // eviction timing (see chunk_reuse)
   int fp8;                // FP8 pages: rows are quantized on the way in
@@ -550,15 +565,22 @@ __device__ inline bool chunk_reuse(const ChunkArgs& a, int sh, int h, int tok0, 
   return (static_cast<uint32_t>(e) & kFlagBit) != 0;
 }
 
-constexpr int kChunkTPT = 16;   // consecutive chunk tokens per thread in the scans
+constexpr int kScanThreads = 1024;
+constexpr int kScanTPT = 4;   // consecutive chunk tokens per thread in the scan
 
 // Pass 1 (one block per head): count fresh tokens and the pages they need,
 // and give every fresh token its slot (L0 + its index among the fresh ones;
 // the slot array is scratch, so writing it before validation is harmless).
-// Each thread takes kChunkTPT consecutive tokens (their flags are loaded
-// together), so a 4096-token chunk needs one block scan.
-__global__ __launch_bounds__(256) void chunk_count_kernel(ChunkArgs a) {
-  __shared__ int lds[17];
+// Before a masked prefill it also lists the kept chunk tokens in position
+// order and counts them before every 32-aligned position (a token is kept
+// unless its own decision hides it, or, with immediate eviction, that of the
+// token w after it in the chunk); chunk boundaries that disagree with the
+// host's then set the sticky status, so that the attention does nothing.
+// Bound by the latency of its dependent loads and scans: 4096 tokens take one
+// round of 1024 threads, 9.6 us (22 us for the list, in 16 rounds of 256
+// tokens, and 10 us for the counts in a launch of their own, before).
+__global__ __launch_bounds__(kScanThreads) void chunk_scan_kernel(ChunkArgs a) {
+  __shared__ int lds[34];
   if (load_status(a.status) != 0) return;
   const int hh = blockIdx.x;
   const int i = hh / a.H, h = hh % a.H;
@@ -567,35 +589,55 @@ __global__ __launch_bounds__(256) void chunk_count_kernel(ChunkArgs a) {
   bool bad = (s < 0 || s >= a.max_seqs || C < 0 || C > a.max_len || a.cu[0] != 0 ||
               a.cu[a.n] != a.total || tok0 < 0 || tok0 + C > a.total);
   if (bad) {
-    if (threadIdx.x == 0) atomicCAS(reinterpret_cast<int*>(a.err), 0, DMS_ERR_INVALID);
+    if (threadIdx.x == 0) {
+      if (a.list != nullptr) set_status(a.status_w, DMS_ERR_INVALID);
+      else atomicCAS(reinterpret_cast<int*>(a.err), 0, DMS_ERR_INVALID);
+    }
     return;
   }
+  if (a.list != nullptr && hh == 0 && threadIdx.x == 0) *a.work_ctr = 0;
   const int sh = s * a.H + h;
   const int pos0 = a.st.pos[s];
   const int L0 = a.st.len[sh];
   int32_t* slots = a.slots + static_cast<size_t>(tok0) * a.H + h;   // token c at c * H
-  int cnt = 0;
-  for (int base = 0; base < C; base += blockDim.x * kChunkTPT) {
-    const int c0 = base + threadIdx.x * kChunkTPT;
-    bool f[kChunkTPT];
-    int mine = 0;
+  int32_t* list = a.list + static_cast<size_t>(h) * a.total + tok0;
+  int32_t* kept_before = a.kept_before + static_cast<size_t>(h) * a.tph + tok0 / 32 + i;
+  int cnt = 0, kcnt = 0;
+  for (int base = 0; base < C; base += kScanThreads * kScanTPT) {
+    const int c0 = base + threadIdx.x * kScanTPT;
+    bool fresh[kScanTPT], kept[kScanTPT];
+    int2 mine = make_int2(0, 0);
 #pragma unroll
-    for (int u = 0; u < kChunkTPT; ++u) {
-      f[u] = c0 + u < C && !chunk_reuse(a, sh, h, tok0, pos0, c0 + u);
-      mine += f[u];
+    for (int u = 0; u < kScanTPT; ++u) {
+      const int c = c0 + u;
+      fresh[u] = c < C && !chunk_reuse(a, sh, h, tok0, pos0, c);
+      kept[u] = false;
+      if (a.list != nullptr && c < C) {
+        const int64_t x = a.immediate ? static_cast<int64_t>(c) + a.w : c;
+        kept[u] = x >= C || !chunk_flag(a, tok0, static_cast<int>(x), h);
+      }
+      mine.x += fresh[u];
+      mine.y += kept[u];
     }
-    int tot;
-    int k = L0 + cnt + block_exclusive_scan(mine, lds, &tot);
+    int2 tot;
+    const int2 ex = block_exclusive_scan2(mine, lds, &tot);
+    int k = L0 + cnt + ex.x, kk = kcnt + ex.y;
 #pragma unroll
-    for (int u = 0; u < kChunkTPT; ++u)
-      if (f[u]) slots[static_cast<size_t>(c0 + u) * a.H] = k++;
-    cnt += tot;
+    for (int u = 0; u < kScanTPT; ++u) {
+      const int c = c0 + u;
+      if (fresh[u]) slots[static_cast<size_t>(c) * a.H] = k++;
+      if (a.list != nullptr && c < C && (c & 31) == 0) kept_before[c >> 5] = kk;
+      if (kept[u]) list[kk++] = c;
+    }
+    cnt += tot.x;
+    kcnt += tot.y;
   }
   if (threadIdx.x == 0) {
     const int L1 = L0 + cnt;
     if (L1 > a.max_slots) atomicCAS(reinterpret_cast<int*>(a.err), 0, DMS_ERR_CAPACITY);
     a.fresh[hh] = cnt;
     a.need[hh] = (L1 + a.P - 1) / a.P - (L0 + a.P - 1) / a.P;
+    if (a.list != nullptr) a.list_cnt[hh] = kcnt;
     if (h == 0) a.pos0[i] = pos0;
   }
 }
@@ -606,14 +648,14 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
   __shared__ int lds[17];
   __shared__ int s_abort;
   if (threadIdx.x == 0) s_abort = load_status(a.status) != 0;
-  __syncthreads();
-  if (s_abort) return;
-  // pass 1 of this call ran iff this pass runs: consume and clear its error word
+  // consume and clear pass 1's error word (also where the call does nothing: some blocks of
+  // pass 1 may have run before another one set the status)
   const int err = *a.err;
   __syncthreads();
   if (threadIdx.x == 0) a.err[0] = 0;
+  if (s_abort) return;
   if (bad_seq_ids(a.seq_ids, a.n, a.max_seqs, seen)) {
-    if (threadIdx.x == 0) set_status(a.status, DMS_ERR_BAD_SEQ);
+    if (threadIdx.x == 0) set_status(a.status_w, DMS_ERR_BAD_SEQ);
     return;
   }
   const int NH = a.n * a.H;
@@ -629,128 +671,138 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
   }
   if (threadIdx.x == 0) {
     if (err != 0) {
-      set_status(a.status, err);
+      set_status(a.status_w, err);
     } else if (run > top0) {
-      set_status(a.status, DMS_ERR_OUT_OF_PAGES);
+      set_status(a.status_w, DMS_ERR_OUT_OF_PAGES);
     } else {
       *a.st.top = top0 - run;
       a.err[1] = top0;
     }
   }
   __syncthreads();
-  // positions advance here: pass 1 has read them, pass 3 uses pos0
-  if (err == 0 && run <= top0)
+  // positions and lengths advance here: pass 1 has read them, pass 3 uses pos0
+  // and the fresh counts
+  if (err == 0 && run <= top0) {
     for (int i = threadIdx.x; i < a.n; i += blockDim.x)
       a.st.pos[a.seq_ids[i]] = a.pos0[i] + (a.cu[i + 1] - a.cu[i]);
+    for (int hh = threadIdx.x; hh < NH; hh += blockDim.x)
+      a.st.len[a.seq_ids[hh / a.H] * a.H + hh % a.H] += a.fresh[hh];
+  }
 }
 
-// Pass 3 (one block per head): reused slots, page table, ring, slot metadata.
+// Pass 3 (one block per (head, 16 residue classes modulo w)): slots of the
+// reusing tokens, ring, slot metadata, and the K rows and V columns of the
+// surviving tokens.  A token that reuses takes the slot of the token w before
+// it, so along one class c = r, r + w, r + 2w, ... every token holds the slot
+// of the latest fresh token of the class before it, or, for the first ones,
+// the slot the ring gives for position pos0 + r - w; the class reads and
+// writes no other ring entry than that one, so classes are independent.  Up to
+// 64 members of each class are gathered in LDS at a time, walked there, and
+// the survivors (one in eight at 7/8 evicted) listed for the copy.  4 x 4096
+// tokens, 8 heads, w = 256: 25 us against 32 us for a walk through memory by
+// one block per head and 31 us for a copy launch with a thread group per
+// token, most of which had nothing to do.
+constexpr int kClasses = 16, kMembers = 64;
 __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
-  if (load_status(a.status) != 0) return;
-  const int top_before = a.err[1];
-  const int hh = blockIdx.x;
-  const int i = hh / a.H, h = hh % a.H;
-  const int s = a.seq_ids[i];
-  const int sh = s * a.H + h;
-  const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
-  const int pos0 = a.pos0[i];
-  const int L0 = a.st.len[sh];
-  const size_t pt_base = static_cast<size_t>(sh) * a.maxp;
-  int32_t* slots = a.slots + static_cast<size_t>(tok0) * a.H + h;   // token c at c * H
-  // new pages, popped in page-index order from this head's reserved range
-  const int first_new_page = (L0 + a.P - 1) / a.P;
-  for (int k = threadIdx.x; k < a.need[hh]; k += blockDim.x)
-    a.st.page_table[pt_base + first_new_page + k] = a.st.stack[top_before - 1 - (a.base[hh] + k)];
-  // Reused slots (fresh ones were assigned by pass 1).  A token that reuses
-  // takes the slot of the token w before it, so along one residue class
-  // c = r, r + w, r + 2w, ... every token holds the slot of the latest fresh
-  // token of the class before it, or, for the first ones, the slot the ring
-  // gives for position pos0 + r - w.  One forward walk per class, its flags
-  // and fresh slots loaded kChunkTPT members at a time.
-  for (int r = threadIdx.x; r < min(a.w, C); r += blockDim.x) {
-    int carried = -1;
-    if (pos0 + r >= a.w) {
-      const int32_t e = a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + r) % a.w];
-      carried = static_cast<int>(static_cast<uint32_t>(e) & ~kFlagBit);
-    }
-    for (int c0 = r; c0 < C; c0 += kChunkTPT * a.w) {
-      bool ru[kChunkTPT];
-      int sl[kChunkTPT];
-#pragma unroll
-      for (int u = 0; u < kChunkTPT; ++u) {
-        const int c = c0 + u * a.w;
-        ru[u] = c < C && chunk_reuse(a, sh, h, tok0, pos0, c);
-        sl[u] = (c < C && !ru[u]) ? slots[static_cast<size_t>(c) * a.H] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < kChunkTPT; ++u) {
-        const int c = c0 + u * a.w;
-        if (c >= C) break;
-        if (ru[u]) slots[static_cast<size_t>(c) * a.H] = carried;
-        else carried = sl[u];
-      }
-    }
-  }
-  __syncthreads();  // ring reads above complete before the ring is rewritten
-  const int ring_from = C > a.w ? C - a.w : 0;
-  for (int c = threadIdx.x; c < C; c += blockDim.x) {
-    const int fl = chunk_flag(a, tok0, c, h);
-    const uint32_t fb = fl ? kFlagBit : 0u;
-    const int slot = slots[static_cast<size_t>(c) * a.H];
-    if (c >= ring_from)
-      a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + c) % a.w] =
-          static_cast<int32_t>(static_cast<uint32_t>(slot) | fb);
-    // a token keeps its slot unless the token w later in the chunk takes it
-    const bool survives = (c + a.w >= C) || !chunk_reuse(a, sh, h, tok0, pos0, c + a.w);
-    if (survives)
-      a.st.slot_meta[static_cast<size_t>(sh) * a.max_slots + slot] =
-          static_cast<int32_t>(static_cast<uint32_t>(pos0 + c) | fb);
-  }
-  if (threadIdx.x == 0) a.st.len[sh] = L0 + a.fresh[hh];
-}
-
-// Pass 4 (blocks of 256 / (D/8) tokens of one head): K rows and V columns of
-// the surviving tokens into their slots, D/8 consecutive lanes per token (an
-// aligned lane group: the block size is a multiple of it, so a group is
-// entirely inside or outside the chunk and takes every branch together).
-// The page table entries of pass 3 are complete: separate launch.
-__global__ __launch_bounds__(256) void chunk_copy_kernel(ChunkArgs a) {
+  __shared__ int slot_l[kClasses * kMembers], live_l[kClasses * kMembers];
+  __shared__ int live_cnt;
   if (load_status(a.status) != 0) return;
   const int hh = blockIdx.y;
   const int i = hh / a.H, h = hh % a.H;
-  const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
-  const int kq = a.D / 8;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= C * kq) return;
-  const int c = idx / kq, part = idx % kq;
   const int s = a.seq_ids[i];
   const int sh = s * a.H + h;
+  const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
   const int pos0 = a.pos0[i];
-  if (!((c + a.w >= C) || !chunk_reuse(a, sh, h, tok0, pos0, c + a.w))) return;
-  const int slot = a.slots[static_cast<size_t>(tok0 + c) * a.H + h];
-  const int page = a.st.page_table[static_cast<size_t>(sh) * a.maxp + slot / a.P];
-  const int row = slot % a.P;
-  const int j = row & 31;
-  const size_t src = (static_cast<size_t>(tok0 + c) * a.H + h) * a.D;
-  const uint4 kx = reinterpret_cast<const uint4*>(a.k + src)[part];
-  if (a.mla) {
-    char* tile = a.pool + static_cast<size_t>(page) * a.page_bytes + (row >> 5) * mla_tile_bytes(a.D);
-    *reinterpret_cast<uint4*>(tile + k_elem_off(j, 8 * part)) = kx;
-    return;
-  }
-  const uint4 vx = reinterpret_cast<const uint4*>(a.v + src)[part];
-  if (a.fp8) {
-    char* tile = a.pool + static_cast<size_t>(page) * a.page_bytes + (row >> 5) * fp8_tile_bytes(a.D);
-    fp8_store_token(tile, j, a.D, part, kx, vx);
-    return;
-  }
-  char* tile = a.pool + static_cast<size_t>(page) * a.page_bytes + (row >> 5) * tile_bytes(a.D);
-  *reinterpret_cast<uint4*>(tile + k_elem_off(j, 8 * part)) = kx;
-  const uint32_t vw[4] = {vx.x, vx.y, vx.z, vx.w};
+  const int L0 = a.st.len[sh] - a.fresh[hh];
+  const size_t pt_base = static_cast<size_t>(sh) * a.maxp;
+  const int32_t* slots = a.slots + static_cast<size_t>(tok0) * a.H + h;   // fresh token c at c * H
+  const int32_t* popped = a.st.stack + a.err[1] - 1 - a.base[hh];         // k-th new page at -k
+  const int first_new_page = (L0 + a.P - 1) / a.P;
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < a.need[hh]; k += blockDim.x) a.st.page_table[pt_base + first_new_page + k] = popped[-k];
+  const int r0 = blockIdx.x * kClasses;
+  const int nr = min(kClasses, min(a.w, C) - r0);   // classes of this block
+  if (nr <= 0) return;
+  const int kq = a.D / 8;                           // 16-byte pieces of a row
+  const int log2P = 31 - __clz(a.P);
+  int carried = -1;
+  const int rr = threadIdx.x % kClasses;
+  for (int64_t m0 = 0; m0 * a.w + r0 < C; m0 += kMembers) {
+    if (threadIdx.x == 0) live_cnt = 0;
+    bool lives[kClasses * kMembers / 256];
 #pragma unroll
-  for (int e = 0; e < 8; ++e)
-    *reinterpret_cast<uint16_t*>(tile + v_elem_off(j, part * 8 + e, a.D)) =
-        static_cast<uint16_t>(vw[e >> 1] >> (16 * (e & 1)));
+    for (int u = 0; u < kClasses * kMembers / 256; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      const int64_t c = r0 + rr + (m0 + e / kClasses) * a.w;
+      int v = -2;                                   // no such token
+      lives[u] = false;
+      if (rr < nr && c < C) {
+        v = chunk_reuse(a, sh, h, tok0, pos0, static_cast<int>(c)) ? -1 : slots[static_cast<size_t>(c) * a.H];
+        // a token keeps its slot unless the token w later in the chunk takes it
+        lives[u] = c + a.w >= C || !chunk_reuse(a, sh, h, tok0, pos0, static_cast<int>(c + a.w));
+      }
+      slot_l[e] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < nr) {
+      if (m0 == 0 && pos0 + r0 + rr >= a.w) {
+        const int32_t e = a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + r0 + rr) % a.w];
+        carried = static_cast<int>(static_cast<uint32_t>(e) & ~kFlagBit);
+      }
+      for (int m = 0; m < kMembers; ++m) {
+        const int v = slot_l[m * kClasses + rr];
+        if (v == -2) break;
+        if (v == -1) slot_l[m * kClasses + rr] = carried;
+        else carried = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kClasses * kMembers / 256; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      const int slot = slot_l[e];
+      if (slot < 0) continue;
+      const int c = static_cast<int>(r0 + rr + (m0 + e / kClasses) * a.w);
+      const uint32_t fb = chunk_flag(a, tok0, c, h) ? kFlagBit : 0u;
+      if (C - c <= a.w)
+        a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + c) % a.w] = static_cast<int32_t>(static_cast<uint32_t>(slot) | fb);
+      if (lives[u]) {
+        a.st.slot_meta[static_cast<size_t>(sh) * a.max_slots + slot] =
+            static_cast<int32_t>(static_cast<uint32_t>(pos0 + c) | fb);
+        live_l[atomicAdd(&live_cnt, 1)] = e;
+      }
+    }
+    __syncthreads();
+    // kq consecutive lanes per survivor (an aligned lane group for the FP8
+    // quantizer: it takes every branch together)
+    for (int x = threadIdx.x; x < live_cnt * kq; x += blockDim.x) {
+      const int e = live_l[x / kq], part = x % kq;
+      const int c = static_cast<int>(r0 + e % kClasses + (m0 + e / kClasses) * a.w);
+      const int slot = slot_l[e], row = slot & (a.P - 1), j = row & 31;
+      const int pi = slot >> log2P;
+      const int page = pi >= first_new_page ? popped[first_new_page - pi] : a.st.page_table[pt_base + pi];
+      const size_t src = (static_cast<size_t>(tok0 + c) * a.H + h) * a.D;
+      const uint4 kx = reinterpret_cast<const uint4*>(a.k + src)[part];
+      char* pg = a.pool + static_cast<size_t>(page) * a.page_bytes;
+      if (a.mla) {
+        *reinterpret_cast<uint4*>(pg + (row >> 5) * mla_tile_bytes(a.D) + k_elem_off(j, 8 * part)) = kx;
+        continue;
+      }
+      const uint4 vx = reinterpret_cast<const uint4*>(a.v + src)[part];
+      if (a.fp8) {
+        fp8_store_token(pg + (row >> 5) * fp8_tile_bytes(a.D), j, a.D, part, kx, vx);
+        continue;
+      }
+      char* tile = pg + (row >> 5) * tile_bytes(a.D);
+      *reinterpret_cast<uint4*>(tile + k_elem_off(j, 8 * part)) = kx;
+      const uint32_t vw[4] = {vx.x, vx.y, vx.z, vx.w};
+#pragma unroll
+      for (int d = 0; d < 8; ++d)
+        *reinterpret_cast<uint16_t*>(tile + v_elem_off(j, part * 8 + d, a.D)) =
+            static_cast<uint16_t>(vw[d >> 1] >> (16 * (d & 1)));
+    }
+    __syncthreads();
+  }
 }
 
 }  // namespace
@@ -889,20 +941,18 @@ hipError_t launch_retained(const dms_config& c, const Layout& lo, void* meta, in
   return hipGetLastError();
 }
 
-hipError_t launch_chunk_commit(const dms_config& c, const Layout& lo, void* meta, void* ws,
-                               void* pool, int layer, int n, const int32_t* seq_ids,
-                               const int32_t* cu, int total_tokens, int max_len, const void* k,
-                               const void* v, const uint8_t* flags, hipStream_t st) {
-  ChunkArgs a;
+namespace {
+
+ChunkArgs chunk_args(const dms_config& c, const Layout& lo, void* meta, void* ws, int layer, int n,
+                     const int32_t* seq_ids, const int32_t* cu, int total_tokens, int max_len,
+                     const uint8_t* flags) {
+  ChunkArgs a{};
   char* w = static_cast<char*>(ws);
   a.st = layer_state(lo, meta, layer);
-  a.status = reinterpret_cast<int32_t*>(static_cast<char*>(meta) + lo.status);
+  a.status = a.status_w = reinterpret_cast<int32_t*>(static_cast<char*>(meta) + lo.status);
   a.seq_ids = seq_ids;
   a.cu = cu;
   a.flags = flags;
-  a.k = static_cast<const uint16_t*>(k);
-  a.v = static_cast<const uint16_t*>(v);
-  a.pool = static_cast<char*>(pool);
   a.page_bytes = lo.page_bytes;
   a.need = reinterpret_cast<int32_t*>(w + lo.ws_ck_need);
   a.fresh = reinterpret_cast<int32_t*>(w + lo.ws_ck_fresh);
@@ -923,15 +973,39 @@ hipError_t launch_chunk_commit(const dms_config& c, const Layout& lo, void* meta
   a.immediate = c.eviction == DMS_EVICT_IMMEDIATE;
   a.fp8 = c.kv_format == DMS_KV_FP8;
   a.mla = c.kv_format == DMS_KV_MLA;
-  const int NH = n * c.num_kv_heads;
-  hipLaunchKernelGGL(chunk_count_kernel, dim3(NH), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(chunk_pages_kernel, dim3(1), dim3(kPlanThreads), 0, st, a);
-  hipLaunchKernelGGL(chunk_commit_kernel, dim3(NH), dim3(256), 0, st, a);
-  if (max_len > 0) {
-    const int per_block = 256 / (c.head_dim / 8);   // tokens per copy block
-    hipLaunchKernelGGL(chunk_copy_kernel, dim3((max_len + per_block - 1) / per_block, NH), dim3(256), 0,
-                       st, a);
+  return a;
+}
+
+}  // namespace
+
+hipError_t launch_chunk_scan(const dms_config& c, const Layout& lo, void* meta, void* ws, int layer, int n,
+                             const int32_t* seq_ids, const int32_t* cu, int total_tokens, int max_len,
+                             const uint8_t* flags, bool prefill, hipStream_t st) {
+  ChunkArgs a = chunk_args(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags);
+  if (prefill) {
+    char* w = static_cast<char*>(ws);
+    a.list = reinterpret_cast<int32_t*>(w + lo.ws_pf_meta);
+    a.list_cnt = reinterpret_cast<int32_t*>(w + lo.ws_pf_cum);
+    a.work_ctr = a.list_cnt + lo.max_heads;
+    a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
+    a.tph = lo.pf_tiles_per_head;
   }
+  hipLaunchKernelGGL(chunk_scan_kernel, dim3(n * c.num_kv_heads), dim3(kScanThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_chunk_commit(const dms_config& c, const Layout& lo, void* meta, void* ws,
+                               void* pool, int layer, int n, const int32_t* seq_ids,
+                               const int32_t* cu, int total_tokens, int max_len, const void* k,
+                               const void* v, const uint8_t* flags, hipStream_t st) {
+  ChunkArgs a = chunk_args(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags);
+  a.k = static_cast<const uint16_t*>(k);
+  a.v = static_cast<const uint16_t*>(v);
+  a.pool = static_cast<char*>(pool);
+  hipLaunchKernelGGL(chunk_pages_kernel, dim3(1), dim3(kPlanThreads), 0, st, a);
+  const int classes = std::max(1, std::min(c.window, max_len));
+  hipLaunchKernelGGL(chunk_commit_kernel, dim3((classes + kClasses - 1) / kClasses, n * c.num_kv_heads), dim3(256), 0,
+                     st, a);
   return hipGetLastError();
 }
 

@@ -280,6 +280,11 @@ hipError_t launch_decode_mla(const dms_config& c, const Layout& lo, void* meta, 
 int decode_mla_resident_waves(const dms_config& c);
 hipError_t launch_retained(const dms_config& c, const Layout& lo, void* meta, int layer, int n,
                            const int32_t* seq_ids, int32_t* out, hipStream_t st);
+// Pass 1 of a chunk commit, also before a masked prefill (`prefill`: with the
+// kept-token lists that its attention reads); launch_chunk_commit follows it.
+hipError_t launch_chunk_scan(const dms_config& c, const Layout& lo, void* meta, void* ws, int layer, int n,
+                             const int32_t* seq_ids, const int32_t* cu, int total_tokens, int max_len,
+                             const uint8_t* flags, bool prefill, hipStream_t st);
 hipError_t launch_chunk_commit(const dms_config& c, const Layout& lo, void* meta, void* ws,
                                void* pool, int layer, int n, const int32_t* seq_ids,
                                const int32_t* cu, int total_tokens, int max_len, const void* k,

@@ -14,7 +14,7 @@
 //   3. the band: the chunk tiles from the one holding max(p0, t0 - w + 1) to
 //      t1, masked per element.
 //
-// Pass 0 lists the kept chunk tokens; pass 1 copies the chunk's keys and
+// Pass 0 (chunk_scan_kernel) lists the kept chunk tokens; pass 1 copies the chunk's keys and
 // values, in chunk order and in kept order, into workspace tiles in the
 // pool's tile layout (16-byte pieces in the decode MFMAs' fragment order:
 // keys by (k-step, half, lane), values transposed), so the attention pass
@@ -93,7 +93,6 @@ __device__ inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
 
 struct PrefillArgs {
   const int32_t* status;
-  int32_t* status_w;
   const int32_t* seq_ids;
   const int32_t* cu;
   const uint16_t* q;      // [T, Hq, D]
@@ -128,9 +127,6 @@ __device__ inline bool key_flag(const PrefillArgs& a, int tok0, int C, int c, in
   const int x = a.immediate ? c + a.w : c;
   return x < C && a.flags[static_cast<size_t>(tok0 + x) * a.H + h] != 0;
 }
-__device__ inline bool key_kept(const PrefillArgs& a, int tok0, int C, int c, int h) {
-  return !key_flag(a, tok0, C, c, h);
-}
 
 // Decisions from the borrowed query neuron (Sec. 3.2 rounding, App. C):
 // flags[t][h] = (bf16 q[t][h * g][0] + bias > 0) in float32.
@@ -150,37 +146,6 @@ __device__ inline size_t ws_tile(const PrefillArgs& a, int region, int h, int i,
 __device__ inline size_t ws_kb(const PrefillArgs& a, int h, int i, int j) {
   return static_cast<size_t>(h) * a.tph + a.cu[i] / 32 + i + j;
 }
-
-// Pass 0 (one block per (sequence, head)): validate the chunk boundaries,
-// list the kept tokens of the chunk in position order and count them before
-// every 32-aligned position.
-__global__ __launch_bounds__(kThreads) void prefill_list_kernel(PrefillArgs a) {
-  __shared__ int lds[17];
-  if (load_status(a.status) != 0) return;
-  const int hh = blockIdx.x;
-  const int i = hh / a.H, h = hh % a.H;
-  const int s = a.seq_ids[i];
-  const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
-  const bool bad = (s < 0 || s >= a.max_seqs || C < 0 || C > a.max_len || a.cu[0] != 0 ||
-                    a.cu[a.n] != a.total || tok0 < 0 || tok0 + C > a.total);
-  if (bad) {
-    if (threadIdx.x == 0) atomicCAS(reinterpret_cast<int*>(a.status_w), 0, DMS_ERR_INVALID);
-    return;
-  }
-  if (hh == 0 && threadIdx.x == 0 && a.work_ctr) *a.work_ctr = 0;
-  int run = 0;
-  for (int c0 = 0; c0 < C; c0 += blockDim.x) {
-    const int c = c0 + threadIdx.x;
-    const int kept = (c < C) && key_kept(a, tok0, C, c, h);
-    int tot;
-    const int off = block_exclusive_scan(kept, lds, &tot);
-    if (kept) a.list[static_cast<size_t>(h) * a.total + tok0 + run + off] = c;
-    if (c < C && (c & 31) == 0) a.kept_before[ws_kb(a, h, i, c >> 5)] = run + off;
-    run += tot;
-  }
-  if (threadIdx.x == 0) a.list_cnt[hh] = run;
-}
-
 
 // Attention grid rows by decreasing work (rows are dispatched in order, so
 // the longest heads start first and the short ones fill the tail): one
@@ -1102,7 +1067,6 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   LayerState ls = layer_state(lo, meta, layer);
   PrefillArgs a;
   a.status = reinterpret_cast<const int32_t*>(static_cast<char*>(meta) + lo.status);
-  a.status_w = reinterpret_cast<int32_t*>(static_cast<char*>(meta) + lo.status);
   a.seq_ids = seq_ids;
   a.cu = cu;
   a.q = static_cast<const uint16_t*>(q);
@@ -1146,8 +1110,7 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   const int NH = n * c.num_kv_heads;
   // the timing events bracket every pass
   if (ev_start) (void)hipEventRecord(ev_start, st);
-  hipLaunchKernelGGL(prefill_list_kernel, dim3(NH), dim3(kThreads), 0, st, a);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
   if (NH > 1 && NH <= kOrderMax) {
     a.order = reinterpret_cast<int32_t*>(w + lo.ws_pf_order);
@@ -1487,7 +1450,6 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   LayerState ls = layer_state(lo, meta, layer);
   PrefillArgs a;
   a.status = reinterpret_cast<const int32_t*>(static_cast<char*>(meta) + lo.status);
-  a.status_w = reinterpret_cast<int32_t*>(static_cast<char*>(meta) + lo.status);
   a.seq_ids = seq_ids;
   a.cu = cu;
   a.q = static_cast<const uint16_t*>(q);
@@ -1527,8 +1489,7 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.scale_log2 = c.softmax_scale * 1.4426950408889634f;
   // the timing events bracket every pass
   if (ev_start) (void)hipEventRecord(ev_start, st);
-  hipLaunchKernelGGL(prefill_list_kernel, dim3(n), dim3(kThreads), 0, st, a);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(prefill_tile_mla_kernel, dim3((max_len + 31) / 32, n, 2), dim3(kThreads), 0, st, a);
   e = hipGetLastError();
