@@ -32,6 +32,8 @@
 //    registers.
 //  * Online softmax in the exp2 domain: per-lane max over its 8 scores, then
 //    two cross-row shuffles; the running sum stays per lane until the end.
+#include <type_traits>
+
 #include "dms_common.h"
 #include "dms_fp8.h"
 
@@ -1096,6 +1098,12 @@ __device__ __forceinline__ void write_state(const FusedArgs& f, const int4* s_de
 // of the S merges them (at most four partials, one coherent round trip).
 constexpr int kHeadBlockTiles = 64;
 constexpr int kHeadBlockParts = 4;
+// Heads of at most this many tiles are not split: at 2 heads of 10 tiles the
+// launch took 14.3 us with S = 4 (publishing, counting and merging the parts
+// is three more dependent round trips) and 11 us with S = 1; at 2 or 64 heads
+// of 40 tiles S = 4 is still the faster (20.2 and 25.5 us against 22.3 and
+// 26.8).
+constexpr int kWholeHeadTiles = 12;
 
 template <int D, bool FP8>
 __device__ __forceinline__ void decode_head_block(const LdsPlan& plan, int hh, int S, int s,
@@ -1231,11 +1239,15 @@ __global__ __launch_bounds__(256, 1) void decode_step_kernel(
   const int nb = gridDim.x;
   const int T = __builtin_amdgcn_readfirstlane(total);
   // every workgroup takes the same decision from the same plan
-  int wide = 0;
-  for (int hh = threadIdx.x; hh < a.NH; hh += blockDim.x) wide |= s_cum[hh + 1] - s_cum[hh] > kHeadBlockTiles;
+  int wide = 0, split = 0;
+  for (int hh = threadIdx.x; hh < a.NH; hh += blockDim.x) {
+    wide |= s_cum[hh + 1] - s_cum[hh] > kHeadBlockTiles;
+    split |= s_cum[hh + 1] - s_cum[hh] > kWholeHeadTiles;
+  }
   wide = __syncthreads_or(wide);
+  split = __syncthreads_or(split);
   if (!wide && a.NH <= nb) {
-    const int S = min(kHeadBlockParts, nb / a.NH);
+    const int S = split ? min(kHeadBlockParts, nb / a.NH) : 1;
     if (static_cast<int>(blockIdx.x) < a.NH * S)
       decode_head_block<D, FP8>(LdsPlan{s_cum, s_desc, T, 1, a.NH}, blockIdx.x / S, S, blockIdx.x % S,
                                 f.st.page_table, pool, q, k_in, v_in, head_cnt, part_ml, part_acc, out, a, s_fold,
@@ -1250,6 +1262,271 @@ __global__ __launch_bounds__(256, 1) void decode_step_kernel(
   }
   // the workgroup whose count completed the launch's writes the new state
   if (wid == 0 && __shfl(ticket, 0, 64) == nb - 1) write_state(f, s_desc, s_aux, new_top, threadIdx.x & 63);
+}
+
+// ---------------------------------------------------------------------------
+// Calls of few short heads: one workgroup per head, planned while it streams.
+// Such a call is a chain of dependent round trips to memory, not a stream (a
+// few hundred KB in all), so the chain is what this launch shortens.  Eleven
+// waves stream the head, each through its own loads of what it needs of the
+// state (sequence id -> position, length and the page table's row, one entry
+// per lane -> ring entry, with the first tiles already in flight), while the
+// twelfth plans the whole call (validation, page pops, the new state of every
+// head).  They meet once before anything is written.  The eleven results fold
+// through LDS, so nothing is merged through memory.  Taken where a head's
+// page table bounds its tiles by kShortTiles, since only the host's capacity
+// is known at launch, and the call has at most kShortHeads heads (one
+// workgroup per CU).  Measured against the launch above: 2 heads of 10 tiles
+// 14.4 -> 6.6 us, 2 heads of 40 tiles 20.2 -> 16.0 us, 64 heads of 40 tiles
+// 25.5 -> 18.6 us.  Eight waves with two tiles in flight each ran 6.7, 16.2
+// and 19.0 us, sixteen waves 25 us for 40 tiles (128 registers each: the
+// stream spills).
+// ---------------------------------------------------------------------------
+constexpr int kShortTiles = 64;     // 32-slot tiles of one head (one page-table entry per lane)
+constexpr int kShortHeads = 256;
+constexpr int kShortWaves = 12;     // streaming waves, then the planner
+constexpr int kShortStreams = kShortWaves - 1;
+constexpr int kShortPer = kShortHeads / 64;   // heads per lane of the planner
+
+// Rows at or past `valid` of a fully loaded last tile: value elements (and
+// FP8 scales) zeroed, as load_tail does; compute_tile hides their scores.
+template <int D>
+__device__ inline void mask_tail(Frag<D>& f, int valid, int G) {
+  const int nv = valid - 8 * G;
+  u32x4 keep;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) keep[j] = (2 * j < nv ? 0x0000FFFFu : 0u) | (2 * j + 1 < nv ? 0xFFFF0000u : 0u);
+#pragma unroll
+  for (int b = 0; b < D / 16; ++b) f.vt[b] &= keep;
+}
+template <int D>
+__device__ inline void mask_tail(FragF8<D>& f, int valid, int G) {
+  const int nv = valid - 8 * G;
+  const uint64_t keep8 = nv >= 8 ? ~0ull : (nv <= 0 ? 0ull : (~0ull >> (8 * (8 - nv))));
+  const uint32_t klo = static_cast<uint32_t>(keep8), khi = static_cast<uint32_t>(keep8 >> 32);
+#pragma unroll
+  for (int p = 0; p < D / 32; ++p) f.v[p] &= u32x4{klo, khi, klo, khi};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if ((i & 1) * 4 + c >= nv) f.s[i][c] = 0u;
+}
+
+// The planner wave: rule R1 for every head of the call, head 64 k + lane in
+// entry k.  Returns the error of the call (DMS_OK: none; a sticky error set
+// before counts as one), the same in every workgroup.
+struct ShortPlan {
+  int s[kShortPer], pos[kShortPer], dec[kShortPer], L[kShortPer], slot[kShortPer], fresh[kShortPer], page[kShortPer];
+  int new_top;
+};
+__device__ __forceinline__ int short_plan(const FusedArgs& f, ShortPlan& p, uint32_t* s_seen, int lane) {
+  const int NH = f.n * f.H;
+  for (int i = lane; i < ((f.max_seqs + 31) >> 5); i += 64) s_seen[i] = 0;
+  const int status = load_status(f.status), top0 = *f.st.top;
+#pragma unroll
+  for (int k = 0; k < kShortPer; ++k) {
+    const int hh = 64 * k + lane;
+    p.s[k] = hh < NH ? f.seq_ids[hh / f.H] : 0;
+    p.dec[k] = hh < NH ? token_decision(f.flags, f.q_dec, hh, f.H, f.g, f.D, f.bias) : 0;
+  }
+  int bad = 0;
+#pragma unroll
+  for (int k = 0; k < kShortPer; ++k) {
+    const int hh = 64 * k + lane;
+    const bool in = p.s[k] >= 0 && p.s[k] < f.max_seqs;
+    bad |= !in;
+    const int s = in ? p.s[k] : 0;   // clamped: the values are only used once every id is known to be valid
+    p.pos[k] = hh < NH ? f.st.pos[s] : 0;
+    p.L[k] = hh < NH ? f.st.len[s * f.H + hh % f.H] : 0;
+    if (hh < NH && hh % f.H == 0 && in) {
+      const uint32_t bit = 1u << (s & 31);
+      if (atomicOr(&s_seen[s >> 5], bit) & bit) bad = 1;
+    }
+  }
+  if (status != 0) return status;
+  if (__builtin_amdgcn_ballot_w64(bad)) return DMS_ERR_BAD_SEQ;
+  int cap = 0, pops = 0;
+#pragma unroll
+  for (int k = 0; k < kShortPer; ++k) {
+    const int hh = 64 * k + lane;
+    p.slot[k] = p.fresh[k] = 0;
+    p.page[k] = -1;
+    int need = 0;
+    if (hh < NH) {
+      const int32_t e = f.st.ring[static_cast<size_t>(p.s[k] * f.H + hh % f.H) * f.w + p.pos[k] % f.w];
+      const bool reuse = takes_old_slot(p.pos[k], f.w, e, p.dec[k], f.immediate);
+      p.slot[k] = reuse ? static_cast<int>(static_cast<uint32_t>(e) & ~kFlagBit) : p.L[k];
+      p.fresh[k] = !reuse;
+      cap |= p.fresh[k] && p.slot[k] >= f.max_slots;
+      need = p.fresh[k] && (p.slot[k] & (f.P - 1)) == 0;
+      p.L[k] += p.fresh[k];
+    }
+    const int inc = wave_inclusive_scan(need);
+    const int at = pops + inc - need;   // pops go in call order, then head
+    if (need && at < top0) p.page[k] = f.st.stack[top0 - 1 - at];
+    pops += __shfl(inc, 63, 64);
+  }
+  if (__builtin_amdgcn_ballot_w64(cap)) return DMS_ERR_CAPACITY;
+  if (pops > top0) return DMS_ERR_OUT_OF_PAGES;
+  p.new_top = top0 - pops;
+  return DMS_OK;
+}
+
+__device__ __forceinline__ void short_write_state(const FusedArgs& f, const ShortPlan& p, int lane) {
+  const int NH = f.n * f.H;
+#pragma unroll
+  for (int k = 0; k < kShortPer; ++k) {
+    const int hh = 64 * k + lane;
+    if (hh < NH) {
+      const size_t sh = static_cast<size_t>(p.s[k]) * f.H + hh % f.H;
+      const uint32_t fb = p.dec[k] ? kFlagBit : 0u;
+      if (f.flags_out != nullptr) f.flags_out[hh] = static_cast<uint8_t>(p.dec[k]);
+      if (p.page[k] >= 0) f.st.page_table[sh * f.maxp + p.slot[k] / f.P] = p.page[k];
+      if (p.fresh[k]) f.st.len[sh] = p.L[k];
+      f.st.ring[sh * f.w + p.pos[k] % f.w] = static_cast<int32_t>(static_cast<uint32_t>(p.slot[k]) | fb);
+      f.st.slot_meta[sh * f.max_slots + p.slot[k]] = static_cast<int32_t>(static_cast<uint32_t>(p.pos[k]) | fb);
+      if (hh % f.H == 0) f.st.pos[p.s[k]] = p.pos[k] + 1;
+    }
+  }
+  if (lane == 0) {
+    *f.st.top = p.new_top;
+    __hip_atomic_store(f.plan_ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+template <int D, bool FP8>
+__global__ __launch_bounds__(64 * kShortWaves, 1) void decode_short_kernel(
+    FusedArgs f, char* __restrict__ pool, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_in,
+    const uint16_t* __restrict__ v_in, float* __restrict__ out, DecodeParams a) {
+  using Tile = typename std::conditional<FP8, FragF8<D>, Frag<D>>::type;
+  constexpr size_t kTileBytes = FP8 ? static_cast<size_t>(D) * 64 + 256 : static_cast<size_t>(D) * 128;
+  __shared__ uint32_t s_seen[kMaxSeqs / 32];
+  __shared__ int s_err, s_page;
+  __shared__ f32x4 fold[kShortStreams][D / 16][64];
+  __shared__ float2 fold_ml[kShortStreams][kMaxGroup];
+  const int lane = threadIdx.x & 63;
+  const int r = lane & 15, G = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hh = blockIdx.x;
+  if (wid == kShortStreams) {
+    ShortPlan p;
+    const int err = short_plan(f, p, s_seen, lane);
+    if (lane == 0) s_err = err;
+    if (err == DMS_OK) {
+      // page popped for this workgroup's head
+      int mine = -1;
+#pragma unroll
+      for (int k = 0; k < kShortPer; ++k)
+        if (k == hh >> 6) mine = p.page[k];
+      mine = __shfl(mine, hh & 63, 64);
+      if (lane == 0) s_page = mine;
+    }
+    __syncthreads();
+    if (err != DMS_OK) {
+      if (lane == 0) set_status(f.status, err);
+      return;
+    }
+    // every wave of this workgroup has read the state: count it in; the
+    // workgroup that completes the launch's count writes the new state
+    int ticket = 0;
+    if (lane == 0) ticket = atomicAdd(f.plan_ctr, 1);
+    if (__shfl(ticket, 0, 64) == static_cast<int>(gridDim.x) - 1) short_write_state(f, p, lane);
+  } else {
+    const int h = hh % f.H;
+    const int s = min(max(f.seq_ids[hh / f.H], 0), f.max_seqs - 1);   // clamped: only used for a valid call
+    const int dec = token_decision(f.flags, f.q_dec, hh, f.H, f.g, f.D, f.bias);
+    u32x4 qf[D / 32];
+    const char* qrow = reinterpret_cast<const char*>(q + (static_cast<size_t>(hh) * a.g + r) * D);
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i) qf[i] = r < a.g ? ldg16(qrow + (32 * i + 8 * G) * 2) : u32x4{0u, 0u, 0u, 0u};
+    if (a.zero_neuron && r == 0 && G == 0) qf[0][0] &= 0xFFFF0000u;   // the borrowed decision neuron (App. C)
+    const size_t sh = static_cast<size_t>(s) * f.H + h;
+    const int pos = __builtin_amdgcn_readfirstlane(f.st.pos[s]);
+    const int L = __builtin_amdgcn_readfirstlane(f.st.len[sh]);
+    int pt = lane < f.maxp ? f.st.page_table[sh * f.maxp + lane] : 0;   // page of lane's slots lane * P ..
+    // tiles of this wave: its share of those before the append; a tile that
+    // the append starts goes to the last wave
+    const int nt = min((L + kTile - 1) / kTile, kShortTiles);
+    const int t_lo = wid * nt / kShortStreams;
+    int t_hi = (wid + 1) * nt / kShortStreams;
+    const int tpp = a.log2P - 5;
+    auto tile_of = [&](int t) -> char* {
+      return pool + static_cast<size_t>(__builtin_amdgcn_readlane(pt, t >> tpp)) * a.page_bytes +
+             static_cast<size_t>(t & ((1 << tpp) - 1)) * kTileBytes;
+    };
+    auto load = [&](Tile& t, const char* p) {
+      if constexpr (FP8) load_tile_f8<D>(t, p, lane, G); else load_tile<D>(t, p, lane);
+    };
+    const int32_t e = f.st.ring[sh * f.w + pos % f.w];
+    Tile fa;
+    if (t_lo < t_hi) load(fa, tile_of(t_lo));
+    const bool reuse = takes_old_slot(pos, f.w, __builtin_amdgcn_readfirstlane(e), dec, f.immediate);
+    const int slot = reuse ? static_cast<int>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(e)) & ~kFlagBit) : L;
+    const int Lnew = L + !reuse;
+    const int zt = slot >> 5;
+    __syncthreads();
+    if (s_err != DMS_OK) return;
+    const int page = __builtin_amdgcn_readfirstlane(s_page);
+    if (page >= 0 && lane == slot >> a.log2P) pt = page;   // the page table may not hold it yet
+    if (wid == kShortStreams - 1 && zt == nt) t_hi = nt + 1;
+    if (zt >= t_lo && zt < t_hi) {
+      // the token appended by this call, before this wave's loads of its tile
+      // (same-wave stores and loads to one address stay in order)
+      char* tile = tile_of(zt);
+      const int j = slot & 31;
+      if constexpr (FP8) {
+        if (lane < D / 8)
+          fp8_store_token(tile, j, D, lane, reinterpret_cast<const uint4*>(k_in + static_cast<size_t>(hh) * D)[lane],
+                          reinterpret_cast<const uint4*>(v_in + static_cast<size_t>(hh) * D)[lane]);
+      } else {
+        if (lane < D / 8)
+          *reinterpret_cast<u32x4*>(tile + k_elem_off(j, 8 * lane)) =
+              reinterpret_cast<const u32x4*>(k_in + static_cast<size_t>(hh) * D)[lane];
+#pragma unroll
+        for (int x = lane; x < D; x += 64)
+          *reinterpret_cast<uint16_t*>(tile + v_elem_off(j, x, D)) = v_in[static_cast<size_t>(hh) * D + x];
+      }
+      if (zt == t_lo) load(fa, tile);
+    }
+    Acc<D> acc;
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) acc.o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc.m = -INFINITY;
+    acc.l = 0.f;
+    auto compute = [&](Tile& t, int at) {
+      const int valid = Lnew - at * kTile;
+      if (valid < kTile) mask_tail<D>(t, valid, G);
+      if constexpr (FP8) compute_tile_f8<D>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
+      else compute_tile<D>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
+    };
+    for (int t = t_lo; t < t_hi; ++t) {
+      if (t > t_lo) load(fa, tile_of(t));
+      compute(fa, t);
+    }
+    float l = acc.l;
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) fold[wid][b][lane] = acc.o[b];
+    if (G == 0) fold_ml[wid][r] = make_float2(acc.m, l);
+  }
+  __syncthreads();
+  // wave b folds row block b of the waves' results (the appended token is
+  // attended, so some wave has a finite maximum)
+  if (wid >= D / 16 || r >= a.g) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kShortStreams; ++j) M = fmaxf(M, fold_ml[j][r].x);
+  float den = 0.f;
+  f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < kShortStreams; ++j) {
+    const float wj = __builtin_amdgcn_exp2f(fold_ml[j][r].x - M);   // 0 for a wave without tiles
+    den += wj * fold_ml[j][r].y;
+    num += wj * fold[j][wid][lane];
+  }
+  *reinterpret_cast<f32x4*>(out + (static_cast<size_t>(hh) * a.g + r) * D + 4 * G + 16 * wid) = num * (1.0f / den);
 }
 
 // Split heads of a planned decode launch, merged after it: one wave per call
@@ -1349,6 +1626,12 @@ DecodeParams decode_params(const dms_config& c, const Layout& lo, int D, int n, 
   return a;
 }
 
+// Whether a decode step takes decode_short_kernel (see there).
+bool short_call(const dms_config& c, int n) {
+  return static_cast<int64_t>(c.max_pages_per_head) * c.page_size <= kShortTiles * kTile &&
+         static_cast<int64_t>(n) * c.num_kv_heads <= kShortHeads;
+}
+
 template <int D, bool FP8>
 hipError_t launch_decode_step_d(const dms_config& c, const Layout& lo, void* meta, void* ws,
                                 void* pool, int layer, int n, const int32_t* seq_ids,
@@ -1378,7 +1661,12 @@ hipError_t launch_decode_step_d(const dms_config& c, const Layout& lo, void* met
   f.D = D;
   const DecodeParams a = decode_params(c, lo, D, n, waves);
   if (ev_start) (void)hipEventRecord(ev_start, st);
-  hipLaunchKernelGGL((decode_step_kernel<D, FP8>), dim3(waves / kWavesPerBlock), dim3(256), 0, st, f,
+  if (short_call(c, n))
+    hipLaunchKernelGGL((decode_short_kernel<D, FP8>), dim3(a.NH), dim3(64 * kShortWaves), 0, st, f,
+                       static_cast<char*>(pool), static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                       static_cast<const uint16_t*>(v), out, a);
+  else
+    hipLaunchKernelGGL((decode_step_kernel<D, FP8>), dim3(waves / kWavesPerBlock), dim3(256), 0, st, f,
                      reinterpret_cast<int32_t*>(w + lo.ws_head_cnt), static_cast<char*>(pool),
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                      static_cast<const uint16_t*>(v), reinterpret_cast<float2*>(w + lo.ws_part_ml),
@@ -1491,7 +1779,7 @@ constexpr int kFuseCallHeads = 128;
 bool decode_step_fusable(const dms_config& c, int n) {
   static_assert(kFuseCallHeads <= kFuseMaxHeads, "fused calls are planned in LDS");
   return c.kv_format != DMS_KV_MLA && c.quest_page_budget == 0 &&
-         static_cast<int64_t>(n) * c.num_kv_heads <= kFuseCallHeads;
+         (static_cast<int64_t>(n) * c.num_kv_heads <= kFuseCallHeads || short_call(c, n));
 }
 
 hipError_t launch_decode_step(const dms_config& c, const Layout& lo, void* meta, void* ws, void* pool,

@@ -1,0 +1,56 @@
+"""Decode steps of few short heads (one workgroup per head, planned while it
+streams): heads with no, one and many tiles, tiles the append starts, every
+page size and group, popped pages, capacity and pool errors.  State bit-exact,
+outputs within the decode tolerance (tests/dms_testlib.py)."""
+import numpy as np
+import pytest
+
+from dms_testlib import SeqInputs, bf16_to_f32, to_dev
+from test_decode_parity import _append_chunks, _decode_steps, _mk, _oracle_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,P,g,w,H,starts,p", [
+    (64, 32, 1, 1, 1, (0,), 0.5), (128, 64, 6, 16, 2, (31, 0), 0.5), (128, 256, 16, 40, 1, (1990,), 0.0),
+    (64, 128, 5, 7, 3, (500, 95, 63), 0.75), (128, 32, 7, 300, 4, (352, 351), 0.875),
+    (64, 64, 2, 16, 64, (40, 33, 64, 1), 0.5)])       # 256 heads: one per compute unit
+def test_steps(D, P, g, w, H, starts, p):
+    steps = 6
+    maxp = 2048 // P
+    n = len(starts)
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=n, num_kv_heads=H, group_size=g, head_dim=D, window=w,
+                               page_size=P, num_pages=H * sum(-(-(s + steps) // P) for s in starts),
+                               max_pages_per_head=maxp, max_chunk_tokens=max(1, sum(starts))))
+    orc = _oracle_for(cfg)
+    seqs = list(range(n))
+    inputs = {s: SeqInputs(11, 0, s, starts[s] + steps, H, g, D, p) for s in seqs}
+    if any(starts):
+        _append_chunks(dms, cache, orc, seqs, inputs, {s: 0 for s in seqs}, dict(enumerate(starts)), max(starts))
+    _decode_steps(dms, cache, orc, seqs, inputs, dict(enumerate(starts)), steps, g)
+    cache.close()
+
+
+@pytest.mark.parametrize("pages,maxp,err", [(1, 4, "DMS_ERR_OUT_OF_PAGES"), (8, 1, "DMS_ERR_CAPACITY")])
+def test_refused_step_changes_nothing(pages, maxp, err):
+    import torch
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=1, num_kv_heads=1, group_size=2, head_dim=64, window=64,
+                               page_size=32, num_pages=pages, max_pages_per_head=maxp, max_chunk_tokens=32))
+    orc = _oracle_for(cfg)
+    inputs = {0: SeqInputs(12, 0, 0, 33, 1, 2, 64, 0.0)}
+    _append_chunks(dms, cache, orc, [0], inputs, {0: 0}, {0: 32}, 32)
+    x = inputs[0]
+    sid = to_dev(np.zeros(1, np.int32))
+    out = torch.full((1, 2, 64), 7.0, device="cuda")
+    args = (to_dev(x.q[32][None]), to_dev(x.k[32][None]), to_dev(x.v[32][None]), to_dev(x.flags[32][None]), out)
+    for _ in range(2):   # the second call finds the sticky status
+        dms.dms_decode_step(cache.ctx, 0, 1, sid, *args)
+        assert dms.dms_status(cache.ctx) == getattr(dms, err)
+    assert bool((out == 7.0).all())
+    view = cache.export(0)
+    assert view.pos[0] == 32 and view.L[0, 0] == 32
+    dms.dms_clear_status(cache.ctx)
+    dms.dms_decode_step(cache.ctx, 0, 1, to_dev(np.full(1, 5, np.int32)), *args)
+    assert dms.dms_status(cache.ctx) == dms.DMS_ERR_BAD_SEQ
+    assert bool((out == 7.0).all())
+    cache.close()
