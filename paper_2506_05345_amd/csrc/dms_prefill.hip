@@ -91,6 +91,12 @@ __device__ inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// Attention grid row: call head, first token and length of its chunk, state
+// head, position and live length before the chunk, first workspace tile.
+struct __attribute__((aligned(32))) PrefillRow {
+  int hh, tok0, C, sh, p0, L0, tile0, pad;
+};
+
 struct PrefillArgs {
   const int32_t* status;
   const int32_t* seq_ids;
@@ -107,7 +113,7 @@ struct PrefillArgs {
   int32_t* list;          // [H][total]: chunk-local indices of kept tokens
   int32_t* list_cnt;      // [n * H]
   int32_t* kept_before;   // [H][tph]: kept chunk tokens before chunk position 32 j (tile indexing)
-  int32_t* order;         // [n * H]: (sequence, head) of attention grid row y, or null (row y itself)
+  PrefillRow* rows;       // [n * H]: attention grid rows, heaviest first
   int32_t* work_ctr;      // attention work items taken so far (zeroed by pass 0)
   int nx, items;          // query blocks per grid row; rows x nx
   char* tiles;            // [2][H][tph] tiles: chunk tokens, then compacted kept tokens
@@ -151,22 +157,37 @@ __device__ inline size_t ws_kb(const PrefillArgs& a, int h, int i, int j) {
 // the longest heads start first and the short ones fill the tail): one
 // workgroup ranks the n * H (sequence, head) rows by their live length plus
 // half their kept chunk tokens (the cached keys every block of the row
-// attends to, and the mean of its kept-prefix keys); ties keep row order.
+// attends to, and the mean of its kept-prefix keys); ties keep row order, and
+// calls of more than kOrderMax rows keep theirs.  Each row's descriptor saves
+// a work item three dependent loads.
 constexpr int kOrderMax = 512;
 __global__ __launch_bounds__(kThreads) void prefill_order_kernel(PrefillArgs a) {
   __shared__ int work[kOrderMax];
   if (load_status(a.status) != 0) return;
   const int NH = a.n * a.H;
-  for (int x = threadIdx.x; x < NH; x += kThreads) {
-    const int i = x / a.H, h = x % a.H;
-    work[x] = a.len[a.seq_ids[i] * a.H + h] + a.list_cnt[x] / 2;
-  }
+  const bool ranked = NH <= kOrderMax;
+  if (ranked)
+    for (int x = threadIdx.x; x < NH; x += kThreads)
+      work[x] = a.len[a.seq_ids[x / a.H] * a.H + x % a.H] + a.list_cnt[x] / 2;
   __syncthreads();
-  for (int x = threadIdx.x; x < NH; x += kThreads) {
-    const int wx = work[x];
-    int rank = 0;
-    for (int y = 0; y < NH; ++y) rank += work[y] > wx || (work[y] == wx && y < x);
-    a.order[rank] = x;
+  for (int x = blockIdx.x * kThreads + threadIdx.x; x < NH; x += gridDim.x * kThreads) {
+    int rank = x;
+    if (ranked) {
+      rank = 0;
+      const int wx = work[x];
+      for (int y = 0; y < NH; ++y) rank += work[y] > wx || (work[y] == wx && y < x);
+    }
+    const int i = x / a.H, s = a.seq_ids[i], sh = s * a.H + x % a.H, tok0 = a.cu[i];
+    PrefillRow r;
+    r.hh = x;
+    r.tok0 = tok0;
+    r.C = a.cu[i + 1] - tok0;
+    r.sh = sh;
+    r.p0 = a.pos[s];
+    r.L0 = a.len[sh];
+    r.tile0 = tok0 / 32 + i;
+    r.pad = 0;
+    a.rows[rank] = r;
   }
 }
 
@@ -369,7 +390,7 @@ __global__ __launch_bounds__((attn_threads<D, FP8>()), (512 / attn_threads<D, FP
   // attention of work item `item` = (grid row item / nx, query block item % nx)
   auto attend = [&](int item) {
   const int row = item / a.nx;
-  const int hh = a.order ? a.order[row] : row;
+  const int hh = a.rows[row].hh;
   const int i = hh / a.H, h = hh % a.H;
   const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
   const int pb0 = (item - row * a.nx) * a.PB;
@@ -658,20 +679,37 @@ __global__ __launch_bounds__((attn_threads<D, FP8>()), (512 / attn_threads<D, FP
   }
 }
 
-// ---- bf16 pages under delayed eviction: tiles copied by the hardware.
-// Every key source is a plain copy -- pool tiles with their slot metadata,
-// workspace tiles with the metadata pass 1 wrote -- so global -> LDS loads
-// (global_load_lds) move tiles and key rows into four LDS buffers, each tile
-// by one wave (the address work is done once per tile) two tiles ahead of
-// the one being attended, with no staging registers or LDS stores.  Rows
-// past a source's end are fixed up when read: pool slots past the live
-// length hold stale data (values zeroed in registers, keys hidden),
-// kept-list rows from the band on are hidden.
+// ---------------------------------------------------------------------------
+// Attention pass under delayed eviction, 32x32 MFMA products.  A wave holds
+// 32 columns; keys go through LDS 64 at a time (two tiles, two buffers): both
+// tiles' scores, one column maximum and (rare) rescale, the weights, both
+// tiles' value products, one barrier.  A tile read from LDS feeds 32 columns
+// with half the MFMA and LDS read instructions of 16x16 products, and the
+// pool's tile order serves them with one base address per operand and
+// constant offsets:
+//   keys: lane l of k-step s takes dims 16 s + 8 (l / 32) .. + 7 of token
+//     row_token(l % 32) (accumulator registers 8 y .. 8 y + 7 are then tokens
+//     16 y + 8 (l / 32) .. + 7, the B operand of half y of the value product);
+//   values: lane l of (32-dim block b, half y) takes tokens 16 y + 8 (l / 32)
+//     .. + 7 of dim 32 b + l % 32.
+// Both are free of bank conflicts (8-lane runs of 128 bytes).
+//
+// bf16 pages (four waves, two workgroups per CU): every key source is a plain
+// copy -- pool tiles with their slot metadata, workspace tiles with the
+// metadata pass 1 wrote -- so global -> LDS loads move a quarter of a stage
+// per wave while the stage before it is attended.  FP8 pages (eight waves at
+// d = 128: each of a chunk's query blocks stages every cached tile of its
+// head, so more columns per workgroup means fewer dequantizations): codes go
+// through registers and are dequantized into the same order.  Rows past a
+// source's end are fixed up when read: pool slots past the live length hold
+// stale data (values zeroed in registers, keys hidden), kept-list rows from
+// the band on are hidden.
 //
 // The LDS destination of a copy goes in M0, written by the same inline
-// assembly statement as the load; nothing else in this kernel reads M0.  The
+// assembly statement as the load; nothing else in this file reads M0.  The
 // compiler does not count these loads, so the kernel waits for them itself
-// (vmcnt) before the barrier that publishes a tile.
+// (vmcnt) before the barrier that publishes a stage.
+// ---------------------------------------------------------------------------
 #define DMS_LDS __attribute__((address_space(3)))
 #define DMS_CONST __attribute__((address_space(4)))
 
@@ -690,337 +728,331 @@ __device__ inline void lds_copy4(const char* g, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" : : "s"(m0), "v"(g) : "memory", "m0");
 }
 
-// ---- attention pass, the two column blocks of a wave half a tile apart.
-// With every step of a tile in one order (scores, weights, PV) the weights'
-// VALU work (maxima, exponentials, bf16 rounding, denominators) waits for the
-// score MFMAs and the PV MFMAs wait for it.  Here a tile k is attended in two
-// halves, each pairing one block's weights with MFMAs of the other block:
-//   A(k): weights of block 0 on tile k   | scores of block 1 on tile k, then
-//                                        | PV of block 1 on tile k - 1
-//   B(k): weights of block 1 on tile k   | scores of block 0 on tile k + 1,
-//                                        | then PV of block 0 on tile k
-// A half starts with its block's mask, column maxima and (rare, wave-uniform)
-// rescale; the rest is one straight stretch in which scheduling groups
-// alternate single MFMAs with a share of the VALU work and of the LDS operand
-// reads.  Tile k + 1's keys and key rows are read during A(k) (after the
-// score MFMAs of tile k have taken theirs), tile k's values at its end, so
-// one register set holds each operand.  Four LDS buffers: at the start of
-// A(k) one barrier publishes tile k + 1 and frees the buffer of tile k - 1,
-// into which tile k + 3 is copied.
-template <int M, int V, int R, int I = 0>
-__device__ __forceinline__ void interleave() {
-  if constexpr (I < M) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-    constexpr int nr = R / M + (I < R % M ? 1 : 0);
-    if constexpr (nr > 0) __builtin_amdgcn_sched_group_barrier(0x100, nr, 0);   // LDS reads
-    constexpr int nv = V / M + (I < V % M ? 1 : 0);
-    if constexpr (nv > 0) __builtin_amdgcn_sched_group_barrier(0x002, nv, 0);   // VALU
-    interleave<M, V, R, I + 1>();
-  }
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+__device__ inline f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// max / sum over the two lanes of one column (l and l + 32)
+__device__ inline float col_max32(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ inline float col_sum32(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+__device__ inline int row_token(int r) {
+  return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
 }
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_pipe_kernel(PrefillArgs a) {
-  constexpr int NQ = 2;
-  constexpr int kBuf = 4;
-  constexpr int kTB = D * 128;
-  constexpr int kLoads = D / 32;   // 1 KB copies per wave and tile (four waves)
-  constexpr int KS = D / 32;       // k-steps of a score MFMA chain
-  constexpr int OB = D / 16;       // 16-dim output blocks
-  __shared__ __attribute__((aligned(16))) char tile_lds[kBuf][kTB];
-  __shared__ __attribute__((aligned(16))) uint32_t meta_lds[kBuf][64];   // rows 0..31, twice
+template <int D, bool FP8>
+constexpr int delayed_waves() { return attn_threads<D, FP8>() / 64; }
+
+template <int D, bool FP8>
+__global__ __launch_bounds__((64 * delayed_waves<D, FP8>()), (8 / delayed_waves<D, FP8>()))
+void prefill_delayed_kernel(PrefillArgs a) {
+  constexpr int NW = delayed_waves<D, FP8>();
+  constexpr int kTB = D * 128;          // one staged (bf16) tile
+  constexpr size_t kSB = FP8 ? static_cast<size_t>(D) * 64 + 256 : static_cast<size_t>(kTB);   // one stored tile
+  constexpr int KS = D / 16, OB = D / 32;
+  __shared__ __attribute__((aligned(16))) char tile_lds[2][2 * kTB];
+  __shared__ __attribute__((aligned(16))) uint32_t meta_lds[2][2][64];   // [buffer][tile], rows 0..31 twice
+  __shared__ __attribute__((aligned(16))) float scale_lds[FP8 ? 2 : 1][2][64];   // FP8: tile scales
   __shared__ int item_lds[2];
   if (load_status(a.status) != 0) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hf = lane >> 5;
+  const int Hq = a.H * a.g;
+  const float thr = kRescale / a.scale_log2, sl2 = a.scale_log2;
+  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
+  const int kt = row_token(lane & 31);
+  const char* k_base = tile_lds[0] + ((kt >> 2) & 1) * 1024 + hf * 256 + (4 * (kt >> 3) + (kt & 3)) * 16;
+  const char* v_base = tile_lds[0] + D * 64 + ((lane >> 4) & 1) * 1024 + hf * 256 + (lane & 15) * 16;
+
   // attention of work item `item` = (grid row item / nx, query block item % nx)
   auto attend = [&](int item) {
   const int row = item / a.nx;
-  const int hh = a.order ? a.order[row] : row;
-  const int i = hh / a.H, h = hh % a.H;
-  const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
+  typedef int __attribute__((ext_vector_type(8))) i32x8;
+  const i32x8 rd = *((const DMS_CONST i32x8*)(a.rows + row));   // see prefill_order_kernel
+  const int hh = rd[0], tok0 = rd[1], C = rd[2], sh = rd[3], p0 = rd[4], L0 = rd[5], tix = rd[6];
   const int pb0 = (item - row * a.nx) * a.PB;
   if (pb0 >= C) return;
-  const int s = a.seq_ids[i];
-  const int sh = s * a.H + h;
-  const int p0 = a.pos[s];
-  const int L0 = a.len[sh];
+  const int h = hh % a.H;
   const int t0 = p0 + pb0;
   const int t1 = p0 + min(C, pb0 + a.PB);
   const int band_c0 = (max(0, pb0 - a.w + 1) >> 5) << 5;   // chunk-local, < C
   // kept chunk keys strictly before the band, counted by pass 0
-  const int n_pre = a.kept_before[ws_kb(a, h, i, band_c0 >> 5)];
+  const int n_pre = ((const DMS_CONST int32_t*)a.kept_before)[static_cast<size_t>(h) * a.tph + tix + (band_c0 >> 5)];
   const int nc = (L0 + 31) >> 5;
   const int np = (n_pre + 31) >> 5;
   const int nb = (t1 - p0 - band_c0 + 31) >> 5;
   const int ntiles = nc + np + nb;
-  const char* pre_tiles = a.tiles + ws_tile(a, 1, h, i, 0) * kTB;
-  const char* band_tiles = a.tiles + ws_tile(a, 0, h, i, band_c0 >> 5) * kTB;
-  const uint32_t* pre_meta = a.tmeta + ws_tile(a, 1, h, i, 0) * 32;
-  const uint32_t* band_meta = a.tmeta + ws_tile(a, 0, h, i, band_c0 >> 5) * 32;
+  // workspace tile of (region, head, tile): the call's tiles of one region and head are consecutive
+  const size_t pre0 = static_cast<size_t>(a.H + h) * a.tph + tix;
+  const size_t band0 = static_cast<size_t>(h) * a.tph + tix + (band_c0 >> 5);
   const DMS_CONST int32_t* pt = (const DMS_CONST int32_t*)(a.page_table + static_cast<size_t>(sh) * a.maxp);
   const uint32_t* smeta = reinterpret_cast<const uint32_t*>(a.slot_meta + static_cast<size_t>(sh) * a.max_slots);
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, G = lane >> 4;
-  const int Hq = a.H * a.g;
-
-  // column c of the workgroup's 128 (wave, block, lane r) is query head c % g
-  // at position t0 + c / g; a position's g heads may straddle two column
-  // blocks, so only the last 128 mod g columns go unused
-  int tcol[NQ];
-  u32x4 qf[NQ][KS];
-#pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const int col = (wave * NQ + qb) * 16 + r;
-    const int pl = col / a.g, qh = col % a.g;
-    const int t = t0 + pl;
-    const bool ok = (pl < a.PB) && (t < t1);
-    tcol[qb] = ok ? t : -1;
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    const char* qrow = reinterpret_cast<const char*>(
-        a.q + (static_cast<size_t>(tok0 + (t - p0)) * Hq + h * a.g + qh) * D);
-#pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2)
-      qf[qb][s2] = ok ? *reinterpret_cast<const u32x4*>(qrow + (32 * s2 + 8 * G) * 2) : z;
-    if (a.zero_neuron && qh == 0 && G == 0) qf[qb][0][0] &= 0xFFFF0000u;
-  }
-
   // pool page of tile k (only read for k < nc)
   auto page_of = [&](int k) { return k < nc ? pt[(32 * k) >> a.log2P] : 0; };
-  // tile k is copied by wave k % 4 alone (the address work is done once per
-  // tile), 1 KB per instruction
-  auto issue = [&](int k, int page) {
-    if (wave != (k & 3)) return;
-    const char* tile;
-    const uint32_t* mt;
+  auto source = [&](int k, int page, const char*& tile, const uint32_t*& mt) {
     if (k < nc) {
       const int sb = 32 * k;
-      tile = a.pool + static_cast<size_t>(page) * a.page_bytes + static_cast<size_t>((sb & (a.P - 1)) >> 5) * kTB;
+      tile = a.pool + static_cast<size_t>(page) * a.page_bytes + static_cast<size_t>((sb & (a.P - 1)) >> 5) * kSB;
       mt = smeta + sb;
-    } else if (k < nc + np) {
-      tile = pre_tiles + static_cast<size_t>(k - nc) * kTB;
-      mt = pre_meta + (k - nc) * 32;
     } else {
-      tile = band_tiles + static_cast<size_t>(k - nc - np) * kTB;
-      mt = band_meta + (k - nc - np) * 32;
+      const size_t x = k < nc + np ? pre0 + (k - nc) : band0 + (k - nc - np);
+      tile = a.tiles + x * kSB;
+      mt = a.tmeta + x * 32;
     }
-    const int b = k % kBuf;
-    const uint32_t dst = lds_addr(tile_lds[b]);
-#pragma unroll
-    for (int m = 0; m < 4 * kLoads; ++m) lds_copy16(tile + m * 1024 + lane * 16, dst + m * 1024);
-    lds_copy4(reinterpret_cast<const char*>(mt + (lane & 31)), lds_addr(meta_lds[b]));
   };
-  // tile k has landed once the wave that copied it has no copy in flight
-  // (its next copy is issued after tile k is published)
-  auto wait_tile = [&](int k) {
-    if (wave == (k & 3)) __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  // rows of tile k that exist
+  auto rows_of = [&](int k) {
+    return k >= ntiles ? 0 : k < nc ? L0 - 32 * k : (k < nc + np ? n_pre - 32 * (k - nc) : 32);
   };
 
-  f32x4 o[NQ][OB];
-  float m_ref[NQ], l_run[NQ];
+  // ---- staging of stage st (tiles 2 st, 2 st + 1; the last one again past the end)
+  constexpr int kSubs = 2;
+  u32x4 cx[kSubs], sx[kSubs];      // FP8: this thread's code piece, scales (threads 0..15) of each tile
+  float ks[kSubs];                 // key scale of a key piece's token
+  uint32_t mt_reg[kSubs];
+  const int my_sub = (wave >> 1) & 1;
+  auto stage_pages = [&](int st, int (&pg)[kSubs]) {
+    if constexpr (FP8) {
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-#pragma unroll
-    for (int b = 0; b < OB; ++b) o[qb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_ref[qb] = kMInit;
-    l_run[qb] = 0.f;
-  }
-  const uint32_t lo_k = static_cast<uint32_t>(lane * 16);
-  const uint32_t lo_v = static_cast<uint32_t>(D * 64 + lane * 16);
-  const float thr = kRescale / a.scale_log2;
-  const float sl2 = a.scale_log2;
-
-  // operand registers: keys (and key rows) of one tile, values of one tile
-  u32x4 ka[KS], kb[KS], vt[OB];
-  uint32_t nrow = 0;
-  u32x4 nm0, nm1;
-  auto read_k = [&](int k) {
-    const char* tl = tile_lds[k % kBuf];
-#pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2) {
-      ka[s2] = *reinterpret_cast<const u32x4*>(tl + lo_k + s2 * 2048);
-      kb[s2] = *reinterpret_cast<const u32x4*>(tl + lo_k + 1024 + s2 * 2048);
-    }
-    nrow = meta_lds[k % kBuf][lane];
-    nm0 = *reinterpret_cast<const u32x4*>(&meta_lds[k % kBuf][8 * G]);
-    nm1 = *reinterpret_cast<const u32x4*>(&meta_lds[k % kBuf][8 * G + 4]);
-  };
-  auto read_v = [&](int k) {
-    const char* tl = tile_lds[k % kBuf];
-#pragma unroll
-    for (int b = 0; b < OB; ++b) vt[b] = *reinterpret_cast<const u32x4*>(tl + lo_v + b * 1024);
-  };
-  auto scores = [&](int qb, float (&sc)[8]) {
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2) {
-      s0 = mfma_bf16(ka[s2], qf[qb][s2], s0);
-      s1 = mfma_bf16(kb[s2], qf[qb][s2], s1);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sc[j] = s0[j];
-      sc[j + 4] = s1[j];
+      for (int u = 0; u < kSubs; ++u) pg[u] = page_of(min(2 * st + u, ntiles - 1));
+    } else {
+      pg[0] = page_of(min(2 * st + my_sub, ntiles - 1));
     }
   };
-  auto pv = [&](int qb, u32x4 pu) {
+  auto stage_load = [&](int st, int buf, const int (&pg)[kSubs]) {
+    const char* tile;
+    const uint32_t* mt;
+    if constexpr (FP8) {
 #pragma unroll
-    for (int b = 0; b < OB; ++b) o[qb][b] = mfma_bf16(vt[b], pu, o[qb][b]);
-  };
-  // mask, column max and lazy rescale of one block's scores
-  auto head = [&](int qb, float (&sc)[8], bool masked, const int (&kp)[8], const int (&kx)[8]) {
-    if (masked) {
-      const int t = tcol[qb];
+      for (int u = 0; u < kSubs; ++u) {
+        source(min(2 * st + u, ntiles - 1), pg[u], tile, mt);
+        cx[u] = *reinterpret_cast<const u32x4*>(tile + tid * 16);
+        if (tid < 2 * D) {
+          // key piece (p, h, lane L): all 16 codes belong to slot 8 (r/4) + r%4 + 4 h
+          const int r = tid & 15, j = 8 * (r >> 2) + (r & 3) + 4 * ((tid >> 6) & 1);
+          ks[u] = *reinterpret_cast<const float*>(tile + D * 64 + (j >> 3) * 64 + (j & 7) * 4);
+        }
+        if (tid < 16) sx[u] = *reinterpret_cast<const u32x4*>(tile + D * 64 + tid * 16);
+        if (tid < 64) mt_reg[u] = mt[tid & 31];
+      }
+    } else {
+      // wave w copies the keys (w even) or values of tile w / 2 of the stage
+      source(min(2 * st + my_sub, ntiles - 1), pg[0], tile, mt);
+      const char* src = tile + (wave & 1) * (D * 64) + lane * 16;
+      const uint32_t dst = lds_addr(tile_lds[0]) + buf * 2 * kTB + my_sub * kTB + (wave & 1) * (D * 64);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sc[j] = (kp[j] <= t && t < kx[j]) ? sc[j] : -INFINITY;
+      for (int m = 0; m < D / 16; ++m) lds_copy16(src + m * 1024, dst + m * 1024);
+      if (!(wave & 1)) lds_copy4(reinterpret_cast<const char*>(mt + (lane & 31)), lds_addr(meta_lds[buf][my_sub]));
     }
-    float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])),
-                     fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-    mx = col_max(mx);
-    const bool raise = mx > m_ref[qb] + thr;
-    if (__builtin_amdgcn_ballot_w64(raise)) {
-      const float m_new = raise ? mx : m_ref[qb];
-      const float alpha = __builtin_amdgcn_exp2f((m_ref[qb] - m_new) * sl2);
-      l_run[qb] *= alpha;
-#pragma unroll
-      for (int b = 0; b < OB; ++b) o[qb][b] *= alpha;
-      m_ref[qb] = m_new;
-    }
   };
-  // weights p = 2^((s - m) scale) rounded to bf16, in two parts: the first
-  // forms half of the exponentials, the second the rest, the rounding and
-  // the denominator (which adds the rounded values, dot with (1, 1))
-  auto weights1 = [&](int qb, const float (&sc)[8], float (&e)[8]) {
-    const float mb = m_ref[qb] * sl2;
+  auto stage_store = [&](int st, int buf) {
+    if constexpr (FP8) {
+      // a 16-byte code piece becomes two bf16 LDS slots (exact conversion);
+      // the FP8 tile order matches the LDS fragment order (dms_fp8.h)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) e[j] = fmaf(sc[j], sl2, -mb);
+      for (int u = 0; u < kSubs; ++u) {
+        const int k = min(2 * st + u, ntiles - 1);
+        const int valid = k < nc ? min(32, L0 - k * 32) : 32;
+        char* dst = tile_lds[buf] + u * kTB;
+        u32x4 x = cx[u];
+        int P0, step;
+        float scale = 1.0f;
+        if (tid < 2 * D) {          // keys: piece (p, h, lane L), dequantized exactly
+          P0 = 256 * (tid >> 7) + (tid & 127);
+          step = 128;
+          scale = ks[u];
+        } else {                    // values: piece (p, lane L), slots 8G .. 8G+7
+          const int Qv = tid - 2 * D;
+          P0 = D * 4 + 128 * (Qv >> 6) + (Qv & 63);
+          step = 64;
+          const int nv = valid - 8 * ((Qv >> 4) & 3);
+          if (nv < 8) {
+            const uint64_t keep8 = nv <= 0 ? 0ull : (~0ull >> (8 * (8 - nv)));
+            const uint32_t klo = static_cast<uint32_t>(keep8), khi = static_cast<uint32_t>(keep8 >> 32);
+            x &= u32x4{klo, khi, klo, khi};
+          }
+        }
+        u32x4 lo, hi;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) e[j] = __builtin_amdgcn_exp2f(e[j]);
-  };
-  auto weights2 = [&](int qb, float (&e)[8]) {
+        for (int w2 = 0; w2 < 2; ++w2) {
+          lo[2 * w2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[w2], scale, false));
+          lo[2 * w2 + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[w2], scale, true));
+          hi[2 * w2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[2 + w2], scale, false));
+          hi[2 * w2 + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[2 + w2], scale, true));
+        }
+        *reinterpret_cast<u32x4*>(dst + P0 * 16) = lo;
+        *reinterpret_cast<u32x4*>(dst + (P0 + step) * 16) = hi;
+        if (tid < 16) {
+          // scale piece tid: group G = tid / 4, key (tid % 4 < 2) or value scales of
+          // slots 8 G + 4 (tid % 2) .. + 3; missing slots get 0
+          const int j0 = 8 * (tid >> 2) + 4 * (tid & 1);
 #pragma unroll
-    for (int j = 4; j < 8; ++j) e[j] = __builtin_amdgcn_exp2f(e[j]);
-    u32x4 pu;
-    const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x2 pr = {e[2 * j], e[2 * j + 1]};
-      const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
-      pu[j] = __builtin_bit_cast(uint32_t, pb);
-      l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run[qb], false);
-    }
-    return pu;
-  };
-
-  for (int j = 0; j < min(kBuf - 1, ntiles); ++j) issue(j, page_of(j));
-  int page = page_of(kBuf - 1);   // page of the next tile to copy
-  // the query loads and this wave's first copy are in flight together; both
-  // complete here, so that no wait the compiler places for the query loads
-  // can fall inside the loop
-  __builtin_amdgcn_s_waitcnt(wait_vm(0));
-  float sc0[8], sc1[8];
-  u32x4 pu1 = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int b = 0; b < OB; ++b) vt[b] = u32x4{0u, 0u, 0u, 0u};
-  if (ntiles > 0) {
-    wait_tile(0);
-    __syncthreads();
-    read_k(0);
-    scores(0, sc0);
-  }
-  for (int k = 0; k < ntiles; ++k) {
-    // ---- A(k) head: publish tile k + 1, copy tile k + 3 into tile k - 1's buffer
-    if (k + 1 < ntiles) wait_tile(k + 1);
-    __syncthreads();
-    if (k + 3 < ntiles) issue(k + 3, page);
-    // key rows of tile k; rows past the source's end hold no key
-    const int rows = k < nc ? L0 - 32 * k : (k < nc + np ? n_pre - 32 * (k - nc) : 32);
-    uint32_t mrow = nrow;
-    u32x4 m0 = nm0, m1 = nm1;
-    if (rows < 32) {
-      if ((lane & 31) >= rows) mrow = kNoKey;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (8 * G + j >= rows) m0[j] = kNoKey;
-        if (8 * G + 4 + j >= rows) m1[j] = kNoKey;
+          for (int c = 0; c < 4; ++c)
+            if (j0 + c >= valid) sx[u][c] = 0u;
+          *reinterpret_cast<u32x4*>(&scale_lds[buf][u][4 * tid]) = sx[u];
+        }
+        if (tid < 64) meta_lds[buf][u][tid] = mt_reg[u];
       }
     }
-    // a key row needs the per-element mask iff some query t in [t0, t1)
-    // does not see it: no key, causal (position > t0) or flagged and
-    // expiring by t1 - 1
+  };
+  int pg[kSubs] = {0, 0};
+  stage_pages(0, pg);
+  stage_load(0, 0, pg);
+  stage_pages(1, pg);
+
+  // ---- this lane's column: query head col % g at position t0 + col / g (a
+  // position's g heads may straddle two waves; the last 32 NW mod g columns
+  // go unused)
+  const int col = wave * 32 + (lane & 31);
+  const int pl = col / a.g, qh = col % a.g;
+  const bool ok = pl < a.PB && t0 + pl < t1;
+  const int t = ok ? t0 + pl : -1;
+  u32x4 qf[KS];
+  {
+    const uint16_t* qrow = a.q + (static_cast<size_t>(tok0 + (ok ? t - p0 : 0)) * Hq + h * a.g + qh) * D + 8 * hf;
+#pragma unroll
+    for (int x = 0; x < KS; ++x)
+      qf[x] = ok ? *reinterpret_cast<const u32x4*>(qrow + 16 * x) : u32x4{0u, 0u, 0u, 0u};
+    // the borrowed decision neuron takes no part in attention (App. C)
+    if (a.zero_neuron && qh == 0 && hf == 0) qf[0][0] &= 0xFFFF0000u;
+  }
+  f32x16 o[OB];
+#pragma unroll
+  for (int x = 0; x < OB; ++x)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
+  float m_ref = kMInit, l_run = 0.f;
+  if constexpr (FP8) stage_store(0, 0);
+
+  auto stage = [&](int st, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    constexpr int tl = buf * 2 * kTB;
+    if constexpr (!FP8) __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    __syncthreads();
+    const bool more = 2 * st + 2 < ntiles;
+    if (more) stage_load(st + 1, buf ^ 1, pg);
+    const int rows0 = rows_of(2 * st), rows1 = rows_of(2 * st + 1);
+    // a key row (this lane's of the stage's 64) needs the per-element mask iff some query t
+    // in [t0, t1) does not see it: no key, causal (position > t0) or flagged and expiring by
+    // t1 - 1
+    const uint32_t mrow = (lane & 31) < (hf ? rows1 : rows0) ? meta_lds[buf][hf][lane & 31] : kNoKey;
     const int kpr = static_cast<int>(mrow & ~kFlagBit);
     const bool need = mrow == kNoKey || kpr > t0 || ((mrow & kFlagBit) && kpr + a.w <= t1 - 1);
-    const bool masked = __builtin_amdgcn_ballot_w64(need) != 0;
-    int kp[8], kx[8];
-    if (masked) {
+    const uint64_t hidden = __builtin_amdgcn_ballot_w64(need);
+    f32x16 s[2];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t km = j < 4 ? m0[j] : m1[j - 4];
-        kp[j] = static_cast<int>(km & ~kFlagBit);
-        kx[j] = (km & kFlagBit) ? kp[j] + a.w : 0x7FFFFFFF;
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[u][i] = 0.f;
+#pragma unroll
+      for (int x = 0; x < KS; ++x)
+        s[u] = mfma32(*reinterpret_cast<const u32x4*>(k_base + tl + u * kTB + (x >> 1) * 2048 + (x & 1) * 512), qf[x], s[u]);
+      if (static_cast<uint32_t>(hidden >> (32 * u))) {
+        const int rows = u ? rows1 : rows0;
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const int j0 = 16 * (i4 >> 1) + 8 * hf + 4 * (i4 & 1);
+          const u32x4 km = *reinterpret_cast<const u32x4*>(&meta_lds[buf][u][j0]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int kp = static_cast<int>(km[e] & ~kFlagBit);
+            const int kx = (km[e] & kFlagBit) ? kp + a.w : 0x7FFFFFFF;   // first query that no longer sees it
+            s[u][4 * i4 + e] = (j0 + e < rows && kp <= t && t < kx) ? s[u][4 * i4 + e] : -INFINITY;
+          }
+        }
       }
     }
-    head(0, sc0, masked, kp, kx);
-    // ---- A(k) stretch
-    float e[8];
-    __builtin_amdgcn_sched_barrier(0);
-    scores(1, sc1);
-    weights1(0, sc0, e);
-    interleave<2 * KS, 12, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    pv(1, pu1);
-    read_k(k + 1);
-    const u32x4 pu0 = weights2(0, e);
-    interleave<OB, 12, 2 * KS + 3>();
-    __builtin_amdgcn_sched_barrier(0);
-    // the weights are formed here, beside the MFMAs above, not next to their
-    // first use in B(k)
-    asm volatile("" : : "v"(pu0), "v"(l_run[0]));
-    read_v(k);
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- B(k) head
-    if (rows < 32) {
-      // stale pool slots: value elements of rows 8 G + e >= rows are zeroed
-      u32x4 keep;
+    float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        keep[q] = (8 * G + 2 * q < rows ? 0x0000FFFFu : 0u) | (8 * G + 2 * q + 1 < rows ? 0xFFFF0000u : 0u);
+    for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
+    mx = col_max32(mx);
+    const bool raise = mx > m_ref + thr;   // false while the column has seen no key
+    if (__builtin_amdgcn_ballot_w64(raise)) {
+      const float m_new = raise ? mx : m_ref;
+      const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
+      l_run *= alpha;
 #pragma unroll
-      for (int b = 0; b < OB; ++b) vt[b] &= keep;
+      for (int x = 0; x < OB; ++x) o[x] *= alpha;
+      m_ref = m_new;
     }
-    head(1, sc1, masked, kp, kx);
-    // ---- B(k) stretch
-    __builtin_amdgcn_sched_barrier(0);
-    scores(0, sc0);
-    weights1(1, sc1, e);
-    interleave<2 * KS, 12, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    pv(0, pu0);
-    pu1 = weights2(1, e);
-    interleave<OB, 12, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" : : "v"(pu1), "v"(l_run[1]));
-    // after this iteration's last LDS operand use: a scalar load in flight
-    // would turn every LDS wait before it into a full one
-    if (k + 4 < nc) page = pt[(32 * (k + 4)) >> a.log2P];
+    const float mb = m_ref * sl2;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      // weights p = 2^((s - m) scale) rounded to bf16 for the MFMA; the
+      // denominator adds the same rounded values (dot with (1, 1)), so a
+      // single dominant key returns its value row exactly; hidden keys give 0
+      u32x4 pu[2];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[u][2 * j], sl2, -mb)),
+                          __builtin_amdgcn_exp2f(fmaf(s[u][2 * j + 1], sl2, -mb))};
+        const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
+        pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
+        l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
+        if constexpr (FP8) {
+          // PV weights carry the value scale: rounding commutes with a
+          // power-of-two factor, so these are the rounded weights times it.
+          // scales: [slot group of 8][key scales (8) | value scales (8)]
+          const f32x2 vs = *reinterpret_cast<const f32x2*>(&scale_lds[buf][u][16 * (2 * (j >> 2) + hf) + 8 + 2 * (j & 3)]);
+          pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr * vs, bf16x2));
+        }
+      }
+      const char* vt = v_base + tl + u * kTB;
+      const int rows = u ? rows1 : rows0;
+      if (!FP8 && rows < 32) {
+        // stale pool slots: value elements of rows past the end are zeroed
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          u32x4 keep;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int j = 16 * y + 8 * hf + 2 * e;
+            keep[e] = (j < rows ? 0x0000FFFFu : 0u) | (j + 1 < rows ? 0xFFFF0000u : 0u);
+          }
+#pragma unroll
+          for (int x = 0; x < OB; ++x)
+            o[x] = mfma32(*reinterpret_cast<const u32x4*>(vt + x * 2048 + y * 512) & keep, pu[y], o[x]);
+        }
+      } else {
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+          for (int x = 0; x < OB; ++x)
+            o[x] = mfma32(*reinterpret_cast<const u32x4*>(vt + x * 2048 + y * 512), pu[y], o[x]);
+      }
+    }
+    if (more) stage_store(st + 1, buf ^ 1);
+    // after this stage's last LDS operand use: a scalar load in flight would
+    // turn every LDS wait before it into a full one
+    if (2 * st + 4 < ntiles) stage_pages(st + 2, pg);
+  };
+  for (int st = 0; 2 * st < ntiles; st += 2) {
+    stage(st, std::integral_constant<int, 0>{});
+    if (2 * st + 2 < ntiles) stage(st + 1, std::integral_constant<int, 1>{});
   }
-  if (ntiles > 0) pv(1, pu1);
 
   // ---- outputs
+  const float l = col_sum32(l_run);
+  if (ok) {
+    const float inv = 1.0f / l;
+    float* dst = a.out + (static_cast<size_t>(tok0 + (t - p0)) * Hq + h * a.g + qh) * D + 4 * hf;
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    float l = l_run[qb];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    const int t = tcol[qb];
-    if (t >= 0) {
-      const int qh = ((wave * NQ + qb) * 16 + r) % a.g;
-      const float inv = 1.0f / l;
-      float* dst = a.out + (static_cast<size_t>(tok0 + (t - p0)) * Hq + h * a.g + qh) * D + 4 * G;
+    for (int x = 0; x < OB; ++x)
 #pragma unroll
-      for (int b = 0; b < OB; ++b) *reinterpret_cast<f32x4*>(dst + 16 * b) = o[qb][b] * inv;
-    }
+      for (int y = 0; y < 4; ++y)
+        *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
+            f32x4{o[x][4 * y], o[x][4 * y + 1], o[x][4 * y + 2], o[x][4 * y + 3]} * inv;
   }
 };
 
@@ -1030,14 +1062,14 @@ __global__ __launch_bounds__(256, 2) void prefill_pipe_kernel(PrefillArgs a) {
   // and the workgroups finish together (the launch has as many workgroups as
   // fit on the chip at once).
   int item = blockIdx.x, buf = 0;
-  if (threadIdx.x == 0) item_lds[0] = gridDim.x + atomicAdd(a.work_ctr, 1);
+  if (tid == 0) item_lds[0] = gridDim.x + atomicAdd(a.work_ctr, 1);
   while (item < a.items) {
     attend(item);
     __syncthreads();   // the fetched index is visible; every wave is done with the LDS buffers
     const int next = item_lds[buf];
-    if (threadIdx.x == 0) item_lds[buf ^ 1] = gridDim.x + atomicAdd(a.work_ctr, 1);
+    if (tid == 0) item_lds[buf ^ 1] = gridDim.x + atomicAdd(a.work_ctr, 1);
     buf ^= 1;
-    item = next;
+    item = __builtin_amdgcn_readfirstlane(next);
   }
 }
 
@@ -1083,7 +1115,7 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   a.tiles = w + lo.ws_pf_tiles;
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
-  a.order = nullptr;
+  a.rows = reinterpret_cast<PrefillRow*>(w + lo.ws_pf_order);
   a.work_ctr = a.list_cnt + lo.max_heads;   // the word after the per-head counts
   a.nx = a.items = 0;
   a.tph = lo.pf_tiles_per_head;
@@ -1102,22 +1134,18 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   a.max_seqs = c.max_seqs;
   a.total = total_tokens;
   a.max_len = max_len;
-  const bool pipe = !FP8 && !a.immediate;
-  // positions per attention workgroup: its (position, head) columns fill 16
-  // per column block, kNQ blocks per wave
-  a.PB = (pipe ? 256 : attn_threads<D, FP8>()) / 64 * kNQ * 16 / c.group_size;
+  // positions per attention workgroup: its (position, head) columns, 32 per wave
+  a.PB = attn_threads<D, FP8>() / 64 * 32 / c.group_size;
   a.scale_log2 = c.softmax_scale * 1.4426950408889634f;
   const int NH = n * c.num_kv_heads;
   // the timing events bracket every pass
   if (ev_start) (void)hipEventRecord(ev_start, st);
   hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
-  if (NH > 1 && NH <= kOrderMax) {
-    a.order = reinterpret_cast<int32_t*>(w + lo.ws_pf_order);
-    hipLaunchKernelGGL(prefill_order_kernel, dim3(1), dim3(kThreads), 0, st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  hipLaunchKernelGGL(prefill_order_kernel, dim3(NH <= kOrderMax ? 1 : (NH + kThreads - 1) / kThreads), dim3(kThreads),
+                     0, st, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((prefill_tile_kernel<D, FP8>), dim3((max_len + 31) / 32, NH, 2), dim3(kThreads), 0,
                      st, a);
   e = hipGetLastError();
@@ -1127,12 +1155,11 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   // until none is left
   a.nx = static_cast<int>(grid.x);
   a.items = a.nx * NH;
-  if (pipe)
-    hipLaunchKernelGGL((prefill_pipe_kernel<D>), dim3(min(a.items, 2 * cu_count())), dim3(256), 0, st, a);
+  const dim3 wgs(min(a.items, 512 / attn_threads<D, FP8>() * cu_count()));
+  if (a.immediate)
+    hipLaunchKernelGGL((prefill_kernel<D, kNQ, FP8>), wgs, dim3(attn_threads<D, FP8>()), 0, st, a);
   else
-    hipLaunchKernelGGL((prefill_kernel<D, kNQ, FP8>),
-                       dim3(min(a.items, 512 / attn_threads<D, FP8>() * cu_count())),
-                       dim3(attn_threads<D, FP8>()), 0, st, a);
+    hipLaunchKernelGGL((prefill_delayed_kernel<D, FP8>), wgs, dim3(attn_threads<D, FP8>()), 0, st, a);
   e = hipGetLastError();
   if (ev_stop) (void)hipEventRecord(ev_stop, st);
   return e;
@@ -1466,7 +1493,7 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.tiles = w + lo.ws_pf_tiles;
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
-  a.order = nullptr;
+  a.rows = nullptr;
   a.work_ctr = nullptr;
   a.nx = a.items = 0;
   a.tph = lo.pf_tiles_per_head;
