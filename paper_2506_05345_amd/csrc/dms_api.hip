@@ -119,7 +119,7 @@ Layout make_layout(const dms_config& c) {
   // kept chunk tokens before every 32-aligned chunk position, per KV head
   // (same indexing as the tiles of one region)
   lo.ws_pf_kb = take(H * static_cast<size_t>(lo.pf_tiles_per_head) * 4);
-  lo.ws_pf_order = take(NH * 32);   // attention workgroup rows, heaviest head first
+  lo.ws_pf_order = take(NH * 36 + 4);   // attention rows, heaviest head first, and their first work items
   lo.ws_q_sel = take(NH * static_cast<size_t>(c.quest_page_budget) * 4);
   lo.ws_q_page = take(NH * static_cast<size_t>(c.quest_page_budget) * 4);
   lo.ws_q_len = take(NH * 4);

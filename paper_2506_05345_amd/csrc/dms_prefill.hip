@@ -20,21 +20,20 @@
 // keys by (k-step, half, lane), values transposed), so the attention pass
 // stages every source the same way.
 //
-// Attention pass: a workgroup (4 waves) owns one (sequence, KV head, block of
-// query positions).  Its columns are (position, query head) pairs, the g
-// heads of a position consecutive, packed 16 to an MFMA column block (a
-// position's heads may straddle two blocks); each wave holds NQ column
-// blocks.  Key tiles of 32 are staged into LDS in the order the MFMA
-// operand loads consume them (no bank conflicts) -- by hardware copies into
-// four buffers for bf16 pages under delayed eviction, through registers into
-// two otherwise -- and read by every wave with 16-byte LDS loads straight
-// into operand registers.  A tile is masked per element only when some query
-// of the block does not see one of its keys; the online softmax works in the
-// exp2 domain with a lazy rescale.  Pass 0 also counts the kept chunk tokens
-// before every 32-aligned position and a one-block pass ranks the call's
-// (sequence, head) rows by work; the attention launch keeps as many
-// workgroups as fit on the chip, each taking (row, query block) items in
-// that order.
+// Attention pass: a work item is one (sequence, KV head, block of query
+// positions).  Its columns are (position, query head) pairs, the g heads of a
+// position consecutive, packed to the MFMA column blocks (a position's heads
+// may straddle two): 32 per wave under delayed eviction, NQ blocks of 16 per
+// wave under immediate eviction.  Key tiles are staged into LDS in the order
+// the MFMA operand loads consume them (no bank conflicts) -- by hardware
+// copies for bf16 pages under delayed eviction, through registers otherwise --
+// and read by every wave with 16-byte LDS loads straight into operand
+// registers.  A tile is masked per element only when some query of the block
+// does not see one of its keys; the online softmax works in the exp2 domain
+// with a lazy rescale.  Pass 0 also counts the kept chunk tokens before every
+// 32-aligned position and a one-block pass ranks the call's (sequence, head)
+// rows by work; the attention launch keeps as many workgroups as fit on the
+// chip, each taking (row, query block) items in that order.
 #include <type_traits>
 
 #include "dms_common.h"
@@ -52,9 +51,8 @@ constexpr int kThreads = 256;
 // workgroup per CU, two waves per SIMD), else four.  Each of a chunk's query
 // blocks stages every cached tile of its head, so more waves per workgroup
 // means fewer stagings per query: with FP8 pages a staging dequantizes the
-// tile, and eight waves ran 3229 vs 3747 us per call at the 32B-shaped stress
-// step; with bf16 pages eight waves ran slower (2585 vs 2480 us: more waves
-// at every barrier).
+// tile; with bf16 pages it is a hardware copy, and more waves wait at every
+// barrier.
 template <int D, bool FP8>
 constexpr int attn_threads() { return FP8 && D == 128 ? 512 : 256; }
 constexpr uint32_t kNoKey = 0x7FFFFFFFu;  // key position of padding rows (never visible)
@@ -114,6 +112,7 @@ struct PrefillArgs {
   int32_t* list_cnt;      // [n * H]
   int32_t* kept_before;   // [H][tph]: kept chunk tokens before chunk position 32 j (tile indexing)
   PrefillRow* rows;       // [n * H]: attention grid rows, heaviest first
+  int32_t* first_item;    // [n * H + 1]: first work item of each row (n * H <= kOrderMax)
   int32_t* work_ctr;      // attention work items taken so far (zeroed by pass 0)
   int nx, items;          // query blocks per grid row; rows x nx
   char* tiles;            // [2][H][tph] tiles: chunk tokens, then compacted kept tokens
@@ -158,17 +157,20 @@ __device__ inline size_t ws_kb(const PrefillArgs& a, int h, int i, int j) {
 // workgroup ranks the n * H (sequence, head) rows by their live length plus
 // half their kept chunk tokens (the cached keys every block of the row
 // attends to, and the mean of its kept-prefix keys); ties keep row order, and
-// calls of more than kOrderMax rows keep theirs.  Each row's descriptor saves
-// a work item three dependent loads.
+// calls of more than kOrderMax rows keep theirs.  It also writes each row's
+// descriptor (which saves a work item three dependent loads) and first work
+// item, so that rows of shorter chunks have no empty items.
 constexpr int kOrderMax = 512;
 __global__ __launch_bounds__(kThreads) void prefill_order_kernel(PrefillArgs a) {
-  __shared__ int work[kOrderMax];
+  __shared__ int work[kOrderMax], blocks[kOrderMax], lds[17];
   if (load_status(a.status) != 0) return;
   const int NH = a.n * a.H;
   const bool ranked = NH <= kOrderMax;
   if (ranked)
-    for (int x = threadIdx.x; x < NH; x += kThreads)
-      work[x] = a.len[a.seq_ids[x / a.H] * a.H + x % a.H] + a.list_cnt[x] / 2;
+    for (int x = threadIdx.x; x < kOrderMax; x += kThreads) {
+      work[x] = x < NH ? a.len[a.seq_ids[x / a.H] * a.H + x % a.H] + a.list_cnt[x] / 2 : 0;
+      blocks[x] = 0;
+    }
   __syncthreads();
   for (int x = blockIdx.x * kThreads + threadIdx.x; x < NH; x += gridDim.x * kThreads) {
     int rank = x;
@@ -188,7 +190,24 @@ __global__ __launch_bounds__(kThreads) void prefill_order_kernel(PrefillArgs a) 
     r.tile0 = tok0 / 32 + i;
     r.pad = 0;
     a.rows[rank] = r;
+    if (ranked) blocks[rank] = (r.C + a.PB - 1) / a.PB;
   }
+  if (!ranked) return;
+  // first work item of every row
+  __syncthreads();
+  constexpr int kPer = kOrderMax / kThreads;
+  int mine = 0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) mine += blocks[kPer * threadIdx.x + u];
+  int total;
+  int at = block_exclusive_scan(mine, lds, &total);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int x = kPer * threadIdx.x + u;
+    if (x < NH) a.first_item[x] = at;
+    at += blocks[x];
+  }
+  if (threadIdx.x == 0) a.first_item[NH] = total;
 }
 
 // Pass 1 (one block per (32-token tile, sequence x head, region)): copy the
@@ -702,8 +721,21 @@ __global__ __launch_bounds__((attn_threads<D, FP8>()), (512 / attn_threads<D, FP
 // head, so more columns per workgroup means fewer dequantizations): codes go
 // through registers and are dequantized into the same order.  Rows past a
 // source's end are fixed up when read: pool slots past the live length hold
-// stale data (values zeroed in registers, keys hidden), kept-list rows from
+// stale data (values zeroed in LDS, keys hidden), kept-list rows from
 // the band on are hidden.
+//
+// The two tiles' score chains alternate, and the second tile's weights are
+// formed between the first tile's value products.  Operands are read kAhead
+// products before their use, in pinned order: left to itself the compiler
+// reads each just before its product and waits.  The first stage of the next
+// item is copied beside the last one of the present item.  Four prompts of
+// 4096 to 16384 tokens in chunks of 4096 a sequence (8 KV heads of 5, d = 128,
+// window 256, 7/8 flagged) take 1628 us, every pass and commit counted, from
+// 2068 us with 16x16 products and 32 keys per barrier (1856 before the operand
+// order and the item overlap); two of 3001 and 11999 tokens with FP8 pages (4
+// heads of 7) take 856, from 1084 us.  Bound by the softmax's exponentials
+// and conversions, which the matrix core does not fully cover with two waves
+// per SIMD.
 //
 // The LDS destination of a copy goes in M0, written by the same inline
 // assembly statement as the load; nothing else in this file reads M0.  The
@@ -744,9 +776,116 @@ __device__ inline float col_sum32(float x) {
   const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
+// keeps the compiler from forming what follows from x ahead of a loop and holding it
+__device__ inline int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 __device__ inline int row_token(int r) {
   return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
 }
+
+// One work item of an attention pass: (row, query block) and the key tiles it
+// attends -- nc pool tiles, np tiles of kept chunk keys, then the band.
+struct Item {
+  int hh, tok0, C, sh, p0, L0, t0, t1, n_pre, nc, np, ntiles, pre0, band0;
+};
+
+// Work item `item`; `first`: the rows' first items in LDS (ranked calls).
+__device__ __forceinline__ Item prefill_item(const PrefillArgs& a, const int* first, int item, int lane) {
+  Item it;
+  const int NH = a.n * a.H;
+  int row, block;
+  if (NH <= kOrderMax) {
+    // the last row whose first item is not past this one
+    row = -1;
+    for (int x = 0; x < NH; x += 64)
+      row += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x + lane < NH && first[min(x + lane, NH)] <= item));
+    row = __builtin_amdgcn_readfirstlane(row);
+    block = item - __builtin_amdgcn_readfirstlane(first[row]);
+  } else {
+    row = item / a.nx;
+    block = item - row * a.nx;
+  }
+  typedef int __attribute__((ext_vector_type(8))) i32x8;
+  const i32x8 rd = *((const DMS_CONST i32x8*)(a.rows + row));
+  it.hh = rd[0];
+  it.tok0 = rd[1];
+  it.C = rd[2];
+  it.sh = rd[3];
+  it.p0 = rd[4];
+  it.L0 = rd[5];
+  const int h = it.hh % a.H, pb0 = block * a.PB;
+  it.t0 = it.p0 + pb0;
+  it.t1 = it.p0 + min(it.C, pb0 + a.PB);
+  // band: chunk tiles from the one holding max(p0, t0 - w + 1) up to t1
+  const int band_c0 = (max(0, pb0 - a.w + 1) >> 5) << 5;   // chunk-local, < C
+  it.pre0 = (a.H + h) * a.tph + rd[6];
+  it.band0 = h * a.tph + rd[6] + (band_c0 >> 5);
+  it.nc = (it.L0 + 31) >> 5;
+  if (pb0 >= it.C) {   // unranked calls only: no columns, one tile of any bits
+    it.t1 = it.t0;
+    it.n_pre = it.nc = it.np = 0;
+    it.ntiles = 1;
+    it.band0 = h * a.tph + rd[6];
+    return it;
+  }
+  // kept chunk keys strictly before the band, counted by pass 0
+  it.n_pre = ((const DMS_CONST int32_t*)a.kept_before)[it.band0];
+  it.np = (it.n_pre + 31) >> 5;
+  it.ntiles = it.nc + it.np + ((it.t1 - it.p0 - band_c0 + 31) >> 5);
+  return it;
+}
+// pool page of tile k (only read for k < nc)
+__device__ __forceinline__ int pool_page(const PrefillArgs& a, const Item& it, int k) {
+  return k < it.nc ? ((const DMS_CONST int32_t*)(a.page_table + static_cast<size_t>(it.sh) * a.maxp))[(32 * k) >> a.log2P] : 0;
+}
+// stored tile k and its key rows (workspace tiles of one region and head are consecutive)
+__device__ __forceinline__ void tile_source(const PrefillArgs& a, const Item& it, int k, int page, size_t tile_size,
+                                            const char*& tile, const uint32_t*& mt) {
+  if (k < it.nc) {
+    const int sb = 32 * k;
+    tile = a.pool + static_cast<size_t>(page) * a.page_bytes + static_cast<size_t>((sb & (a.P - 1)) >> 5) * tile_size;
+    mt = reinterpret_cast<const uint32_t*>(a.slot_meta + static_cast<size_t>(it.sh) * a.max_slots) + sb;
+  } else {
+    const size_t x = k < it.nc + it.np ? it.pre0 + (k - it.nc) : it.band0 + (k - it.nc - it.np);
+    tile = a.tiles + x * tile_size;
+    mt = a.tmeta + x * 32;
+  }
+}
+// rows of tile k that exist
+__device__ __forceinline__ int rows_of(const Item& it, int k) {
+  return k >= it.ntiles ? 0 : k < it.nc ? it.L0 - 32 * k : (k < it.nc + it.np ? it.n_pre - 32 * (k - it.nc) : 32);
+}
+// a key row (position | flag << 31) needs the per-element mask iff some query t in [t0, t1) does
+// not see it: no key, causal (position > t0) or flagged and expiring by t1 - 1
+__device__ __forceinline__ bool row_hidden(uint32_t mrow, const Item& it, int w) {
+  const int kp = static_cast<int>(mrow & ~kFlagBit);
+  return (mrow == kNoKey) | (kp > it.t0) | (((mrow & kFlagBit) != 0) & (kp + w <= it.t1 - 1));
+}
+// Scores of one tile with the keys that the column at position t does not see
+// set to -inf; mp: the lane's key rows (register i: row 16 (i / 8) + i % 8 past mp).
+__device__ __forceinline__ void mask_scores(f32x16& s, const uint32_t* mp, int rows, int t, int w, int lane) {
+  if (rows < 32) {   // rows past the source's end hold no key
+    const int j0 = 8 * (fresh(lane) >> 5);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (j0 + 16 * (i >> 3) + (i & 7) >= rows) s[i] = -INFINITY;
+  }
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) {
+    const u32x4 km = *reinterpret_cast<const u32x4*>(mp + 16 * (i4 >> 1) + 4 * (i4 & 1));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // seen from its own position on, if flagged for w positions (no key: position
+      // 2^31 - 1; unused column: t = -1)
+      const uint32_t age = static_cast<uint32_t>(t) - (km[e] & ~kFlagBit);
+      const uint32_t seen = (km[e] & kFlagBit) ? static_cast<uint32_t>(w) : 0x7FFFFFFFu;
+      s[4 * i4 + e] = age < seen ? s[4 * i4 + e] : -INFINITY;
+    }
+  }
+}
+constexpr int kAhead = 4;   // MFMAs between an operand's LDS read and its use
 
 template <int D, bool FP8>
 constexpr int delayed_waves() { return attn_threads<D, FP8>() / 64; }
@@ -761,7 +900,7 @@ void prefill_delayed_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(16))) char tile_lds[2][2 * kTB];
   __shared__ __attribute__((aligned(16))) uint32_t meta_lds[2][2][64];   // [buffer][tile], rows 0..31 twice
   __shared__ __attribute__((aligned(16))) float scale_lds[FP8 ? 2 : 1][2][64];   // FP8: tile scales
-  __shared__ int item_lds[2];
+  __shared__ int item_lds[2], first_lds[kOrderMax + 1];
   if (load_status(a.status) != 0) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -774,46 +913,21 @@ void prefill_delayed_kernel(PrefillArgs a) {
   const char* k_base = tile_lds[0] + ((kt >> 2) & 1) * 1024 + hf * 256 + (4 * (kt >> 3) + (kt & 3)) * 16;
   const char* v_base = tile_lds[0] + D * 64 + ((lane >> 4) & 1) * 1024 + hf * 256 + (lane & 15) * 16;
 
-  // attention of work item `item` = (grid row item / nx, query block item % nx)
-  auto attend = [&](int item) {
-  const int row = item / a.nx;
-  typedef int __attribute__((ext_vector_type(8))) i32x8;
-  const i32x8 rd = *((const DMS_CONST i32x8*)(a.rows + row));   // see prefill_order_kernel
-  const int hh = rd[0], tok0 = rd[1], C = rd[2], sh = rd[3], p0 = rd[4], L0 = rd[5], tix = rd[6];
-  const int pb0 = (item - row * a.nx) * a.PB;
-  if (pb0 >= C) return;
-  const int h = hh % a.H;
-  const int t0 = p0 + pb0;
-  const int t1 = p0 + min(C, pb0 + a.PB);
-  const int band_c0 = (max(0, pb0 - a.w + 1) >> 5) << 5;   // chunk-local, < C
-  // kept chunk keys strictly before the band, counted by pass 0
-  const int n_pre = ((const DMS_CONST int32_t*)a.kept_before)[static_cast<size_t>(h) * a.tph + tix + (band_c0 >> 5)];
-  const int nc = (L0 + 31) >> 5;
-  const int np = (n_pre + 31) >> 5;
-  const int nb = (t1 - p0 - band_c0 + 31) >> 5;
-  const int ntiles = nc + np + nb;
-  // workspace tile of (region, head, tile): the call's tiles of one region and head are consecutive
-  const size_t pre0 = static_cast<size_t>(a.H + h) * a.tph + tix;
-  const size_t band0 = static_cast<size_t>(h) * a.tph + tix + (band_c0 >> 5);
-  const DMS_CONST int32_t* pt = (const DMS_CONST int32_t*)(a.page_table + static_cast<size_t>(sh) * a.maxp);
-  const uint32_t* smeta = reinterpret_cast<const uint32_t*>(a.slot_meta + static_cast<size_t>(sh) * a.max_slots);
-
-  // pool page of tile k (only read for k < nc)
-  auto page_of = [&](int k) { return k < nc ? pt[(32 * k) >> a.log2P] : 0; };
-  auto source = [&](int k, int page, const char*& tile, const uint32_t*& mt) {
-    if (k < nc) {
-      const int sb = 32 * k;
-      tile = a.pool + static_cast<size_t>(page) * a.page_bytes + static_cast<size_t>((sb & (a.P - 1)) >> 5) * kSB;
-      mt = smeta + sb;
-    } else {
-      const size_t x = k < nc + np ? pre0 + (k - nc) : band0 + (k - nc - np);
-      tile = a.tiles + x * kSB;
-      mt = a.tmeta + x * 32;
-    }
-  };
-  // rows of tile k that exist
-  auto rows_of = [&](int k) {
-    return k >= ntiles ? 0 : k < nc ? L0 - 32 * k : (k < nc + np ? n_pre - 32 * (k - nc) : 32);
+  // ---- work items: (row, query block), heaviest rows first.  The next item's
+  // descriptor is loaded and its first stage copied beside the last stage of
+  // the present one, so that a short item does not wait
+  // for its chain of dependent loads (about a third of a 600-key item's time).
+  const int NH = a.n * a.H;
+  const bool ranked = NH <= kOrderMax;
+  if (ranked)
+    for (int x = tid; x <= NH; x += 64 * NW) first_lds[x] = a.first_item[x];
+  __syncthreads();
+  const int items = ranked ? __builtin_amdgcn_readfirstlane(first_lds[NH]) : a.items;
+  // ranked: first_lds holds the rows' first items (see prefill_order_kernel)
+  auto load_item = [&](int item) { return prefill_item(a, first_lds, item, lane); };
+  auto page_of = [&](const Item& it, int k) { return pool_page(a, it, k); };
+  auto source = [&](const Item& it, int k, int page, const char*& tile, const uint32_t*& mt) {
+    tile_source(a, it, k, page, kSB, tile, mt);
   };
 
   // ---- staging of stage st (tiles 2 st, 2 st + 1; the last one again past the end)
@@ -822,21 +936,21 @@ void prefill_delayed_kernel(PrefillArgs a) {
   float ks[kSubs];                 // key scale of a key piece's token
   uint32_t mt_reg[kSubs];
   const int my_sub = (wave >> 1) & 1;
-  auto stage_pages = [&](int st, int (&pg)[kSubs]) {
+  auto stage_pages = [&](const Item& it, int st, int (&pg)[kSubs]) {
     if constexpr (FP8) {
 #pragma unroll
-      for (int u = 0; u < kSubs; ++u) pg[u] = page_of(min(2 * st + u, ntiles - 1));
+      for (int u = 0; u < kSubs; ++u) pg[u] = page_of(it, min(2 * st + u, it.ntiles - 1));
     } else {
-      pg[0] = page_of(min(2 * st + my_sub, ntiles - 1));
+      pg[0] = page_of(it, min(2 * st + my_sub, it.ntiles - 1));
     }
   };
-  auto stage_load = [&](int st, int buf, const int (&pg)[kSubs]) {
+  auto stage_load = [&](const Item& it, int st, int buf, const int (&pg)[kSubs]) {
     const char* tile;
     const uint32_t* mt;
     if constexpr (FP8) {
 #pragma unroll
       for (int u = 0; u < kSubs; ++u) {
-        source(min(2 * st + u, ntiles - 1), pg[u], tile, mt);
+        source(it, min(2 * st + u, it.ntiles - 1), pg[u], tile, mt);
         cx[u] = *reinterpret_cast<const u32x4*>(tile + tid * 16);
         if (tid < 2 * D) {
           // key piece (p, h, lane L): all 16 codes belong to slot 8 (r/4) + r%4 + 4 h
@@ -848,7 +962,7 @@ void prefill_delayed_kernel(PrefillArgs a) {
       }
     } else {
       // wave w copies the keys (w even) or values of tile w / 2 of the stage
-      source(min(2 * st + my_sub, ntiles - 1), pg[0], tile, mt);
+      source(it, min(2 * st + my_sub, it.ntiles - 1), pg[0], tile, mt);
       const char* src = tile + (wave & 1) * (D * 64) + lane * 16;
       const uint32_t dst = lds_addr(tile_lds[0]) + buf * 2 * kTB + my_sub * kTB + (wave & 1) * (D * 64);
 #pragma unroll
@@ -856,14 +970,14 @@ void prefill_delayed_kernel(PrefillArgs a) {
       if (!(wave & 1)) lds_copy4(reinterpret_cast<const char*>(mt + (lane & 31)), lds_addr(meta_lds[buf][my_sub]));
     }
   };
-  auto stage_store = [&](int st, int buf) {
+  auto stage_store = [&](const Item& it, int st, int buf) {
     if constexpr (FP8) {
       // a 16-byte code piece becomes two bf16 LDS slots (exact conversion);
       // the FP8 tile order matches the LDS fragment order (dms_fp8.h)
 #pragma unroll
       for (int u = 0; u < kSubs; ++u) {
-        const int k = min(2 * st + u, ntiles - 1);
-        const int valid = k < nc ? min(32, L0 - k * 32) : 32;
+        const int k = min(2 * st + u, it.ntiles - 1);
+        const int valid = k < it.nc ? min(32, it.L0 - k * 32) : 32;
         char* dst = tile_lds[buf] + u * kTB;
         u32x4 x = cx[u];
         int P0, step;
@@ -906,170 +1020,181 @@ void prefill_delayed_kernel(PrefillArgs a) {
       }
     }
   };
-  int pg[kSubs] = {0, 0};
-  stage_pages(0, pg);
-  stage_load(0, 0, pg);
-  stage_pages(1, pg);
 
-  // ---- this lane's column: query head col % g at position t0 + col / g (a
-  // position's g heads may straddle two waves; the last 32 NW mod g columns
-  // go unused)
+  if (static_cast<int>(blockIdx.x) >= items) return;
+  Item cur = load_item(blockIdx.x);
+  int pg[kSubs] = {0, 0};
+  stage_pages(cur, 0, pg);
+  stage_load(cur, 0, 0, pg);
+  stage_pages(cur, 1, pg);
+  if constexpr (FP8) stage_store(cur, 0, 0);
+  int par = 0, ib = 0;   // LDS buffer of the present stage, slot of the next item's index
+
+  // this lane's column: query head col % g at position t0 + col / g (a
+  // position's g heads may straddle two waves; the last 32 NW mod g columns go
+  // unused)
   const int col = wave * 32 + (lane & 31);
   const int pl = col / a.g, qh = col % a.g;
-  const bool ok = pl < a.PB && t0 + pl < t1;
-  const int t = ok ? t0 + pl : -1;
-  u32x4 qf[KS];
-  {
-    const uint16_t* qrow = a.q + (static_cast<size_t>(tok0 + (ok ? t - p0 : 0)) * Hq + h * a.g + qh) * D + 8 * hf;
+  while (true) {
+    const int h = cur.hh % a.H;
+    const bool ok = pl < a.PB && cur.t0 + pl < cur.t1;
+    const int t = ok ? cur.t0 + pl : -1;
+    const size_t orow = static_cast<size_t>(cur.tok0 + (ok ? t - cur.p0 : 0)) * Hq + h * a.g + qh;
+    u32x4 qf[KS];
 #pragma unroll
     for (int x = 0; x < KS; ++x)
-      qf[x] = ok ? *reinterpret_cast<const u32x4*>(qrow + 16 * x) : u32x4{0u, 0u, 0u, 0u};
+      qf[x] = ok ? *reinterpret_cast<const u32x4*>(a.q + orow * D + 16 * x + 8 * hf) : u32x4{0u, 0u, 0u, 0u};
     // the borrowed decision neuron takes no part in attention (App. C)
     if (a.zero_neuron && qh == 0 && hf == 0) qf[0][0] &= 0xFFFF0000u;
-  }
-  f32x16 o[OB];
+    f32x16 o[OB];
 #pragma unroll
-  for (int x = 0; x < OB; ++x)
+    for (int x = 0; x < OB; ++x)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
-  float m_ref = kMInit, l_run = 0.f;
-  if constexpr (FP8) stage_store(0, 0);
-
-  auto stage = [&](int st, auto buf_c) {
-    constexpr int buf = decltype(buf_c)::value;
-    constexpr int tl = buf * 2 * kTB;
-    if constexpr (!FP8) __builtin_amdgcn_s_waitcnt(wait_vm(0));
-    __syncthreads();
-    const bool more = 2 * st + 2 < ntiles;
-    if (more) stage_load(st + 1, buf ^ 1, pg);
-    const int rows0 = rows_of(2 * st), rows1 = rows_of(2 * st + 1);
-    // a key row (this lane's of the stage's 64) needs the per-element mask iff some query t
-    // in [t0, t1) does not see it: no key, causal (position > t0) or flagged and expiring by
-    // t1 - 1
-    const uint32_t mrow = (lane & 31) < (hf ? rows1 : rows0) ? meta_lds[buf][hf][lane & 31] : kNoKey;
-    const int kpr = static_cast<int>(mrow & ~kFlagBit);
-    const bool need = mrow == kNoKey || kpr > t0 || ((mrow & kFlagBit) && kpr + a.w <= t1 - 1);
-    const uint64_t hidden = __builtin_amdgcn_ballot_w64(need);
-    f32x16 s[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[u][i] = 0.f;
-#pragma unroll
-      for (int x = 0; x < KS; ++x)
-        s[u] = mfma32(*reinterpret_cast<const u32x4*>(k_base + tl + u * kTB + (x >> 1) * 2048 + (x & 1) * 512), qf[x], s[u]);
-      if (static_cast<uint32_t>(hidden >> (32 * u))) {
-        const int rows = u ? rows1 : rows0;
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int j0 = 16 * (i4 >> 1) + 8 * hf + 4 * (i4 & 1);
-          const u32x4 km = *reinterpret_cast<const u32x4*>(&meta_lds[buf][u][j0]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int kp = static_cast<int>(km[e] & ~kFlagBit);
-            const int kx = (km[e] & kFlagBit) ? kp + a.w : 0x7FFFFFFF;   // first query that no longer sees it
-            s[u][4 * i4 + e] = (j0 + e < rows && kp <= t && t < kx) ? s[u][4 * i4 + e] : -INFINITY;
-          }
+      for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
+    float m_ref = kMInit, l_run = 0.f;
+    if (tid == 0) item_lds[ib] = gridDim.x + atomicAdd(a.work_ctr, 1);   // read after this item's last barrier
+    Item nxt = cur;
+    bool have_next = false;
+    auto stage = [&](int st, auto last_c) {
+      constexpr bool last = decltype(last_c)::value;
+      const int buf = par, tl = par * 2 * kTB;
+      if constexpr (!FP8) __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      __syncthreads();
+      if constexpr (!last) {
+        stage_load(cur, st + 1, buf ^ 1, pg);
+      } else {
+        const int item = __builtin_amdgcn_readfirstlane(item_lds[ib]);
+        have_next = item < items;
+        if (have_next) {
+          nxt = load_item(item);
+          stage_pages(nxt, 0, pg);
+          stage_load(nxt, 0, buf ^ 1, pg);
         }
       }
-    }
-    float mx = fmaxf(s[0][0], s[1][0]);
+      const int rows0 = rows_of(cur, 2 * st), rows1 = rows_of(cur, 2 * st + 1);
+      if (!FP8 && (cur.L0 & 31) && st == (cur.nc - 1) >> 1) {
+        // the pool's last tile: value elements of slots past the live length are stale
+        const int sub = (cur.nc - 1) & 1, valid = cur.L0 & 31;
+        for (int P = tid; P < D * 4; P += 64 * NW) {
+          const int nv = valid - 8 * ((P >> 4) & 3);   // elements of this piece that exist
+          if (nv >= 8) continue;
+          u32x4* x = reinterpret_cast<u32x4*>(tile_lds[0] + tl + sub * kTB + D * 64 + P * 16);
+          u32x4 keep;
 #pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
-    mx = col_max32(mx);
-    const bool raise = mx > m_ref + thr;   // false while the column has seen no key
-    if (__builtin_amdgcn_ballot_w64(raise)) {
-      const float m_new = raise ? mx : m_ref;
-      const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
-      l_run *= alpha;
+          for (int e = 0; e < 4; ++e) keep[e] = (2 * e < nv ? 0x0000FFFFu : 0u) | (2 * e + 1 < nv ? 0xFFFF0000u : 0u);
+          *x &= keep;
+        }
+        __syncthreads();
+      }
+      // this lane's of the stage's 64 key rows
+      uint32_t mrow = meta_lds[buf][0][64 * hf + (lane & 31)];
+      if ((lane & 31) >= (hf ? rows1 : rows0)) mrow = kNoKey;
+      const uint64_t hidden = __builtin_amdgcn_ballot_w64(row_hidden(mrow, cur, a.w));
+      __builtin_amdgcn_sched_barrier(0);
+      // Operands are read kAhead MFMAs ahead of their use in an order that is
+      // pinned step by step: left alone the compiler reads each operand right
+      // before its MFMA and waits out the LDS latency every time.
+      f32x16 s[2];
 #pragma unroll
-      for (int x = 0; x < OB; ++x) o[x] *= alpha;
-      m_ref = m_new;
-    }
-    const float mb = m_ref * sl2;
+      for (int i = 0; i < 16; ++i) s[0][i] = s[1][i] = 0.f;
+      {
+        u32x4 op[kAhead];
+        auto read = [&](int e) {   // tile e % 2, k-step e / 2: the two chains take turns
+          return *reinterpret_cast<const u32x4*>(k_base + tl + (e & 1) * kTB + (e >> 2) * 2048 + ((e >> 1) & 1) * 512);
+        };
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+        for (int e = 0; e < kAhead; ++e) op[e] = read(e);
+#pragma unroll
+        for (int e = 0; e < 2 * KS; ++e) {
+          __builtin_amdgcn_sched_barrier(0);
+          s[e & 1] = mfma32(op[e % kAhead], qf[e >> 1], s[e & 1]);
+          if (e + kAhead < 2 * KS) op[e % kAhead] = read(e + kAhead);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (hidden) {
+        mask_scores(s[0], &meta_lds[buf][0][8 * hf], rows0, t, a.w, lane);
+        mask_scores(s[1], &meta_lds[buf][1][8 * hf], rows1, t, a.w, lane);
+      }
+      float mx = fmaxf(s[0][0], s[1][0]);
+  #pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
+      mx = col_max32(mx);
+      const bool raise = mx > m_ref + thr;   // false while the column has seen no key
+      if (__builtin_amdgcn_ballot_w64(raise)) {
+        const float m_new = raise ? mx : m_ref;
+        const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
+        l_run *= alpha;
+  #pragma unroll
+        for (int x = 0; x < OB; ++x) o[x] *= alpha;
+        m_ref = m_new;
+      }
+      const float mb = m_ref * sl2;
       // weights p = 2^((s - m) scale) rounded to bf16 for the MFMA; the
       // denominator adds the same rounded values (dot with (1, 1)), so a
       // single dominant key returns its value row exactly; hidden keys give 0
-      u32x4 pu[2];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      u32x4 pu[2][2];
+      auto weight_pair = [&](int u, int j) {
         const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[u][2 * j], sl2, -mb)),
                           __builtin_amdgcn_exp2f(fmaf(s[u][2 * j + 1], sl2, -mb))};
         const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
-        pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
+        pu[u][j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
         l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
         if constexpr (FP8) {
           // PV weights carry the value scale: rounding commutes with a
           // power-of-two factor, so these are the rounded weights times it.
           // scales: [slot group of 8][key scales (8) | value scales (8)]
           const f32x2 vs = *reinterpret_cast<const f32x2*>(&scale_lds[buf][u][16 * (2 * (j >> 2) + hf) + 8 + 2 * (j & 3)]);
-          pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr * vs, bf16x2));
+          pu[u][j >> 2][j & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr * vs, bf16x2));
+        }
+      };
+#pragma unroll
+      for (int j = 0; j < 8; ++j) weight_pair(0, j);
+      // value product e of the stage: tile e / (2 OB), token half (e / OB) % 2, dim block e % OB
+      auto read_v = [&](int e) {
+        return *reinterpret_cast<const u32x4*>(v_base + tl + e / (2 * OB) * kTB + (e % OB) * 2048 + (e / OB) % 2 * 512);
+      };
+      // the second tile's weights beside the first one's products
+      u32x4 op[kAhead];
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e) op[e] = read_v(e);
+#pragma unroll
+      for (int e = 0; e < 4 * OB; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        o[e % OB] = mfma32(op[e % kAhead], pu[e / (2 * OB)][(e / OB) % 2], o[e % OB]);
+        if (e + kAhead < 4 * OB) op[e % kAhead] = read_v(e + kAhead);
+        if (e < 2 * OB) {
+#pragma unroll
+          for (int j = e * 8 / (2 * OB); j < (e + 1) * 8 / (2 * OB); ++j) weight_pair(1, j);
         }
       }
-      const char* vt = v_base + tl + u * kTB;
-      const int rows = u ? rows1 : rows0;
-      if (!FP8 && rows < 32) {
-        // stale pool slots: value elements of rows past the end are zeroed
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!last) stage_store(cur, st + 1, buf ^ 1);
+      else if (have_next) stage_store(nxt, 0, buf ^ 1);
+      par ^= 1;
+      // after this stage's last LDS operand use: a scalar load in flight would
+      // turn every LDS wait before it into a full one
+      if constexpr (!last) stage_pages(cur, st + 2, pg);
+      else if (have_next) stage_pages(nxt, 1, pg);
+    };
+    const int last_st = (cur.ntiles - 1) >> 1;
+    for (int st = 0; st < last_st; ++st) stage(st, std::false_type{});
+    stage(last_st, std::true_type{});
+
+    const float l = col_sum32(l_run);
+    if (ok) {
+      const float inv = 1.0f / l;
+      float* dst = a.out + orow * D + 4 * hf;
 #pragma unroll
-        for (int y = 0; y < 2; ++y) {
-          u32x4 keep;
+      for (int x = 0; x < OB; ++x)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int j = 16 * y + 8 * hf + 2 * e;
-            keep[e] = (j < rows ? 0x0000FFFFu : 0u) | (j + 1 < rows ? 0xFFFF0000u : 0u);
-          }
-#pragma unroll
-          for (int x = 0; x < OB; ++x)
-            o[x] = mfma32(*reinterpret_cast<const u32x4*>(vt + x * 2048 + y * 512) & keep, pu[y], o[x]);
-        }
-      } else {
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-          for (int x = 0; x < OB; ++x)
-            o[x] = mfma32(*reinterpret_cast<const u32x4*>(vt + x * 2048 + y * 512), pu[y], o[x]);
-      }
+        for (int y = 0; y < 4; ++y)
+          *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
+              f32x4{o[x][4 * y], o[x][4 * y + 1], o[x][4 * y + 2], o[x][4 * y + 3]} * inv;
     }
-    if (more) stage_store(st + 1, buf ^ 1);
-    // after this stage's last LDS operand use: a scalar load in flight would
-    // turn every LDS wait before it into a full one
-    if (2 * st + 4 < ntiles) stage_pages(st + 2, pg);
-  };
-  for (int st = 0; 2 * st < ntiles; st += 2) {
-    stage(st, std::integral_constant<int, 0>{});
-    if (2 * st + 2 < ntiles) stage(st + 1, std::integral_constant<int, 1>{});
-  }
-
-  // ---- outputs
-  const float l = col_sum32(l_run);
-  if (ok) {
-    const float inv = 1.0f / l;
-    float* dst = a.out + (static_cast<size_t>(tok0 + (t - p0)) * Hq + h * a.g + qh) * D + 4 * hf;
-#pragma unroll
-    for (int x = 0; x < OB; ++x)
-#pragma unroll
-      for (int y = 0; y < 4; ++y)
-        *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
-            f32x4{o[x][4 * y], o[x][4 * y + 1], o[x][4 * y + 2], o[x][4 * y + 3]} * inv;
-  }
-};
-
-  // Items one after another: the first from the workgroup's grid position, the
-  // rest in order from a counter that pass 0 zeroed, each fetched one item
-  // ahead.  Rows come heaviest first, so the last items to start are short
-  // and the workgroups finish together (the launch has as many workgroups as
-  // fit on the chip at once).
-  int item = blockIdx.x, buf = 0;
-  if (tid == 0) item_lds[0] = gridDim.x + atomicAdd(a.work_ctr, 1);
-  while (item < a.items) {
-    attend(item);
-    __syncthreads();   // the fetched index is visible; every wave is done with the LDS buffers
-    const int next = item_lds[buf];
-    if (tid == 0) item_lds[buf ^ 1] = gridDim.x + atomicAdd(a.work_ctr, 1);
-    buf ^= 1;
-    item = __builtin_amdgcn_readfirstlane(next);
+    if (!have_next) return;
+    cur = nxt;
+    ib ^= 1;
   }
 }
 
@@ -1116,6 +1241,7 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
   a.rows = reinterpret_cast<PrefillRow*>(w + lo.ws_pf_order);
+  a.first_item = reinterpret_cast<int32_t*>(a.rows + lo.max_heads);
   a.work_ctr = a.list_cnt + lo.max_heads;   // the word after the per-head counts
   a.nx = a.items = 0;
   a.tph = lo.pf_tiles_per_head;
@@ -1494,6 +1620,7 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
   a.rows = nullptr;
+  a.first_item = nullptr;
   a.work_ctr = nullptr;
   a.nx = a.items = 0;
   a.tph = lo.pf_tiles_per_head;

@@ -1,0 +1,33 @@
+"""Chunked prefill where the attention pass's units end: 32-row tiles and
+64-row stages of the cache, the kept keys and the band; one position more than
+a workgroup holds; sequences with nothing in the call; more rows than the
+ranking pass orders.  Outputs against dense masked attention."""
+import pytest
+
+from test_prefill_parity import _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _tiles(d, g, w, lens, chunks, H=1, page=32, **kw):
+    n, longest = len(lens), max(lens)
+    per = -(-longest // page) + 1
+    _run(dict(num_layers=1, max_seqs=n, num_kv_heads=H, group_size=g, head_dim=d, window=w, page_size=page,
+              num_pages=n * H * per, max_pages_per_head=per, max_chunk_tokens=n * max(chunks)),
+         list(range(n)), dict(enumerate(lens)), chunks, 91, 0.5, nan_pools=True, **kw)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("g,w,lens,chunks", [
+    (1, 1, (1, 31, 33), [1, 32]),                    # one key; a tile and one key
+    (4, 64, (64, 97, 161, 130), [64, 33]),           # whole and half stages; finished sequences
+    (3, 40, (86, 85, 170), [43, 42, 85]),            # 128 / 3 = 42 positions, 256 / 3 = 85 per workgroup
+    (16, 200, (300, 9), [9, 17, 256])])              # window longer than the chunk, straddling stages
+def test_edges(fp8, d, g, w, lens, chunks):
+    _tiles(d, g, w, lens, chunks, H=2, fp8=fp8)
+
+
+@pytest.mark.parametrize("n", [32, 33])   # 512 rows are ranked, 528 are taken in call order
+def test_many_rows(n):
+    _tiles(64, 2, 8, [5 + (s * 13) % 60 for s in range(n)], [40, 9], H=16)
