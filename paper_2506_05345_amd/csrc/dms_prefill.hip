@@ -1297,7 +1297,9 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
 // 576-dim rows shared by the g query heads, in the absorbed form of the
 // latent decode: column (position t, query head h) scores row j by q . row
 // over all 576 dims and sums the rows' first 512 (latent) dims.  The mask and
-// the three key sources are the standard prefill's.  Columns are packed 16
+// the three key sources are the standard prefill's.  Under delayed
+// eviction prefill_mla_delayed_kernel attends; under immediate eviction
+// prefill_mla_kernel: columns packed 16
 // per MFMA block -- 16 / g positions x g heads for g <= 16, else one position
 // x 16 of its heads -- and each of a workgroup's four waves takes one column
 // block (its 16 x 512 float32 accumulators fill most of a wave's registers).
@@ -1332,6 +1334,14 @@ __global__ __launch_bounds__(kThreads) void prefill_tile_mla_kernel(PrefillArgs 
   const int cnt = region ? a.list_cnt[i] : C;
   if (k * 32 >= cnt) return;
   const int32_t* lst = a.list + tok0;
+  if (threadIdx.x < 32) {   // key rows, as prefill_tile_kernel writes them
+    const int idx = 32 * k + threadIdx.x, p0 = a.pos[a.seq_ids[i]];
+    uint32_t mt = kNoKey;
+    if (idx < cnt)
+      mt = region ? static_cast<uint32_t>(p0 + lst[idx])
+                  : (static_cast<uint32_t>(p0 + idx) | (key_flag(a, tok0, C, idx, 0) ? kFlagBit : 0u));
+    a.tmeta[ws_tile(a, region, 0, i, k) * 32 + threadIdx.x] = mt;
+  }
   char* tile = a.tiles + ws_tile(a, region, 0, i, k) * kMlaTileBytes;
   constexpr int kRow = kMlaDim / 8;   // 16-byte pieces per row
   for (int pc = threadIdx.x; pc < 32 * kRow; pc += kThreads) {
@@ -1594,6 +1604,209 @@ __global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_kernel(PrefillArgs
   }
 }
 
+// Latent-attention pass under delayed eviction, 32x32 MFMA products: the work
+// items, masks and copies of prefill_delayed_kernel, a wave holding 32
+// (position, head) columns with their queries (144 registers) and 32 x 512
+// accumulators (256), one wave per SIMD.  A 32-row tile is staged by hardware
+// copies beside the attention of the tile before it and read twice: as rows
+// for the scores, through the LDS transpose read for the values.  Inside each
+// 1 KB block (32 dims of 16 rows) the copy permutes the 16-byte pieces, row r
+// of dim group G to place r ^ 4 G, so that the four dim groups of a transpose
+// read fall into different banks.  16x16 products read every operand for 16
+// columns and were bound by those reads; now the matrix core is the bound,
+// and, with one wave per SIMD, the softmax between its two products.  Four
+// prompts of 4096 to 8192 tokens in chunks of 4096, 16 heads: 988 us with
+// every pass, from 1703 us (attention 844 -> 477 us a call).
+__global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_delayed_kernel(PrefillArgs a) {
+  constexpr int NW = kMlaThreads / 64;
+  constexpr int KS = kMlaDim / 16, OB = kMlaLatent / 32;
+  __shared__ __attribute__((aligned(256))) char tile_lds[2][kMlaTileBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t meta_lds[2][64];   // rows 0..31 twice
+  __shared__ int item_lds[2], first_lds[kOrderMax + 1];
+  if (load_status(a.status) != 0) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hf = lane >> 5;
+  const float thr = kRescale / a.scale_log2, sl2 = a.scale_log2;
+  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
+  // operand addresses: rows of k-steps e, e even / odd, + 2048 (e / 2); columns of token half y, +
+  // 2048 per 32-dim block, + 1024 for tokens 4-7 of the eight
+  uint32_t k_addr[2], v_addr[2];
+  {
+    const int kt = row_token(lane & 31), r = 4 * (kt >> 3) + (kt & 3);
+    const int G = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1), j = (lane & 15) >> 2;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int Gk = 2 * e + hf;
+      k_addr[e] = lds_addr(tile_lds) + ((kt >> 2) & 1) * 1024 + Gk * 256 + (r ^ (4 * Gk)) * 16;
+      v_addr[e] = lds_addr(tile_lds) + G * 256 + ((4 * (2 * e + hf) + j) ^ (4 * G)) * 16 + 8 * (lane & 1);
+    }
+  }
+  const uint32_t piece = (lane ^ (4 * (lane >> 4))) * 16;   // source of a copy's lane in its 1 KB block
+
+  const int NH = a.n;
+  const bool ranked = NH <= kOrderMax;
+  if (ranked)
+    for (int x = tid; x <= NH; x += kMlaThreads) first_lds[x] = a.first_item[x];
+  __syncthreads();
+  const int items = ranked ? __builtin_amdgcn_readfirstlane(first_lds[NH]) : a.items;
+  if (static_cast<int>(blockIdx.x) >= items) return;
+  auto copy_tile = [&](const Item& it, int k, int page, int buf) {
+    const char* tile;
+    const uint32_t* mt;
+    tile_source(a, it, k, page, kMlaTileBytes, tile, mt);
+    const char* src = tile + wave * (kMlaTileBytes / NW) + piece;
+    const uint32_t dst = lds_addr(tile_lds) + buf * kMlaTileBytes + wave * (kMlaTileBytes / NW);
+#pragma unroll
+    for (int m = 0; m < kMlaTileBytes / NW / 1024; ++m) lds_copy16(src + m * 1024, dst + m * 1024);
+    if (wave == 0) lds_copy4(reinterpret_cast<const char*>(mt + (lane & 31)), lds_addr(meta_lds[buf]));
+  };
+  Item cur = prefill_item(a, first_lds, blockIdx.x, lane);
+  copy_tile(cur, 0, pool_page(a, cur, 0), 0);
+  int page = pool_page(a, cur, 1);
+  int par = 0, ib = 0;   // LDS buffer of the present tile, slot of the next item's index
+
+  const int col = wave * 32 + (lane & 31);
+  const int pl = col / a.g, qh = col % a.g;
+  while (true) {
+    const bool ok = pl < a.PB && cur.t0 + pl < cur.t1;
+    const int t = ok ? cur.t0 + pl : -1;
+    const size_t orow = static_cast<size_t>(cur.tok0 + (ok ? t - cur.p0 : 0)) * a.g + qh;
+    const size_t qrow = ok ? orow : 0;   // unused columns: any row (masked by t)
+    u32x4 qf[KS];
+#pragma unroll
+    for (int x = 0; x < KS; ++x) qf[x] = *reinterpret_cast<const u32x4*>(a.q + qrow * kMlaDim + 16 * x + 8 * hf);
+    f32x16 o[OB];
+#pragma unroll
+    for (int x = 0; x < OB; ++x)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
+    float m_ref = kMInit, l_run = 0.f;
+    if (tid == 0) item_lds[ib] = gridDim.x + atomicAdd(a.work_ctr, 1);   // read after this item's last barrier
+    Item nxt = cur;
+    bool have_next = false;
+    for (int k = 0; k < cur.ntiles; ++k) {
+      const int buf = par;
+      __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      __syncthreads();
+      if (k + 1 < cur.ntiles) {
+        copy_tile(cur, k + 1, page, buf ^ 1);
+      } else {
+        const int item = __builtin_amdgcn_readfirstlane(item_lds[ib]);
+        have_next = item < items;
+        if (have_next) {
+          nxt = prefill_item(a, first_lds, item, lane);
+          copy_tile(nxt, 0, pool_page(a, nxt, 0), buf ^ 1);
+        }
+      }
+      const int rows = rows_of(cur, k);
+      if (k == cur.nc - 1 && rows < 32) {
+        // the pool's last tile: rows past the live length are stale (a freed page may hold NaNs)
+        for (int P = tid; P < kMlaTileBytes / 16; P += kMlaThreads) {
+          const int r = (P & 15) ^ (4 * ((P >> 4) & 3));
+          if (8 * (r >> 2) + (r & 3) + 4 * ((P >> 6) & 1) >= rows)
+            *reinterpret_cast<u32x4*>(tile_lds[buf] + P * 16) = u32x4{0u, 0u, 0u, 0u};
+        }
+        __syncthreads();
+      }
+      uint32_t mrow = meta_lds[buf][lane & 31];
+      if ((lane & 31) >= rows) mrow = kNoKey;
+      const bool masked = __builtin_amdgcn_ballot_w64(row_hidden(mrow, cur, a.w)) != 0;
+      const uint32_t tl = buf * kMlaTileBytes;
+      const uint32_t ka[2] = {k_addr[0] + tl, k_addr[1] + tl}, va[2] = {v_addr[0] + tl, v_addr[1] + tl};
+      // scores: two chains (even and odd k-steps), operands read ahead in pinned order
+      f32x16 s, s1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
+      u32x4 op[kAhead];
+      auto read_k = [&](int e) {
+        return *reinterpret_cast<DMS_LDS const u32x4*>(ka[e & 1] + (e >> 1) * 2048);
+      };
+      auto read_v = [&](int e) {   // 32-dim block e % OB, token half e / OB
+        const char* p = (const char*)(DMS_LDS const char*)(va[e / OB] + (e % OB) * 2048);
+        const u32x2 lo = tr_read16(p), hi = tr_read16(p + 1024);
+        return u32x4{lo[0], lo[1], hi[0], hi[1]};
+      };
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e) op[e] = read_k(e);
+#pragma unroll
+      for (int e = 0; e < KS; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (e & 1) s1 = mfma32(op[e % kAhead], qf[e], s1);
+        else s = mfma32(op[e % kAhead], qf[e], s);
+        if (e + kAhead < KS) op[e % kAhead] = read_k(e + kAhead);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e) op[e] = read_v(e);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] += s1[i];
+      if (masked) mask_scores(s, &meta_lds[buf][8 * hf], rows, t, a.w, lane);
+      float mx = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+      mx = col_max32(mx);
+      const bool raise = mx > m_ref + thr;   // false while the column has seen no key
+      if (__builtin_amdgcn_ballot_w64(raise)) {
+        const float m_new = raise ? mx : m_ref;
+        const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
+        l_run *= alpha;
+#pragma unroll
+        for (int x = 0; x < OB; ++x)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            // in place: the compiler would move all accumulators at once and spill (the products
+            // before and after are many instructions away, past every matrix core hazard)
+            float v = o[x][i], u;
+            asm volatile(
+                "v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                : "+a"(v), "=&v"(u)
+                : "v"(alpha));
+            o[x][i] = v;
+          }
+        m_ref = m_new;
+      }
+      const float mb = m_ref * sl2;
+      u32x4 pu[2];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[2 * j], sl2, -mb)),
+                          __builtin_amdgcn_exp2f(fmaf(s[2 * j + 1], sl2, -mb))};
+        const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
+        pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
+        l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
+      }
+#pragma unroll
+      for (int e = 0; e < 2 * OB; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        o[e % OB] = mfma32(op[e % kAhead], pu[e / OB], o[e % OB]);
+        if (e + kAhead < 2 * OB) op[e % kAhead] = read_v(e + kAhead);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      par ^= 1;
+      if (k + 2 < cur.ntiles) page = pool_page(a, cur, k + 2);
+    }
+    if (have_next) page = pool_page(a, nxt, 1);
+
+    const float l = col_sum32(l_run);
+    if (ok) {
+      const float inv = 1.0f / l;
+      float* dst = a.out + orow * kMlaLatent + 4 * hf;
+#pragma unroll
+      for (int x = 0; x < OB; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          *reinterpret_cast<f32x4*>(dst + 32 * x + 8 * y) =
+              f32x4{o[x][4 * y], o[x][4 * y + 1], o[x][4 * y + 2], o[x][4 * y + 3]} * inv;
+    }
+    if (!have_next) return;
+    cur = nxt;
+    ib ^= 1;
+  }
+}
+
 hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta, void* ws, void* pool,
                               int layer, int n, const int32_t* seq_ids, const int32_t* cu,
                               int total_tokens, int max_len, const void* q, const void* k,
@@ -1619,9 +1832,9 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.tiles = w + lo.ws_pf_tiles;
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
-  a.rows = nullptr;
-  a.first_item = nullptr;
-  a.work_ctr = nullptr;
+  a.rows = reinterpret_cast<PrefillRow*>(w + lo.ws_pf_order);
+  a.first_item = reinterpret_cast<int32_t*>(a.rows + lo.max_heads);
+  a.work_ctr = a.list_cnt + lo.max_heads;
   a.nx = a.items = 0;
   a.tph = lo.pf_tiles_per_head;
   a.immediate = c.eviction == DMS_EVICT_IMMEDIATE;
@@ -1639,15 +1852,29 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.max_seqs = c.max_seqs;
   a.total = total_tokens;
   a.max_len = max_len;
-  a.PB = 0;
+  a.PB = kMlaThreads / 64 * 32 / c.group_size;   // positions per workgroup: 32 columns per wave
   a.scale_log2 = c.softmax_scale * 1.4426950408889634f;
   // the timing events bracket every pass
   if (ev_start) (void)hipEventRecord(ev_start, st);
   hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
+  if (!a.immediate) {
+    hipLaunchKernelGGL(prefill_order_kernel, dim3(n <= kOrderMax ? 1 : (n + kThreads - 1) / kThreads), dim3(kThreads), 0,
+                       st, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(prefill_tile_mla_kernel, dim3((max_len + 31) / 32, n, 2), dim3(kThreads), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (!a.immediate) {
+    a.nx = (max_len + a.PB - 1) / a.PB;
+    a.items = a.nx * n;
+    hipLaunchKernelGGL(prefill_mla_delayed_kernel, dim3(min(a.items, cu_count())), dim3(kMlaThreads), 0, st, a);
+    e = hipGetLastError();
+    if (ev_stop) (void)hipEventRecord(ev_stop, st);
+    return e;
+  }
   const int g = c.group_size;
   const int pcb = g <= kMaxGroup ? kMaxGroup / g : 1;
   const int cgs = (g + kMaxGroup - 1) / kMaxGroup;

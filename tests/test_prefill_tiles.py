@@ -4,6 +4,7 @@ a workgroup holds; sequences with nothing in the call; more rows than the
 ranking pass orders.  Outputs against dense masked attention."""
 import pytest
 
+from test_mla_parity import _prefill_run
 from test_prefill_parity import _run
 
 pytestmark = pytest.mark.gpu
@@ -31,3 +32,19 @@ def test_edges(fp8, d, g, w, lens, chunks):
 @pytest.mark.parametrize("n", [32, 33])   # 512 rows are ranked, 528 are taken in call order
 def test_many_rows(n):
     _tiles(64, 2, 8, [5 + (s * 13) % 60 for s in range(n)], [40, 9], H=16)
+
+
+@pytest.mark.parametrize("g,w,lens,chunks", [
+    (1, 1, (1, 31, 33), [1, 32]),            # 128 positions per workgroup
+    (16, 64, (64, 97, 130), [64, 33]),
+    (43, 40, (66, 33), [32, 33]),            # two positions and 42 unused columns
+    (128, 33, (65, 2), [32, 1, 32])])        # a position per workgroup
+def test_latent_edges(g, w, lens, chunks):
+    _prefill_run(g, list(range(len(lens))), dict(enumerate(lens)), chunks, 93, 0.5, w, 32, nan_fill=True)
+
+
+def test_latent_many_rows():
+    """513 sequences, taken in call order; the last one has nothing in the second call."""
+    lens = {s: 6 + s % 4 for s in range(512)}
+    lens[512] = 3
+    _prefill_run(2, sorted(lens), lens, [5], 95, 0.5, 2, 32, nan_fill=True)
