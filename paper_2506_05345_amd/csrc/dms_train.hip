@@ -23,12 +23,14 @@
 // core (about half busy in each).  32x32 products take half the MFMA and LDS
 // read instructions per key of 16x16 ones.  One layer of 8 x 5 heads, 2 x
 // 8192 tokens, w = 256, before (16x16 products on tiles re-laid in memory by a
-// pass of their own) and now: forward 1836 -> 1430 us (960 TFLOP/s), dQ 4005
-// -> 1850 us (1110 of its three products), dK / dV 5160 -> 2590 us (1060 of
-// its four), tiling and row sums 380 us -> none.  Pairing each tile's weights
-// with the next tile's scores and the last tile's value products in one
-// scheduled stretch ran 1540 to 1700 us forward: the second wave of a SIMD
-// already fills the gaps, and the tile-by-tile barriers cost more.
+// pass of their own) and now: forward 1836 -> 1400 us (980 TFLOP/s), dQ 4005
+// -> 1820 us (1130 of its three products), dK / dV 5160 -> 2570 us (1070 of
+// its four), tiling and row sums 380 us -> none; operands read ahead in pinned
+// order are 2 to 4 % of each pass here, 3 to 14 % with 2 x 1021 tokens.
+// Pairing each tile's weights with the next tile's scores and the last tile's
+// value products in one scheduled stretch ran 1540 to 1700 us forward: the
+// second wave of a SIMD already fills the gaps, and the tile-by-tile barriers
+// cost more.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -236,6 +238,10 @@ __device__ inline u32x4 col_operand(int tile, const LaneAddresses& r, int b, int
 // keeps the compiler from forming (and holding) every operand address ahead of the loop
 __device__ inline void refresh(LaneOffsets& o) { asm volatile("" : "+v"(o.row), "+v"(o.col), "+v"(o.src)); }
 
+// Operands are read kAhead MFMAs ahead of their use, in an order pinned step
+// by step (sched_barrier): left alone the compiler reads most operands right
+// before their MFMA and waits out the LDS latency every time.
+constexpr int kAhead = 4;
 // Scheduling order of a stretch of M MFMAs: P LDS reads ahead, then R reads
 // beside each (bounds the operands in flight, so that the accumulators and the
 // resident operands fit without spills).
@@ -248,6 +254,11 @@ __device__ __forceinline__ void paced() {
     __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
   }
 }
+// Key-major pass, whose sums and operands leave few registers: its score
+// products are paced (pinned, they ran 2680 against 2437 us), its sums pinned
+// with two operands ahead (2437 against 2495 us paced, and 72 against 84 where
+// splits leave one wave per SIMD or fewer).
+constexpr int kFew = 2;
 
 // ---------------------------------------------------------------------------
 // Shared arguments of the attention passes
@@ -303,12 +314,11 @@ __device__ inline int mask_class(int j0, int j1, int q0, int q1, int w, int T) {
   return 2;
 }
 
-// Scores of one 32-key tile for a wave's 32 columns, masked: register i of a
-// lane is key jt + 16 (i / 8) + 8 (lane / 32) + i % 8.  The bias of old keys
-// starts the accumulation (class 0; zeros otherwise); t < 0 (unused column)
-// hides every key of a mixed tile.
-__device__ inline f32x16 score_tile(int ktile, const float* bias, const float* zeros, const LaneAddresses& ad,
-                                    const u32x4 (&qf)[kKS], int cls, int jt, int t, int w, int hf) {
+// Scores of one 32-key tile for a wave's 32 columns: register i of a lane is
+// key jt + 16 (i / 8) + 8 (lane / 32) + i % 8.  The bias of old keys starts the
+// accumulation (class 0; zeros otherwise); mixed tiles (class 2) are masked
+// after it, t < 0 (unused column) hiding every key.
+__device__ inline f32x16 score_start(const float* bias, const float* zeros, int cls, int hf) {
   const float* c = (cls == 0 ? bias : zeros) + 8 * hf;
   f32x16 s;
 #pragma unroll
@@ -317,21 +327,19 @@ __device__ inline f32x16 score_tile(int ktile, const float* bias, const float* z
 #pragma unroll
     for (int e = 0; e < 4; ++e) s[4 * i + e] = x[e];
   }
+  return s;
+}
+__device__ inline void score_mask(f32x16& s, const float* bias, int jt, int t, int w, int hf) {
+  const int d = t - jt - 8 * hf;
 #pragma unroll
-  for (int x = 0; x < kKS; ++x) s = mfma(row_operand(ktile, ad, x), qf[x], s);
-  if (cls == 2) {
-    const int d = t - jt - 8 * hf;
-    f32x4 bv[4];
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + 16 * (i >> 1) + 8 * hf + 4 * (i & 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      bv[i] = *reinterpret_cast<const f32x4*>(bias + 16 * (i >> 1) + 8 * hf + 4 * (i & 1));
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int k = 16 * (i >> 3) + (i & 7);
-      s[i] = k > d ? -INFINITY : (k > d - w ? s[i] : s[i] + bv[i >> 2][i & 3]);
+    for (int e = 0; e < 4; ++e) {
+      const int k = 16 * (i >> 1) + 4 * (i & 1) + e;
+      s[4 * i + e] = k > d ? -INFINITY : (k > d - w ? s[4 * i + e] : s[4 * i + e] + bv[e]);
     }
   }
-  return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -397,13 +405,22 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
     // 64 keys at a time: both tiles' scores, one maximum and (rare) rescale, the weights, both
     // tiles' products (a second tile past the last is hidden: every key is after t)
     constexpr int tl = buf * kStage;
-    f32x16 s[2];
+    const int jt = 64 * st;
+    const int c0 = mask_class(jt, jt + 32, t0, t1, a.w, a.T), c1 = mask_class(jt + 32, jt + 64, t0, t1, a.w, a.T);
+    f32x16 s[2] = {score_start(&bias_lds[buf][0], zero_lds, c0, hf), score_start(&bias_lds[buf][32], zero_lds, c1, hf)};
+    u32x4 op[kAhead];
+    // score product e: tile e % 2, k-step e / 2 (the two chains take turns)
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const int jt = 64 * st + 32 * sub;
-      s[sub] = score_tile(tl + 2 * kUnit * sub, &bias_lds[buf][32 * sub], zero_lds, ad, qf,
-                          mask_class(jt, jt + 32, t0, t1, a.w, a.T), jt, t, a.w, hf);
+    for (int e = 0; e < kAhead; ++e) op[e] = row_operand(tl + 2 * kUnit * (e & 1), ad, e >> 1);
+#pragma unroll
+    for (int e = 0; e < 2 * kKS; ++e) {
+      __builtin_amdgcn_sched_barrier(0);
+      s[e & 1] = mfma(op[e % kAhead], qf[e >> 1], s[e & 1]);
+      if (e + kAhead < 2 * kKS) op[e % kAhead] = row_operand(tl + 2 * kUnit * (e & 1), ad, (e + kAhead) >> 1);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (c0 == 2) score_mask(s[0], &bias_lds[buf][0], jt, t, a.w, hf);
+    if (c1 == 2) score_mask(s[1], &bias_lds[buf][32], jt + 32, t, a.w, hf);
     float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
     for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
@@ -418,24 +435,33 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
       m_ref = m_new;
     }
     const float mb = m_ref * a.scale_log2;
+    // the denominator adds the bf16-rounded weights the MFMA uses (dot
+    // with (1, 1) on each packed pair as it is made)
+    u32x4 pu[2][2];
+    auto weight_pair = [&](int u, int j) {
+      const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[u][2 * j], a.scale_log2, -mb)),
+                        __builtin_amdgcn_exp2f(fmaf(s[u][2 * j + 1], a.scale_log2, -mb))};
+      const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
+      pu[u][j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
+      l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
+    };
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      // the denominator adds the bf16-rounded weights the MFMA uses (dot
-      // with (1, 1) on each packed pair as it is made)
-      u32x4 pu[2];
+    for (int j = 0; j < 8; ++j) weight_pair(0, j);
+    // value product e: tile e / 8, token half (e / 4) % 2, dim block e % 4; the
+    // second tile's weights are formed beside the first one's products
+    auto read_v = [&](int e) {
+      return col_operand(tl + 2 * kUnit * (e / (2 * kDB)) + kUnit, ad, e % kDB, (e / kDB) % 2);
+    };
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const f32x2 pr = {__builtin_amdgcn_exp2f(fmaf(s[sub][2 * j], a.scale_log2, -mb)),
-                          __builtin_amdgcn_exp2f(fmaf(s[sub][2 * j + 1], a.scale_log2, -mb))};
-        const bf16x2 pb = __builtin_convertvector(pr, bf16x2);
-        pu[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, pb);
-        l_run = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, l_run, false);
-      }
+    for (int e = 0; e < kAhead; ++e) op[e] = read_v(e);
 #pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int x = 0; x < kDB; ++x) o[x] = mfma(col_operand(tl + 2 * kUnit * sub + kUnit, ad, x, y), pu[y], o[x]);
+    for (int e = 0; e < 4 * kDB; ++e) {
+      __builtin_amdgcn_sched_barrier(0);
+      o[e % kDB] = mfma(op[e % kAhead], pu[e / (2 * kDB)][(e / kDB) % 2], o[e % kDB]);
+      if (e + kAhead < 4 * kDB) op[e % kAhead] = read_v(e + kAhead);
+      if (e < 8) weight_pair(1, e);
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
   for (int st = 0; 2 * st < ntiles; st += 2) {
     attend(st, std::integral_constant<int, 0>{});
@@ -547,19 +573,34 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
       const int jt = 64 * st + 32 * sub;
       constexpr int t_buf = buf * kStage;
       const int tl = t_buf + 2 * kUnit * sub;
-      f32x16 s = score_tile(tl, &bias_lds[buf][32 * sub], zero_lds, ad, qf,
-                            mask_class(jt, jt + 32, t0, t1, a.w, a.T), jt, t, a.w, hf);
-      f32x16 dp = mfma(row_operand(tl + kUnit, ad, 0), df[0], neg_d);
+      const int cls = mask_class(jt, jt + 32, t0, t1, a.w, a.T);
+      f32x16 s = score_start(&bias_lds[buf][32 * sub], zero_lds, cls, hf), dp;
+      u32x4 op[kAhead];
+      // product e: scores (keys) and dP (values) take turns, k-step e / 2
 #pragma unroll
-      for (int x = 1; x < kKS; ++x) dp = mfma(row_operand(tl + kUnit, ad, x), df[x], dp);
+      for (int e = 0; e < kAhead; ++e) op[e] = row_operand(tl + kUnit * (e & 1), ad, e >> 1);
+#pragma unroll
+      for (int e = 0; e < 2 * kKS; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (e & 1) dp = mfma(op[e % kAhead], df[e >> 1], e == 1 ? neg_d : dp);
+        else s = mfma(op[e % kAhead], qf[e >> 1], s);
+        if (e + kAhead < 2 * kKS) op[e % kAhead] = row_operand(tl + kUnit * (e & 1), ad, (e + kAhead) >> 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (cls == 2) score_mask(s, &bias_lds[buf][32 * sub], jt, t, a.w, hf);
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e) op[e] = col_operand(tl, ad, e % kDB, e / kDB);
       float ds[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(fmaf(s[i], a.scale_log2, -lse2)) * dp[i];
       const u32x4 du[2] = {pack_bf16(ds), pack_bf16(ds + 8)};
 #pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int x = 0; x < kDB; ++x) dqa[x] = mfma(col_operand(tl, ad, x, y), du[y], dqa[x]);
+      for (int e = 0; e < 2 * kDB; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        dqa[e % kDB] = mfma(op[e % kAhead], du[e / kDB], dqa[e % kDB]);
+        if (e + kAhead < 2 * kDB) op[e % kAhead] = col_operand(tl, ad, (e + kAhead) % kDB, (e + kAhead) / kDB);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   for (int st = 0; 2 * st < ntiles; st += 2) {
@@ -692,16 +733,20 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
       p[i] = s[i];
       ds[i] = dp[i];
     }
+    const u32x4 pu[2] = {pack_bf16(p), pack_bf16(p + 8)}, du[2] = {pack_bf16(ds), pack_bf16(ds + 8)};
+    // product e: dV (dO) and dK (Q) take turns, dim block (e / 2) % 4, token half e / 8
+    u32x4 op[kFew];
+    auto read = [&](int e) { return col_operand(tl + kUnit * ((e & 1) ^ 1), lo, (e >> 1) % kDB, e / (2 * kDB)); };
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      const u32x4 pu = pack_bf16(p + 8 * y), du = pack_bf16(ds + 8 * y);
+    for (int e = 0; e < kFew; ++e) op[e] = read(e);
 #pragma unroll
-      for (int x = 0; x < kDB; ++x) {
-        dva[x] = mfma(col_operand(tl + kUnit, lo, x, y), pu, dva[x]);
-        dka[x] = mfma(col_operand(tl, lo, x, y), du, dka[x]);
-      }
+    for (int e = 0; e < 4 * kDB; ++e) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int x = (e >> 1) % kDB, y = e / (2 * kDB);
+      if (e & 1) dka[x] = mfma(op[e % kFew], du[y], dka[x]);
+      else dva[x] = mfma(op[e % kFew], pu[y], dva[x]);
+      if (e + kFew < 4 * kDB) op[e % kFew] = read(e + kFew);
     }
-    paced<4, 4 * kDB, 2>();
     __builtin_amdgcn_sched_barrier(0);
   };
   auto publish = [&](int st) {   // stage st is in LDS for every wave; copy the next one
