@@ -31,7 +31,7 @@ TRAFFIC_PROFILES = {
     ("qwen-r1-32b-8x", "bf16"): "decode_kernel_qwen-r1-32b-8x.txt",
     ("qwen-r1-32b-8x", "fp8"): "decode_kernel_qwen-r1-32b-8x-fp8.txt",
     ("qwen-r1-7b-4x", "bf16"): "decode_kernel_qwen-r1-7b-4x.txt",
-    ("qwen-r1-1.5b-8x", "bf16"): "decode_step_kernel_qwen-r1-1.5b-8x.txt",
+    ("qwen-r1-1.5b-8x", "bf16"): "decode_short_kernel_qwen-r1-1.5b-8x.txt",
 }
 LATENCY_STEPS = 50   # default steps timed one by one for the per-step distribution
 
@@ -96,17 +96,21 @@ def profiled_traffic(profile, sources):
     return int(val) if val else None
 
 
-def decode_kernel_name(wl, quest_pages):
+def decode_kernel_name(wl, quest_pages, head_slots):
     """The launch that the decode kernel timing covers for this workload: the
     latent-attention kernel, the decode over Quest's selection (planned in the
-    launch up to 1024 call heads), the fused small-call step (up to 128 call
-    heads), or the planned decode kernel with the merge launch after it."""
+    launch up to 1024 call heads), a workgroup per head (up to 256 call heads
+    whose page table holds at most 2048 slots), the fused small-call step (up
+    to 128 call heads), or the planned decode kernel with the merge launch
+    after it."""
     D, NH = wl["head_dim"], wl["batch"] * wl["kv_heads"]
     if wl.get("kv_format", 0) == MLA:
         return "decode_mla_kernel"
     planned = f"decode_kernel<{D}> + merge_kernel<{D}>"
     if quest_pages > 0:
         return f"decode_attended_kernel<{D}>" if NH <= 1024 else planned
+    if NH <= 256 and head_slots <= 2048:
+        return f"decode_short_kernel<{D}>"
     return f"decode_step_kernel<{D}>" if NH <= 128 else planned
 
 
@@ -1259,7 +1263,8 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
             "traffic_source": "profiles/" + traffic_profile if traffic is not None else None,
-            "kernel": decode_kernel_name(wl, args.quest_pages),
+            "kernel": decode_kernel_name(wl, args.quest_pages,
+                                         cache.cfg.max_pages_per_head * cache.cfg.page_size),
             "kernel_timing": "HIP events around each decode launch, eager pass of the next "
                              f"{args.steps} steps",
             "kernel_avg_us": round(1e3 * kern_avg_ms, 2),

@@ -26,7 +26,7 @@
 // pass of their own) and now: forward 1836 -> 1400 us (980 TFLOP/s), dQ 4005
 // -> 1820 us (1130 of its three products), dK / dV 5160 -> 2570 us (1070 of
 // its four), tiling and row sums 380 us -> none; operands read ahead in pinned
-// order are 2 to 4 % of each pass here, 3 to 14 % with 2 x 1021 tokens.
+// order are 2 to 4 % of each pass here, 6 to 14 % with 1777 tokens of 2 heads.
 // Pairing each tile's weights with the next tile's scores and the last tile's
 // value products in one scheduled stretch ran 1540 to 1700 us forward: the
 // second wave of a SIMD already fills the gaps, and the tile-by-tile barriers
