@@ -18,23 +18,29 @@
 // 128 heads are two blocks per unit, dispatched to one XCD together so that
 // the second reads the unit's rows mostly from that XCD's L2).  Per tile:
 //  * the block copies the tile (36 KB, 36 one-KB wave loads) straight into
-//    one of four LDS buffers with global->LDS loads, three tiles ahead of the
-//    one being computed;
+//    one of four LDS buffers with global->LDS loads, two tiles ahead of the
+//    one being scored;
 //  * wave i < groups scores the tile for its 16 heads: the rows are stored in
 //    the fragment order of the 16x16x32 score MFMA (A operand: 16 rows, 32
 //    dims; two halves of 16 rows), so its A operands are 1 KB contiguous LDS
 //    reads; it keeps the group's running maximum and sum and leaves the
 //    tile's probabilities (bf16) and the rescale factor in LDS;
-//  * every wave then multiplies the probabilities of all the block's groups
-//    into its own 64 latent dims (O^T = V^T P, 16 output dims x 16 heads per
-//    MFMA).  The V^T operand (8 consecutive rows of one dim per lane) is the
+//  * one step later waves 4-7 multiply the probabilities of all the block's
+//    groups into their own 128 latent dims (O^T = V^T P, 16 output dims x 16
+//    heads per MFMA), while the first four score the next tile: each SIMD
+//    holds a wave of either kind, one barrier a tile.  The V^T operand (8 consecutive rows of one dim per lane) is the
 //    transpose of how rows are stored; the LDS transpose read of gfx950
 //    (ds_read_b64_tr_b16) forms it straight from the tile, reading 512
 //    contiguous bytes per instruction.
-// At a segment end (the unit's part of one head) each wave writes its 64
+// At a segment end (the unit's part of one head) each V wave writes its 128
 // dims of every head of the block: the head's output when the unit covered
 // the whole head, else one partial per (unit, head); the block that
 // completes a split head's tile count merges its partials in unit order.
+// Scoring and multiplying in turn, with two barriers a tile, took 245 us for
+// a decode call of 128 sequences with 128 query heads after 32768 tokens
+// (window 256, 7/8 flagged, planning included), side by side 235 us.  At 16
+// query heads one wave of each kind works and HBM is the bound: 5.1 TB/s
+// either way.
 #include "dms_common.h"
 
 namespace dms {
@@ -140,10 +146,11 @@ struct MlaPtrs {
 
 struct Smem {
   char tile[kNBuf][kTileBytes];             // tiles as stored (score fragment order)
-  u32x4 p[kBlockGroups][64];                // bf16 probabilities, PV B operand order
-  float alpha[kBlockGroups][kMaxGroup];     // rescale of a group's accumulators
+  // of the tile being scored and the one before it:
+  u32x4 p[2][kBlockGroups][64];             // bf16 probabilities, PV B operand order
+  float alpha[2][kBlockGroups][kMaxGroup];  // rescale of a group's accumulators
   float2 ml[kBlockGroups][kMaxGroup];       // (max, sum) at a segment end
-  int4 raise4;                              // per group: its maximum rose (rescale)
+  int4 raise4[2];                           // per group: its maximum rose (rescale)
   int last;
 };
 
@@ -270,17 +277,17 @@ __device__ __forceinline__ void run_role(Smem& S, const MlaPtrs& P, const MlaPar
 #pragma unroll
         for (int b = 0; b < kPvBlocks; ++b) acc[gi][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int i = 0; i < n; ++i) {
+    // step i: the scorers take tile i while the V waves take tile i - 1
+    for (int i = 0; i <= n; ++i) {
       const int t = t_lo + i;
-      const char* tl = S.tile[i & (kNBuf - 1)];
       // i == 0: the token row was loaded before the tiles
-      if constexpr (!kScore) wait_tile(i == 0 ? 0 : min(kNBuf - 2, n - 1 - i));
-      __syncthreads();   // tile i is in LDS; every wave is done with tile i - 1
+      if constexpr (!kScore) wait_tile(i == 0 ? 0 : min(kNBuf - 3, n - 1 - i));
+      __syncthreads();   // tile i is in LDS, tile i - 1's probabilities too; every wave is done with tile i - 2
       if constexpr (!kScore) {
-        if (i + kNBuf - 1 < n)
-          tile_to_lds(tile_of(t + kNBuf - 1), S.tile[(i + kNBuf - 1) & (kNBuf - 1)], v, lane, blk == a.nblk - 1);
+        if (i > 0 && i + kNBuf - 2 < n)
+          tile_to_lds(tile_of(t + kNBuf - 2), S.tile[(i + kNBuf - 2) & (kNBuf - 1)], v, lane, blk == a.nblk - 1);
       }
-      if (has_tok && t == tz) {
+      if (i < n && has_tok && t == tz) {
         if (tok_wave) {
           char* tw = S.tile[i & (kNBuf - 1)];
           const int j = d.z & 31;
@@ -289,10 +296,13 @@ __device__ __forceinline__ void run_role(Smem& S, const MlaPtrs& P, const MlaPar
         }
         __syncthreads();
       }
-      // rows at or past L are stale in the head's last tile
-      const int valid = (i == n - 1 && seg_end == c1) ? L - t * kTile : kTile;
+      // this role's tile; rows at or past L are stale in the head's last one
+      const int mine = kScore ? i : i - 1;
+      const int slot = mine & 1;
+      const char* tl = S.tile[mine & (kNBuf - 1)];
+      const int valid = (mine == n - 1 && seg_end == c1) ? L - (t_lo + mine) * kTile : kTile;
       if constexpr (kScore) {
-        if (active) {
+        if (active && i < n) {
           // the tile's 36 A pieces (1 KB each, piece 2s + h: half h, k-step
           // s) read from LDS in batches of kScoreBatch k-steps, the next
           // batch's reads in flight while the current one is multiplied
@@ -348,13 +358,13 @@ __device__ __forceinline__ void run_role(Smem& S, const MlaPtrs& P, const MlaPar
             psum += static_cast<float>(pb);
           }
           l += psum;
-          S.p[sg][lane] = __builtin_bit_cast(u32x4, pr);
-          if (G == 0) S.alpha[sg][r] = alpha;
-          if (lane == 0) reinterpret_cast<int*>(&S.raise4)[sg] = any;
+          S.p[slot][sg][lane] = __builtin_bit_cast(u32x4, pr);
+          if (G == 0) S.alpha[slot][sg][r] = alpha;
+          if (lane == 0) reinterpret_cast<int*>(&S.raise4[slot])[sg] = any;
         }
       }
-      __syncthreads();   // probabilities and rescale factors of every group
       if constexpr (!kScore) {
+        if (i == 0) continue;
         // V^T operands of this wave's row blocks (latent dims 128 v + 16 b ..),
         // rows 8G .. 8G+7 per lane, straight from the tile
         u32x4 vt[kPvBlocks];
@@ -366,14 +376,14 @@ __device__ __forceinline__ void run_role(Smem& S, const MlaPtrs& P, const MlaPar
           vt[b] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
         // every group's probabilities, rescale flag and factor
-        const int4 up4 = S.raise4;
+        const int4 up4 = S.raise4[slot];
         const int upg[kBlockGroups] = {up4.x, up4.y, up4.z, up4.w};
         u32x4 pb[kBlockGroups];
         float al[kBlockGroups];
 #pragma unroll
         for (int gi = 0; gi < kBlockGroups; ++gi) {
-          pb[gi] = S.p[gi][lane];
-          al[gi] = S.alpha[gi][r];
+          pb[gi] = S.p[slot][gi][lane];
+          al[gi] = S.alpha[slot][gi][r];
         }
         if (valid < kTile) {
           // stale rows of a freed page may hold any bits: zero them in V
