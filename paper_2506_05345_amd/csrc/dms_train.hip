@@ -177,7 +177,8 @@ __device__ inline int fresh(int x) {
 }
 
 // One wave copies rows t0 .. t0 + 31 of one head (row t at base + t * stride
-// bytes) to the LDS tile `dst`; rows past the last token repeat it.
+// bytes) to the LDS tile `dst`; rows past the last token repeat it (zero_rows
+// clears them once they have landed).
 __device__ inline void copy_tile(const char* base, int t0, int T, uint32_t stride, const LaneOffsets& o,
                                  int lane, uint32_t dst) {
   if (t0 + 32 <= T) {
@@ -194,6 +195,15 @@ __device__ inline void copy_tile(const char* base, int t0, int T, uint32_t strid
       lds_copy16(base + static_cast<size_t>(r0) * stride, d * stride + 16 * (c ^ (4 * tr + (m & 3))), dst + 1024 * m);
     }
   }
+}
+
+// Rows from .. 31 of the LDS tile that this wave copied, after it has waited for
+// the copy and before the barrier that publishes it: their weights are 0, and
+// 0 times an Inf or NaN of another token must not reach the sums.
+__device__ inline void zero_rows(uint32_t tile, int from, int lane) {
+  const int ln = fresh(lane);
+  for (int r = from + (ln >> 4); r < 32; r += 4)
+    *reinterpret_cast<DMS_LDS u32x4*>(tile + r * kRowB + 16 * (ln & 15)) = u32x4{0u, 0u, 0u, 0u};
 }
 
 // Operand reads of the LDS tile at byte address `t` (a multiple of 256).
@@ -386,6 +396,12 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
               tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
     if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
   };
+  // rows past the last token, and a second tile past the block's last, are zero
+  const int end = min(a.T, 32 * ntiles);
+  auto clear = [&](int st, int buf) {
+    const int from = end - 64 * st - 32 * (wave & 1);
+    if (from < 32) zero_rows(tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), max(from, 0), lane);
+  };
 
   f32x16 o[kDB];
 #pragma unroll
@@ -400,6 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
   auto attend = [&](int st, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
     wait_copies();
+    clear(st, buf);
     __syncthreads();
     if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
     // 64 keys at a time: both tiles' scores, one maximum and (rare) rescale, the weights, both
@@ -523,6 +540,12 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
               tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
     if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
   };
+  // rows past the last token, and a second tile past the block's last, are zero
+  const int end = min(a.T, 32 * ntiles);
+  auto clear = [&](int st, int buf) {
+    const int from = end - 64 * st - 32 * (wave & 1);
+    if (from < 32) zero_rows(tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), max(from, 0), lane);
+  };
   issue(0, 0);
 
   u32x4 qf[kKS], df[kKS];
@@ -566,6 +589,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
   auto attend = [&](int st, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
     wait_copies();
+    clear(st, buf);
     __syncthreads();
     if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
 #pragma unroll
@@ -751,6 +775,9 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
   };
   auto publish = [&](int st) {   // stage st is in LDS for every wave; copy the next one
     wait_copies();
+    // the last query tile (a group of steps, the first ones): rows past the last token are zero
+    if (first + 2 * st + (wave & 1) < a.g && (a.T & 31))
+      zero_rows(tiles + (st & 1) * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), a.T & 31, lane);
     __syncthreads();
     if (st + 1 < nst) issue((st & 1) ^ 1);
   };

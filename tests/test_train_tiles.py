@@ -24,25 +24,64 @@ def test_tile_edges(B, T, H, g, w, seed):
         assert r[name] <= GRAD_TOL, (name, r)
 
 
+def _inputs(B, T, H, g, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    shapes = {"q": (B, T, H * g, D), "k": (B, T, H, D), "v": (B, T, H, D), "dout": (B, T, H * g, D)}
+    x = {n: _dev_bf16(_bf16(rng.normal(size=s))) for n, s in shapes.items()}
+    x["alpha"] = torch.from_numpy(rng.uniform(0, 1, (B, T, H)).astype(np.float32)).cuda()
+    return x
+
+
+def _fwd_bwd(x, w):
+    """(out, lse, dq, dk, dv, dalpha) of one forward and backward call."""
+    import torch
+    from paper_2506_05345_amd import dms
+    B, T, H, _ = x["k"].shape
+    cfg = dms.make_train_config(B, T, H, x["q"].shape[2] // H, D, w)
+    ws = torch.empty(dms.dms_train_workspace(cfg), dtype=torch.uint8, device="cuda")
+    out = torch.empty(x["q"].shape, device="cuda")
+    lse = torch.empty((B, x["q"].shape[2], T), device="cuda")
+    grads = [torch.empty(x[n].shape, device="cuda") for n in ("q", "k", "v", "alpha")]
+    dms.dms_train_attention_fwd(cfg, x["q"], x["k"], x["v"], x["alpha"], out, lse, ws)
+    dms.dms_train_attention_bwd(cfg, x["q"], x["k"], x["v"], x["alpha"], out, lse, x["dout"], *grads, ws)
+    torch.cuda.synchronize()
+    return [out, lse, *grads]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,at", [("v", 40), ("k", 40), ("v", 101), ("k", 101)])
+def test_later_rows_stay_out_of_earlier_blocks(name, at):
+    """Blocks of 32 positions (four query heads) that end on an odd tile: a non-finite row of the tile
+    after their last one leaves them as they are, bit for bit."""
+    T, first = 128, at // 32 * 32
+    x = _inputs(1, T, 2, 4, 31)
+    clean = _fwd_bwd(x, 16)
+    x[name] = x[name].clone()
+    x[name][0, at] = float("inf") if name == "v" else float("nan")
+    got = _fwd_bwd(x, 16)
+    for i, ax in ((0, 1), (1, 2), (2, 1)):   # out, lse, dq
+        assert got[i].narrow(ax, 0, first).equal(clean[i].narrow(ax, 0, first)), i
+
+
+@pytest.mark.gpu
+def test_infinite_last_row_stays_infinite():
+    """The rows that fill the last tile add nothing, not a NaN from a repeated infinity."""
+    import torch
+    T = 50
+    x = _inputs(1, T, 1, 4, 32)
+    x["v"][0, T - 1] = float("inf")
+    assert bool(torch.isposinf(_fwd_bwd(x, 16)[0][0, T - 1]).all())
+    x = _inputs(1, T, 1, 4, 32)
+    x["dout"][0, T - 1] = float("inf")
+    assert bool(torch.isposinf(_fwd_bwd(x, 16)[4][0, T - 1]).all())
+
+
 @pytest.mark.gpu
 def test_unaligned_views_give_the_same_bits():
     import torch
-    from paper_2506_05345_amd import dms
-    B, T, H, g, w = 1, 150, 2, 3, 40
-    rng = np.random.default_rng(30)
-    shapes = {"q": (B, T, H * g, D), "k": (B, T, H, D), "v": (B, T, H, D), "dout": (B, T, H * g, D)}
-    x = {n: _dev_bf16(_bf16(rng.normal(size=s))) for n, s in shapes.items()}
-    alpha = torch.from_numpy(rng.uniform(0, 1, (B, T, H)).astype(np.float32)).cuda()
-    cfg = dms.make_train_config(B, T, H, g, D, w)
-    ws = torch.empty(dms.dms_train_workspace(cfg), dtype=torch.uint8, device="cuda")
-
-    def run(x):
-        out = torch.empty(shapes["q"], device="cuda")
-        lse = torch.empty((B, H * g, T), device="cuda")
-        grads = [torch.empty(shapes[n], device="cuda") for n in ("q", "k", "v")] + [torch.empty_like(alpha)]
-        dms.dms_train_attention_fwd(cfg, x["q"], x["k"], x["v"], alpha, out, lse, ws)
-        dms.dms_train_attention_bwd(cfg, x["q"], x["k"], x["v"], alpha, out, lse, x["dout"], *grads, ws)
-        return [out, lse, *grads]
+    w = 40
+    x = _inputs(1, 150, 2, 3, 30)
 
     def shifted(t):
         buf = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
@@ -51,6 +90,7 @@ def test_unaligned_views_give_the_same_bits():
         assert v.data_ptr() % 16
         return v
 
-    for a, b in zip(run(x), run({n: shifted(t) for n, t in x.items()})):
+    y = {n: shifted(t) if n != "alpha" else t for n, t in x.items()}
+    for a, b in zip(_fwd_bwd(x, w), _fwd_bwd(y, w)):
         # the split of the key-major pass depends on the room that the copies leave
         assert torch.allclose(a, b, rtol=1e-5, atol=1e-5 * float(a.abs().max()))
