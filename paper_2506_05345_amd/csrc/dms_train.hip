@@ -806,11 +806,15 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
       }
     }
   }
+  // a fully evicted key (keep = 0) takes exactly nothing from them, also where its sums, formed
+  // without that factor, overflowed
 #pragma unroll
-  for (int x = 0; x < kDB; ++x) {
-    dka[x] *= keep;
-    dva[x] *= keep;
-  }
+  for (int x = 0; x < kDB; ++x)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      dka[x][i] = keep == 0.f ? 0.f : dka[x][i] * keep;
+      dva[x][i] = keep == 0.f ? 0.f : dva[x][i] * keep;
+    }
   // ---- the rest, masked per element
   for (; st < nst; ++st) {
     publish(st);

@@ -78,6 +78,39 @@ def test_infinite_last_row_stays_infinite():
 
 
 @pytest.mark.gpu
+def test_evicted_key_takes_nothing_from_old_queries():
+    """alpha = 1 on a key whose scores lie about 84 above the log-sum-exp of every query past its window:
+    exp(s - lse) is finite in float32, its products with dout (dV) and q (dK) are not.  The key's dK and dV
+    are those of the queries in its window alone."""
+    import oracle
+    T, w, j = 256, 8, 20
+    x = _inputs(1, T, 1, 1, 33)
+    for n in ("q", "k", "v", "dout"):
+        x[n] = x[n].float().mul_(0.01).bfloat16()
+    x["alpha"].fill_(0.25)
+    x["alpha"][0, j] = 1.0
+    x["q"][..., 0] = 32.0
+    x["k"][..., 0] = 0.0
+    x["k"][0, j, 0, 0] = 31.5      # scaled score 32 * 31.5 / sqrt(128) = 89.1
+    x["dout"].fill_(0.0)
+    x["dout"][0, :, 0, 1:9] = 16384.0   # into dV only: no value has these dims
+    x["dout"][0, :, 0, 10] = 1.0        # sum dout out = 1: dS = -exp(s - lse)
+    x["v"][..., 1:9] = 0.0
+    x["v"][..., 10] = 1.0
+    x["v"][0, j, 0] = 0.0
+    got = [t.cpu().numpy() for t in _fwd_bwd(x, w)]
+    f = [x[n].float().cpu().numpy() for n in ("q", "k", "v")]
+    al, do = x["alpha"].cpu().numpy().astype(np.float64), x["dout"].float().cpu().numpy()
+    lse = oracle.train_attention(*f, al, w, 1)[1][0, 0, j + w:]
+    p = 32 * 31.5 / np.sqrt(D) - lse
+    assert p.min() > 82 and p.max() < 88, (p.min(), p.max())   # exp below 3.4e38, times 16384 above
+    gq, gk, gv, _ = oracle.train_attention_grads(*f, al, do, w, 1)
+    for name, a, ref in (("dq", got[2], gq), ("dk", got[3], gk), ("dv", got[4], gv)):
+        assert np.isfinite(a).all(), name
+        assert np.abs(a - ref).max() <= GRAD_TOL * max(1.0, np.abs(ref).max()), name
+
+
+@pytest.mark.gpu
 def test_unaligned_views_give_the_same_bits():
     import torch
     w = 40
