@@ -284,7 +284,7 @@ struct TrainArgs {
   float* bias;             // [B, H, 64 nst]: key biases in raw score units
   float* nlse;             // [B, Hq, 32 nt]: -lse / scale (raw score units), -inf past the last token
   float* nsum;             // [B, Hq, 32 nt]: -sum_d dout * out, 0 past the last token
-  float* part;             // [splits - 1] sets of (dk, dv [B, T, H, D], dalpha [B, T, H])
+  float* part;             // [sets] of (dk, dv [B, T, H, D], dalpha [B, T, H])
   float* o_out;
   float* lse_out;
   float* dq;
@@ -292,7 +292,9 @@ struct TrainArgs {
   float* dv;
   float* dalpha;
   size_t part_stride;      // floats of one set
-  int B, T, H, g, w, nt, nst, PB, splits;
+  int B, T, H, g, w, nt, nst, PB;
+  int splits;              // shares of a key block's steps (key-major pass)
+  int split0, count, sets; // of them this launch: the first, how many, and how many go to `part`
   float scale_log2;        // softmax scale * log2(e)
 };
 
@@ -669,8 +671,8 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
   const int2 wg = xcd_order();               // earliest (longest) key blocks first
   const int bh = wg.y;
   const int b = bh / a.H, h = bh % a.H;
-  const int split = wg.x % a.splits;
-  const int j0 = wg.x / a.splits * 128;
+  const int split = a.split0 + wg.x % a.count;
+  const int j0 = wg.x / a.count * 128;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5;
@@ -858,7 +860,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
     float *dk = a.dk, *dv = a.dv, *dal_out = a.dalpha;
     if (split) {
       const size_t kv = static_cast<size_t>(a.B) * a.T * a.H * kTrainD;
-      dk = a.part + (split - 1) * a.part_stride;
+      dk = a.part + (split - max(a.split0, 1)) * a.part_stride;
       dv = dk + kv;
       dal_out = dv + kv;
     }
@@ -877,8 +879,8 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
   }
 }
 
-// Adds the other workgroups' sums of a split key-major pass to the outputs,
-// in split order.
+// Adds the sums that a split key-major pass left in `part` to the outputs, in
+// split order.
 __global__ __launch_bounds__(kThreads) void train_sum_kernel(TrainArgs a) {
   const size_t rows = static_cast<size_t>(a.B) * a.T * a.H, kv = rows * kTrainD;
   const size_t i = (static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x) * 4;
@@ -886,14 +888,14 @@ __global__ __launch_bounds__(kThreads) void train_sum_kernel(TrainArgs a) {
   auto add = [&](float* dst, int n) {
     float x[4];
     for (int e = 0; e < n; ++e) x[e] = dst[e];
-    for (int sp = 1; sp < a.splits; ++sp)
-      for (int e = 0; e < n; ++e) x[e] += a.part[(sp - 1) * a.part_stride + i + e];
+    for (int sp = 0; sp < a.sets; ++sp)
+      for (int e = 0; e < n; ++e) x[e] += a.part[sp * a.part_stride + i + e];
     for (int e = 0; e < n; ++e) dst[e] = x[e];
   };
   if (i < 2 * kv) {   // rows of 128 floats: four at a time never straddle the two tensors
     float* dst = i < kv ? a.dk + i : a.dv + (i - kv);
     f32x4 x = *reinterpret_cast<const f32x4*>(dst);
-    for (int sp = 1; sp < a.splits; ++sp) x += *reinterpret_cast<const f32x4*>(a.part + (sp - 1) * a.part_stride + i);
+    for (int sp = 0; sp < a.sets; ++sp) x += *reinterpret_cast<const f32x4*>(a.part + sp * a.part_stride + i);
     *reinterpret_cast<f32x4*>(dst) = x;
   } else {
     add(a.dalpha + (i - 2 * kv), static_cast<int>(min(static_cast<size_t>(4), 2 * kv + rows - i)));
@@ -1039,20 +1041,31 @@ hipError_t launch_train_bwd(const dms_train_config& c, const void* q, const void
   hipLaunchKernelGGL(train_dq_kernel, grid, dim3(kThreads), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // Key-major pass: about two workgroups per CU, the room left in the
-  // workspace permitting (always at least g sets of sums with aligned inputs)
+  // Key-major pass: about two workgroups per CU.  Copies of unaligned inputs
+  // can leave room for fewer sets of sums than there are splits (with aligned
+  // inputs at least g sets fit, with four copies at least one for g > 1): the
+  // splits then take several launches, each added before the next, so that
+  // the order of the sums does not depend on the addresses.
   a.part = reinterpret_cast<float*>(w + l.part);
   const int blocks = (c.seq_len + 127) / 128;
   const int64_t wgs = static_cast<int64_t>(blocks) * c.batch * c.num_kv_heads;
-  const int64_t room = l.bytes > l.part ? static_cast<int64_t>((l.bytes - l.part) / (l.part_stride * 4)) : 0;
-  a.splits = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({512 / wgs, 1 + room, c.group_size})));
-  hipLaunchKernelGGL(train_dkv_kernel, dim3(blocks * a.splits, c.batch * c.num_kv_heads), dim3(kThreads), 0, st, a);
-  e = hipGetLastError();
-  if (e != hipSuccess || a.splits == 1) return e;
-  const size_t n = (rows * (2 * kTrainD + 1) + 3) / 4;
-  hipLaunchKernelGGL(train_sum_kernel, dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     st, a);
-  return hipGetLastError();
+  const int room = l.bytes > l.part ? static_cast<int>(std::min<size_t>(kMaxGroup, (l.bytes - l.part) / (l.part_stride * 4))) : 0;
+  a.splits = room ? static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(512 / wgs, c.group_size))) : 1;
+  for (int s = 0; s < a.splits; s += a.count) {
+    a.split0 = s;
+    a.sets = std::min(room, a.splits - std::max(s, 1));
+    a.count = a.sets + (s == 0);
+    hipLaunchKernelGGL(train_dkv_kernel, dim3(blocks * a.count, c.batch * c.num_kv_heads), dim3(kThreads), 0, st, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (a.sets == 0) continue;
+    const size_t n = (rows * (2 * kTrainD + 1) + 3) / 4;
+    hipLaunchKernelGGL(train_sum_kernel, dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                       st, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_gumbel_fwd(int n, const float* x, const float* u, float tau, float* alpha,

@@ -111,10 +111,12 @@ def test_evicted_key_takes_nothing_from_old_queries():
 
 
 @pytest.mark.gpu
-def test_unaligned_views_give_the_same_bits():
+@pytest.mark.parametrize("T,H,g", [(150, 2, 3), (97, 1, 6), (200, 1, 16), (64, 2, 2)])
+def test_unaligned_views_give_the_same_bits(T, H, g):
+    """Also where the copies of the inputs leave room for fewer sums than the key-major pass has splits."""
     import torch
     w = 40
-    x = _inputs(1, 150, 2, 3, 30)
+    x = _inputs(1, T, H, g, 30)
 
     def shifted(t):
         buf = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
@@ -125,5 +127,4 @@ def test_unaligned_views_give_the_same_bits():
 
     y = {n: shifted(t) if n != "alpha" else t for n, t in x.items()}
     for a, b in zip(_fwd_bwd(x, w), _fwd_bwd(y, w)):
-        # the split of the key-major pass depends on the room that the copies leave
-        assert torch.allclose(a, b, rtol=1e-5, atol=1e-5 * float(a.abs().max()))
+        assert torch.equal(a, b)
