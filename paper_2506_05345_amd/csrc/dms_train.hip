@@ -158,12 +158,15 @@ __device__ inline LaneOffsets lane_offsets(int lane, uint32_t row_stride) {
 __device__ inline uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DMS_LDS const char*)p));
 }
-// 64 lanes x 16 bytes (4 bytes) from base + off (per lane) to LDS m0 + 16 (4) lane.  The LDS
+// 64 lanes x 16 bytes (4 bytes) from base + off (per lane), or src (per lane), to LDS m0 + 16 (4) lane.  The LDS
 // destination goes in M0, written by the same statement; nothing else in this
 // file reads M0.  The compiler does not count these loads: the kernels wait
 // for them (vmcnt) before the barrier that publishes a stage.
 __device__ inline void lds_copy16(const void* base, uint32_t off, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ inline void lds_copy16(const void* src, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(m0), "v"(src) : "memory", "m0");
 }
 __device__ inline void lds_copy4(const void* base, uint32_t off, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(m0), "v"(off), "s"(base) : "memory", "m0");
@@ -177,11 +180,12 @@ __device__ inline int fresh(int x) {
 }
 
 // One wave copies rows t0 .. t0 + 31 of one head (row t at base + t * stride
-// bytes) to the LDS tile `dst`; rows past the last token repeat it (zero_rows
-// clears them once they have landed).
-__device__ inline void copy_tile(const char* base, int t0, int T, uint32_t stride, const LaneOffsets& o,
-                                 int lane, uint32_t dst) {
-  if (t0 + 32 <= T) {
+// bytes) to the LDS tile `dst`.  Rows from `end` on are copied from 16 zero
+// bytes: their weights are 0, and 0 times an Inf or NaN of some token must not
+// reach the sums.
+__device__ inline void copy_tile(const char* base, int t0, int end, uint32_t stride, const LaneOffsets& o,
+                                 int lane, uint32_t dst, const void* zeros) {
+  if (t0 + 32 <= end) {
     const char* src = base + static_cast<size_t>(t0) * stride;
 #pragma unroll
     for (int m = 0; m < 8; ++m) lds_copy16(src + static_cast<size_t>(4 * m) * stride, o.src ^ (16 * (m & 3)), dst + 1024 * m);
@@ -190,20 +194,11 @@ __device__ inline void copy_tile(const char* base, int t0, int T, uint32_t strid
     const int tr = ln >> 4, c = ln & 15;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      const int r0 = min(t0 + 4 * m, T - 1);                    // first row of the copy
-      const uint32_t d = min(tr, T - 1 - r0);
-      lds_copy16(base + static_cast<size_t>(r0) * stride, d * stride + 16 * (c ^ (4 * tr + (m & 3))), dst + 1024 * m);
+      const int t = t0 + 4 * m + tr;
+      const char* p = base + static_cast<size_t>(t) * stride + 16 * (c ^ (4 * tr + (m & 3)));
+      lds_copy16(t < end ? p : static_cast<const char*>(zeros), dst + 1024 * m);
     }
   }
-}
-
-// Rows from .. 31 of the LDS tile that this wave copied, after it has waited for
-// the copy and before the barrier that publishes it: their weights are 0, and
-// 0 times an Inf or NaN of another token must not reach the sums.
-__device__ inline void zero_rows(uint32_t tile, int from, int lane) {
-  const int ln = fresh(lane);
-  for (int r = from + (ln >> 4); r < 32; r += 4)
-    *reinterpret_cast<DMS_LDS u32x4*>(tile + r * kRowB + 16 * (ln & 15)) = u32x4{0u, 0u, 0u, 0u};
 }
 
 // Operand reads of the LDS tile at byte address `t` (a multiple of 256).
@@ -284,6 +279,7 @@ struct TrainArgs {
   float* bias;             // [B, H, 64 nst]: key biases in raw score units
   float* nlse;             // [B, Hq, 32 nt]: -lse / scale (raw score units), -inf past the last token
   float* nsum;             // [B, Hq, 32 nt]: -sum_d dout * out, 0 past the last token
+  float* zeros;            // 16 zero bytes
   float* part;             // [sets] of (dk, dv [B, T, H, D], dalpha [B, T, H])
   float* o_out;
   float* lse_out;
@@ -305,6 +301,7 @@ __global__ __launch_bounds__(kThreads) void train_bias_kernel(TrainArgs a, bool 
   const int n = 64 * a.nst;
   const int j = blockIdx.x * kThreads + threadIdx.x;
   if (j >= n) return;
+  if (blockIdx.y == 0 && j < 4) a.zeros[j] = 0.f;
   const int b = blockIdx.y / a.H, h = blockIdx.y % a.H;
   float x = 0.f;
   if (j < a.T) x = __log2f(1.0f - a.alpha[(static_cast<size_t>(b) * a.T + j) * a.H + h]) / a.scale_log2;
@@ -393,16 +390,11 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
   const LaneAddresses ad = lane_addresses(tiles, lo);
   const char* kv = reinterpret_cast<const char*>((wave >> 1 ? a.v : a.k) + (static_cast<size_t>(b) * a.T * a.H + h) * kTrainD);
   const float* bias = a.bias + static_cast<size_t>(bh) * 64 * a.nst;
+  const int end = min(a.T, 32 * ntiles);   // a second tile past the block's last one is not read
   auto issue = [&](int st, int buf) {
-    copy_tile(kv, 64 * st + 32 * (wave & 1), a.T, stride, lo, lane,
-              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+    copy_tile(kv, 64 * st + 32 * (wave & 1), end, stride, lo, lane,
+              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), a.zeros);
     if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
-  };
-  // rows past the last token, and a second tile past the block's last, are zero
-  const int end = min(a.T, 32 * ntiles);
-  auto clear = [&](int st, int buf) {
-    const int from = end - 64 * st - 32 * (wave & 1);
-    if (from < 32) zero_rows(tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), max(from, 0), lane);
   };
 
   f32x16 o[kDB];
@@ -418,7 +410,6 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
   auto attend = [&](int st, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
     wait_copies();
-    clear(st, buf);
     __syncthreads();
     if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
     // 64 keys at a time: both tiles' scores, one maximum and (rare) rescale, the weights, both
@@ -537,16 +528,11 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
   const LaneAddresses ad = lane_addresses(tiles, lo);
   const char* kv = reinterpret_cast<const char*>((wave >> 1 ? a.v : a.k) + (static_cast<size_t>(b) * a.T * a.H + h) * kTrainD);
   const float* bias = a.bias + static_cast<size_t>(bh) * 64 * a.nst;
+  const int end = min(a.T, 32 * ntiles);   // a second tile past the block's last one is not read
   auto issue = [&](int st, int buf) {
-    copy_tile(kv, 64 * st + 32 * (wave & 1), a.T, stride, lo, lane,
-              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+    copy_tile(kv, 64 * st + 32 * (wave & 1), end, stride, lo, lane,
+              tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), a.zeros);
     if (wave == 0) lds_copy4(bias + 64 * st, 4 * lane, lds_addr(bias_lds[buf]));
-  };
-  // rows past the last token, and a second tile past the block's last, are zero
-  const int end = min(a.T, 32 * ntiles);
-  auto clear = [&](int st, int buf) {
-    const int from = end - 64 * st - 32 * (wave & 1);
-    if (from < 32) zero_rows(tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), max(from, 0), lane);
   };
   issue(0, 0);
 
@@ -591,7 +577,6 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
   auto attend = [&](int st, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
     wait_copies();
-    clear(st, buf);
     __syncthreads();
     if (2 * st + 2 < ntiles) issue(st + 1, buf ^ 1);
 #pragma unroll
@@ -699,7 +684,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
     if (ld_step < last) {
       const size_t hq = h * a.g + ld_qh;
       copy_tile(reinterpret_cast<const char*>(src + (static_cast<size_t>(b) * a.T * Hq + hq) * kTrainD), 32 * ld_tile,
-                a.T, stride, lo, lane, tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1));
+                a.T, stride, lo, lane, tiles + buf * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), a.zeros);
       if (wave < 2) {
         const int ln = fresh(lane);
         const uint32_t off = 4 * (32 * ld_tile + (ln & 31));
@@ -777,9 +762,6 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_kernel(TrainArgs a) {
   };
   auto publish = [&](int st) {   // stage st is in LDS for every wave; copy the next one
     wait_copies();
-    // the last query tile (a group of steps, the first ones): rows past the last token are zero
-    if (first + 2 * st + (wave & 1) < a.g && (a.T & 31))
-      zero_rows(tiles + (st & 1) * kStage + 2 * kUnit * (wave & 1) + kUnit * (wave >> 1), a.T & 31, lane);
     __syncthreads();
     if (st + 1 < nst) issue((st & 1) ^ 1);
   };
@@ -928,10 +910,10 @@ __global__ __launch_bounds__(kThreads) void train_align_kernel(const uint16_t* s
 }
 
 // Workspace (2 (H + Hq) 16 KB per sequence and 32 positions, and 4 B Hq T):
-// key biases, the two per-row arrays, aligned copies of inputs that need one
+// 16 zero bytes, key biases, the two per-row arrays, aligned copies of inputs that need one
 // and, for a split key-major pass, the further workgroups' sums in what is left.
 struct TrainLayout {
-  size_t bias, nlse, nsum, part, bytes;
+  size_t zeros, bias, nlse, nsum, part, bytes;
   size_t part_stride;   // floats of one set of sums
   int nt, nst;
 };
@@ -947,6 +929,7 @@ TrainLayout train_layout(const dms_train_config& c) {
             align_up(B * Hq * T * 4, kAlign);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
+  l.zeros = take(16);
   l.bias = take(B * H * l.nst * 64 * 4);
   l.nlse = take(B * Hq * l.nt * 32 * 4);
   l.nsum = take(B * Hq * l.nt * 32 * 4);
@@ -969,6 +952,7 @@ hipError_t align_input(const uint16_t*& dst, const void* src, size_t rows, Train
 TrainArgs train_args(const dms_train_config& c, const TrainLayout& l, void* ws) {
   TrainArgs a{};
   char* w = static_cast<char*>(ws);
+  a.zeros = reinterpret_cast<float*>(w + l.zeros);
   a.bias = reinterpret_cast<float*>(w + l.bias);
   a.nlse = reinterpret_cast<float*>(w + l.nlse);
   a.nsum = reinterpret_cast<float*>(w + l.nsum);
