@@ -115,6 +115,7 @@ Layout make_layout(const dms_config& c) {
   lo.ws_pf_tiles = take(2 * H * static_cast<size_t>(lo.pf_tiles_per_head) * D *
                         (c.kv_format == DMS_KV_MLA ? 64 : 128));
   lo.ws_pf_tmeta = take(2 * H * static_cast<size_t>(lo.pf_tiles_per_head) * 32 * 4);   // their key rows
+  lo.ws_pf_zeros = take(D * 64);   // zero values of a tile that does not exist
   lo.ws_pf_flags = take(static_cast<size_t>(c.max_chunk_tokens) * H);  // decisions from q
   // kept chunk tokens before every 32-aligned chunk position, per KV head
   // (same indexing as the tiles of one region)

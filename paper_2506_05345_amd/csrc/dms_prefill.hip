@@ -117,6 +117,7 @@ struct PrefillArgs {
   int nx, items;          // query blocks per grid row; rows x nx
   char* tiles;            // [2][H][tph] tiles: chunk tokens, then compacted kept tokens
   uint32_t* tmeta;        // [2][H][tph][32]: key rows of those tiles (position | flag << 31)
+  char* zeros;            // values of one tile, all 0 (bf16 pages)
   float* out;             // [T, Hq, D]
   size_t page_bytes;
   int n, H, g, w, P, log2P, maxp, max_slots, max_seqs, total, max_len, PB, tph;
@@ -219,6 +220,8 @@ __global__ __launch_bounds__(kThreads) void prefill_tile_kernel(PrefillArgs a) {
   __shared__ uint16_t vrows[32][D + 2];
   if (load_status(a.status) != 0) return;
   const int k = blockIdx.x, hh = blockIdx.y, region = blockIdx.z;
+  if (!FP8 && k == 0 && hh == 0 && region == 1)
+    for (int x = threadIdx.x; x < D * 4; x += kThreads) reinterpret_cast<u32x4*>(a.zeros)[x] = u32x4{0u, 0u, 0u, 0u};
   const int i = hh / a.H, h = hh % a.H;
   const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
   const int cnt = region ? a.list_cnt[hh] : C;
@@ -963,7 +966,10 @@ void prefill_delayed_kernel(PrefillArgs a) {
     } else {
       // wave w copies the keys (w even) or values of tile w / 2 of the stage
       source(it, min(2 * st + my_sub, it.ntiles - 1), pg[0], tile, mt);
-      const char* src = tile + (wave & 1) * (D * 64) + lane * 16;
+      // a tile past the last (the last one again, its keys hidden) has zero values: 0 times an Inf
+      // of the last one must not reach the sums
+      if (wave & 1) tile = 2 * st + my_sub >= it.ntiles ? a.zeros : tile + D * 64;
+      const char* src = tile + lane * 16;
       const uint32_t dst = lds_addr(tile_lds[0]) + buf * 2 * kTB + my_sub * kTB + (wave & 1) * (D * 64);
 #pragma unroll
       for (int m = 0; m < D / 16; ++m) lds_copy16(src + m * 1024, dst + m * 1024);
@@ -977,7 +983,8 @@ void prefill_delayed_kernel(PrefillArgs a) {
 #pragma unroll
       for (int u = 0; u < kSubs; ++u) {
         const int k = min(2 * st + u, it.ntiles - 1);
-        const int valid = k < it.nc ? min(32, it.L0 - k * 32) : 32;
+        // (a tile past the last: none)
+        const int valid = 2 * st + u >= it.ntiles ? 0 : k < it.nc ? min(32, it.L0 - k * 32) : 32;
         char* dst = tile_lds[buf] + u * kTB;
         u32x4 x = cx[u];
         int P0, step;
@@ -1239,6 +1246,7 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   a.list_cnt = reinterpret_cast<int32_t*>(w + lo.ws_pf_cum);
   a.tiles = w + lo.ws_pf_tiles;
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
+  a.zeros = w + lo.ws_pf_zeros;
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
   a.rows = reinterpret_cast<PrefillRow*>(w + lo.ws_pf_order);
   a.first_item = reinterpret_cast<int32_t*>(a.rows + lo.max_heads);
@@ -1831,6 +1839,7 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   a.list_cnt = reinterpret_cast<int32_t*>(w + lo.ws_pf_cum);
   a.tiles = w + lo.ws_pf_tiles;
   a.tmeta = reinterpret_cast<uint32_t*>(w + lo.ws_pf_tmeta);
+  a.zeros = w + lo.ws_pf_zeros;
   a.kept_before = reinterpret_cast<int32_t*>(w + lo.ws_pf_kb);
   a.rows = reinterpret_cast<PrefillRow*>(w + lo.ws_pf_order);
   a.first_item = reinterpret_cast<int32_t*>(a.rows + lo.max_heads);

@@ -29,6 +29,36 @@ def test_edges(fp8, d, g, w, lens, chunks):
     _tiles(d, g, w, lens, chunks, H=2, fp8=fp8)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [5, 33, 70])    # one, two and three tiles
+def test_infinite_value_stays_infinite(d, T):
+    """Stages hold two tiles; where the second does not exist it adds nothing: an infinite value row seen by
+    the last position only makes its output infinite, not NaN, and leaves earlier tiles' positions alone."""
+    import torch
+    from paper_2506_05345_amd import dms
+    H, g, w = 2, 4, 16
+    cfg = dms.make_config(1, 1, H, g, d, w, 32, H * 4, 4, T)
+    gen = torch.Generator("cuda").manual_seed(5)
+    q, k, v = (torch.randn((T, n, d), generator=gen, device="cuda").bfloat16() for n in (H * g, H, H))
+    flags = (torch.rand((T, H), generator=gen, device="cuda") < 0.5).to(torch.uint8)
+    sid, cu = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    outs = []
+    for last in (None, float("inf")):
+        if last is not None:
+            v[T - 1] = last
+        cache = dms.DmsCache(cfg)
+        out = torch.empty((T, H * g, d), device="cuda")
+        dms.dms_prefill_chunk(cache.ctx, 0, 1, sid, cu, T, T, q, k, v, flags, out)
+        torch.cuda.synchronize()
+        assert dms.dms_status(cache.ctx) == 0
+        cache.close()
+        outs.append(out)
+    assert bool(torch.isposinf(outs[1][T - 1]).all())
+    # a workgroup takes 32 positions of 4 heads; the tiles of all but the last end before the row
+    before = (T - 1) // 32 * 32
+    assert outs[1][:before].equal(outs[0][:before])
+
+
 @pytest.mark.parametrize("n", [32, 33])   # 512 rows are ranked, 528 are taken in call order
 def test_many_rows(n):
     _tiles(64, 2, 8, [5 + (s * 13) % 60 for s in range(n)], [40, 9], H=16)
