@@ -104,7 +104,7 @@ Layout make_layout(const dms_config& c) {
   lo.ws_ck_fresh = take(NH * 4);
   lo.ws_ck_base = take(NH * 4);
   lo.ws_ck_pos0 = take(S * 4);
-  lo.ws_ck_err = take(16);
+  lo.ws_ck_top = take(16);
   lo.ws_ck_slot = take(static_cast<size_t>(c.max_chunk_tokens) * H * 4);
   lo.ws_pf_cum = take((NH + 1) * 4);
   lo.ws_pf_meta = take(static_cast<size_t>(c.max_chunk_tokens) * H * 4);

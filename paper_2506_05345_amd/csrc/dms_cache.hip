@@ -25,7 +25,6 @@ __device__ inline int load_status(const int32_t* status) {
 
 struct InitArgs {
   char* meta;
-  int32_t* ck_err;
   int32_t* head_cnt;
   int32_t* plan_ctr;
   int64_t n_heads;
@@ -54,8 +53,6 @@ __global__ void init_state_kernel(InitArgs a) {
     *reinterpret_cast<int32_t*>(b + a.top) = a.num_pages;
     if (blockIdx.y == 0) {
       *reinterpret_cast<int32_t*>(a.meta) = 0;  // status
-      a.ck_err[0] = 0;
-      a.ck_err[1] = 0;
       a.plan_ctr[0] = 0;
     }
   }
@@ -531,11 +528,11 @@ struct ChunkArgs {
   const uint16_t* v;
   char* pool;
   size_t page_bytes;
-  int32_t* need;          // [n*H] pages to pop per head
+  int32_t* need;          // [n*H] pages to pop per head, or the error that refuses the call
   int32_t* fresh;         // [n*H] fresh tokens per head
   int32_t* base;          // [n*H] first pop index per head
   int32_t* pos0;          // [n] position of each sequence before the chunk
-  int32_t* err;           // call-local error word, err[1] = stack height before the call
+  int32_t* top_before;    // stack height before the call
   int32_t* slots;         // [T, H] slot of every fresh chunk token
   // masked prefill (null otherwise): kept chunk tokens, see dms_prefill.hip
   int32_t* list;          // [H][total]
@@ -568,7 +565,9 @@ __device__ inline bool chunk_reuse(const ChunkArgs& a, int sh, int h, int tok0, 
 constexpr int kScanThreads = 1024;
 constexpr int kScanTPT = 4;   // consecutive chunk tokens per thread in the scan
 
-// Pass 1 (one block per head): count fresh tokens and the pages they need,
+// Pass 1 (one block per head): count fresh tokens and the pages they need (a
+// call that pass 2 must refuse is marked in their place, so that nothing is
+// left for a later call where pass 2 does not follow),
 // and give every fresh token its slot (L0 + its index among the fresh ones;
 // the slot array is scratch, so writing it before validation is harmless).
 // Before a masked prefill it also lists the kept chunk tokens in position
@@ -591,7 +590,7 @@ __global__ __launch_bounds__(kScanThreads) void chunk_scan_kernel(ChunkArgs a) {
   if (bad) {
     if (threadIdx.x == 0) {
       if (a.list != nullptr) set_status(a.status_w, DMS_ERR_INVALID);
-      else atomicCAS(reinterpret_cast<int*>(a.err), 0, DMS_ERR_INVALID);
+      else a.need[hh] = DMS_ERR_INVALID;
     }
     return;
   }
@@ -634,9 +633,8 @@ __global__ __launch_bounds__(kScanThreads) void chunk_scan_kernel(ChunkArgs a) {
   }
   if (threadIdx.x == 0) {
     const int L1 = L0 + cnt;
-    if (L1 > a.max_slots) atomicCAS(reinterpret_cast<int*>(a.err), 0, DMS_ERR_CAPACITY);
     a.fresh[hh] = cnt;
-    a.need[hh] = (L1 + a.P - 1) / a.P - (L0 + a.P - 1) / a.P;
+    a.need[hh] = L1 > a.max_slots ? DMS_ERR_CAPACITY : (L1 + a.P - 1) / a.P - (L0 + a.P - 1) / a.P;
     if (a.list != nullptr) a.list_cnt[hh] = kcnt;
     if (h == 0) a.pos0[i] = pos0;
   }
@@ -648,11 +646,7 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
   __shared__ int lds[17];
   __shared__ int s_abort;
   if (threadIdx.x == 0) s_abort = load_status(a.status) != 0;
-  // consume and clear pass 1's error word (also where the call does nothing: some blocks of
-  // pass 1 may have run before another one set the status)
-  const int err = *a.err;
   __syncthreads();
-  if (threadIdx.x == 0) a.err[0] = 0;
   if (s_abort) return;
   if (bad_seq_ids(a.seq_ids, a.n, a.max_seqs, seen)) {
     if (threadIdx.x == 0) set_status(a.status_w, DMS_ERR_BAD_SEQ);
@@ -660,29 +654,31 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
   }
   const int NH = a.n * a.H;
   const int top0 = *a.st.top;
-  int run = 0;
+  int run = 0, invalid = 0, over = 0;
   for (int base = 0; base < NH; base += blockDim.x) {
     const int hh = base + threadIdx.x;
     const int nd = hh < NH ? a.need[hh] : 0;
+    invalid |= nd == DMS_ERR_INVALID;
+    over |= nd == DMS_ERR_CAPACITY;
     int tot;
-    const int off = block_exclusive_scan(nd, lds, &tot);
+    const int off = block_exclusive_scan(max(nd, 0), lds, &tot);
     if (hh < NH) a.base[hh] = run + off;
     run += tot;
   }
+  invalid = __syncthreads_or(invalid);
+  over = __syncthreads_or(over);
+  const int err = invalid ? DMS_ERR_INVALID : over ? DMS_ERR_CAPACITY : run > top0 ? DMS_ERR_OUT_OF_PAGES : DMS_OK;
   if (threadIdx.x == 0) {
-    if (err != 0) {
+    if (err != DMS_OK) {
       set_status(a.status_w, err);
-    } else if (run > top0) {
-      set_status(a.status_w, DMS_ERR_OUT_OF_PAGES);
     } else {
       *a.st.top = top0 - run;
-      a.err[1] = top0;
+      *a.top_before = top0;
     }
   }
-  __syncthreads();
   // positions and lengths advance here: pass 1 has read them, pass 3 uses pos0
   // and the fresh counts
-  if (err == 0 && run <= top0) {
+  if (err == DMS_OK) {
     for (int i = threadIdx.x; i < a.n; i += blockDim.x)
       a.st.pos[a.seq_ids[i]] = a.pos0[i] + (a.cu[i + 1] - a.cu[i]);
     for (int hh = threadIdx.x; hh < NH; hh += blockDim.x)
@@ -716,7 +712,7 @@ __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
   const int L0 = a.st.len[sh] - a.fresh[hh];
   const size_t pt_base = static_cast<size_t>(sh) * a.maxp;
   const int32_t* slots = a.slots + static_cast<size_t>(tok0) * a.H + h;   // fresh token c at c * H
-  const int32_t* popped = a.st.stack + a.err[1] - 1 - a.base[hh];         // k-th new page at -k
+  const int32_t* popped = a.st.stack + *a.top_before - 1 - a.base[hh];         // k-th new page at -k
   const int first_new_page = (L0 + a.P - 1) / a.P;
   if (blockIdx.x == 0)
     for (int k = threadIdx.x; k < a.need[hh]; k += blockDim.x) a.st.page_table[pt_base + first_new_page + k] = popped[-k];
@@ -811,7 +807,6 @@ hipError_t launch_init_state(const dms_config& c, const Layout& lo, void* meta, 
                              hipStream_t st) {
   InitArgs a;
   a.meta = static_cast<char*>(meta);
-  a.ck_err = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + lo.ws_ck_err);
   a.head_cnt = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + lo.ws_head_cnt);
   a.plan_ctr = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + lo.ws_plan_ctr);
   a.n_heads = static_cast<int64_t>(lo.max_heads) * lo.head_groups;
@@ -958,7 +953,7 @@ ChunkArgs chunk_args(const dms_config& c, const Layout& lo, void* meta, void* ws
   a.fresh = reinterpret_cast<int32_t*>(w + lo.ws_ck_fresh);
   a.base = reinterpret_cast<int32_t*>(w + lo.ws_ck_base);
   a.pos0 = reinterpret_cast<int32_t*>(w + lo.ws_ck_pos0);
-  a.err = reinterpret_cast<int32_t*>(w + lo.ws_ck_err);
+  a.top_before = reinterpret_cast<int32_t*>(w + lo.ws_ck_top);
   a.slots = reinterpret_cast<int32_t*>(w + lo.ws_ck_slot);
   a.n = n;
   a.H = c.num_kv_heads;

@@ -4,7 +4,7 @@ with more heads than waves.  Bookkeeping and stored rows are bit-exact."""
 import numpy as np
 import pytest
 
-from dms_testlib import SeqInputs, compare_pool, compare_state, to_dev
+from dms_testlib import SeqInputs, bf16_to_f32, compare_pool, compare_state, to_dev
 from test_decode_parity import _append_chunks, _mk, _oracle_for
 
 pytestmark = pytest.mark.gpu
@@ -73,4 +73,55 @@ def test_refused_prefill_leaves_no_error_behind():
     dms.dms_clear_status(cache.ctx)
     assert prefill([0, 20, 50], 50, 30) == 0
     assert cache.export(0).pos.tolist() == [20, 30]
+    cache.close()
+
+
+@pytest.mark.parametrize("left", [-5, -1, 0x7FFFFFFF])
+def test_chunk_calls_read_nothing_left_in_the_workspace(left):
+    """Whatever an interrupted call left in the scratch of the chunk passes (an error code among it), the
+    next append or prefill is planned from its own tokens alone."""
+    import torch
+    H, n, T = 2, 2, 40
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=n, num_kv_heads=H, group_size=1, head_dim=64, window=8,
+                               page_size=32, num_pages=16, max_pages_per_head=4, max_chunk_tokens=n * T))
+    orc = _oracle_for(cfg)
+    inputs = {s: SeqInputs(9, 0, s, 2 * T, H, 1, 64, 0.5) for s in range(n)}
+    cache.workspace.view(torch.int32).fill_(left)
+    _append_chunks(dms, cache, orc, [0, 1], inputs, {0: 0, 1: 0}, {0: T, 1: T}, T)
+    compare_state(cache.export(0), orc, [0, 1])
+    cache.workspace.view(torch.int32).fill_(left)
+    sid, cu = to_dev(np.arange(n, dtype=np.int32)), to_dev(np.array([0, T, 2 * T], np.int32))
+    x = [to_dev(np.concatenate([getattr(inputs[s], a)[T:] for s in range(n)])) for a in ("q", "k", "v", "flags")]
+    out = torch.full((n * T, H, 64), float("nan"), device="cuda")
+    dms.dms_prefill_chunk(cache.ctx, 0, n, sid, cu, n * T, T, *x, out)
+    assert dms.dms_status(cache.ctx) == 0 and bool(torch.isfinite(out).all())
+    orc.append_chunk([0, 1], [inputs[s].flags[T:] for s in range(n)],
+                     [bf16_to_f32(inputs[s].k[T:]) for s in range(n)], [bf16_to_f32(inputs[s].v[T:]) for s in range(n)])
+    compare_state(cache.export(0), orc, [0, 1])
+    cache.close()
+
+
+def test_refused_chunks_name_their_error():
+    """Boundaries that disagree, too many tokens for a head's pages and an empty pool, each refused with its
+    own error, nothing changed, and a valid call right after."""
+    import torch
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=2, num_kv_heads=1, group_size=1, head_dim=64, window=8,
+                               page_size=32, num_pages=3, max_pages_per_head=2, max_chunk_tokens=200))
+
+    def append(ids, cu):
+        x = torch.zeros((cu[-1], 1, 64), dtype=torch.bfloat16, device="cuda")
+        f = torch.zeros((cu[-1], 1), dtype=torch.uint8, device="cuda")
+        n = len(ids)
+        dms.dms_append_chunk(cache.ctx, 0, n, to_dev(np.array(ids, np.int32)), to_dev(np.array(cu, np.int32)),
+                             cu[-1], max(b - a for a, b in zip(cu, cu[1:])) if n < 2 or cu[1] != 70 else 60, x, x, f)
+        rc = dms.dms_status(cache.ctx)
+        dms.dms_clear_status(cache.ctx)
+        return rc
+
+    assert append([0, 1], [0, 70, 140]) == dms.DMS_ERR_INVALID    # longer than announced; also over capacity
+    assert append([0], [0, 65]) == dms.DMS_ERR_CAPACITY
+    assert append([0, 1], [0, 40, 80]) == dms.DMS_ERR_OUT_OF_PAGES
+    assert cache.export(0).pos.tolist() == [0, 0] and cache.export(0).top == 3
+    assert append([0, 1], [0, 40, 60]) == dms.DMS_OK
+    assert cache.export(0).pos.tolist() == [40, 20]
     cache.close()
