@@ -161,10 +161,37 @@ template <int D>
 struct Acc {
   f32x4 o[D / 16];
   float m, l;  // reference max (log2 units) and this lane's partial sum
+  float top;   // kTileMax: largest score so far
 };
 
+// New reference max of the next tile, whose largest score is mx; the sums so
+// far are rescaled to it.  kTileMax: the tile's own largest score (at most
+// kRescale below the largest so far), so that every tile's largest weight is
+// exactly 1 in bf16.  Launches that give a head few streams take it: with the
+// reference of a stream's first tile, 16 heads of 40 tiles were 1.52e-3 from
+// 64-bit sums with eleven streams a head and 1.46e-3 with sixteen; so they are
+// 1.14e-3, for 0.1 us of the 16 a step of two heads takes.  Otherwise the
+// reference is only raised, and rarely.
+template <int D, bool kTileMax>
+__device__ __forceinline__ void set_reference(Acc<D>& acc, float mx) {
+  float m_new, alpha;
+  if constexpr (kTileMax) {
+    acc.top = fmaxf(acc.top, mx);
+    m_new = fmaxf(mx, acc.top - kRescale);
+  } else {
+    const bool raise = mx > acc.m + kRescale;
+    if (!__builtin_amdgcn_ballot_w64(raise)) return;
+    m_new = raise ? mx : acc.m;
+  }
+  alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
+  acc.l *= alpha;
+#pragma unroll
+  for (int b = 0; b < D / 16; ++b) acc.o[b] *= alpha;
+  acc.m = m_new;
+}
+
 // Scores, online softmax and PV accumulation for one tile; `valid` live tokens.
-template <int D>
+template <int D, bool kTileMax = false>
 __device__ inline void compute_tile(Acc<D>& acc, const Frag<D>& f, const u32x4* qf, float scale,
                                     int valid, int G) {
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -188,15 +215,7 @@ __device__ inline void compute_tile(Acc<D>& acc, const Frag<D>& f, const u32x4* 
                    fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  const bool raise = mx > acc.m + kRescale;
-  if (__builtin_amdgcn_ballot_w64(raise)) {
-    const float m_new = raise ? mx : acc.m;
-    const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-    acc.l *= alpha;
-#pragma unroll
-    for (int b = 0; b < D / 16; ++b) acc.o[b] *= alpha;
-    acc.m = m_new;
-  }
+  set_reference<D, kTileMax>(acc, mx);
   bf16x8 p;
   float psum = 0.f;
 #pragma unroll
@@ -284,7 +303,7 @@ __device__ inline u32x4 f8_to_bf16x8(uint32_t w0, uint32_t w1) {
   return a;
 }
 
-template <int D>
+template <int D, bool kTileMax = false>
 __device__ inline void compute_tile_f8(Acc<D>& acc, const FragF8<D>& f, const u32x4* qf, float scale,
                                        int valid, int G) {
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -311,15 +330,7 @@ __device__ inline void compute_tile_f8(Acc<D>& acc, const FragF8<D>& f, const u3
                    fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  const bool raise = mx > acc.m + kRescale;
-  if (__builtin_amdgcn_ballot_w64(raise)) {
-    const float m_new = raise ? mx : acc.m;
-    const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-    acc.l *= alpha;
-#pragma unroll
-    for (int b = 0; b < D / 16; ++b) acc.o[b] *= alpha;
-    acc.m = m_new;
-  }
+  set_reference<D, kTileMax>(acc, mx);
   bf16x8 p;
   float psum = 0.f;
 #pragma unroll
@@ -668,7 +679,7 @@ struct LdsPlan {
 // appended token written into its tile by the wave whose range covers it
 // (before the range's loads: same-wave stores and loads to one address stay
 // in order), then the tiles, two register sets in flight.
-template <int D, bool FP8>
+template <int D, bool FP8, bool kTileMax = false>
 __device__ __forceinline__ void stream_segment(
   Acc<D>& acc, int hh, const HeadDesc& d, int t_lo, int t_hi, bool head_end,
   const int32_t* __restrict__ page_table, const int32_t* __restrict__ qpage, char* __restrict__ pool,
@@ -692,7 +703,7 @@ __device__ __forceinline__ void stream_segment(
   if (a.zero_neuron && r == 0 && G == 0) qf[0][0] &= 0xFFFF0000u;
 #pragma unroll
   for (int b = 0; b < D / 16; ++b) acc.o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  acc.m = -INFINITY;
+  acc.m = acc.top = -INFINITY;
   acc.l = 0.f;
   const int full_hi = (head_end && (L & (kTile - 1))) ? t_hi - 1 : t_hi;
   // tile t of the head: page from a scalar load (the whole wave works on
@@ -745,25 +756,25 @@ __device__ __forceinline__ void stream_segment(
         load_tile_f8<D>(fb, pb, lane, G);
         __builtin_amdgcn_sched_barrier(0);
         const char* pa = tile_of(t + 2);
-        compute_tile_f8<D>(acc, fa, qf, a.scale_log2, kTile, G);
+        compute_tile_f8<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
         load_tile_f8<D>(fa, pa, lane, G);
         __builtin_amdgcn_sched_barrier(0);
         pb = tile_of(min(t + 3, last));
-        compute_tile_f8<D>(acc, fb, qf, a.scale_log2, kTile, G);
+        compute_tile_f8<D, kTileMax>(acc, fb, qf, a.scale_log2, kTile, G);
       }
       if (t + 1 < full_hi) {
         load_tile_f8<D>(fb, pb, lane, G);
         __builtin_amdgcn_sched_barrier(0);
-        compute_tile_f8<D>(acc, fa, qf, a.scale_log2, kTile, G);
-        compute_tile_f8<D>(acc, fb, qf, a.scale_log2, kTile, G);
+        compute_tile_f8<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
+        compute_tile_f8<D, kTileMax>(acc, fb, qf, a.scale_log2, kTile, G);
       } else {
-        compute_tile_f8<D>(acc, fa, qf, a.scale_log2, kTile, G);
+        compute_tile_f8<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
       }
     }
     if (full_hi < t_hi) {
       FragF8<D> ft;
       load_tail_f8<D>(ft, tile_of(full_hi), lane, L - full_hi * kTile, r, G);
-      compute_tile_f8<D>(acc, ft, qf, a.scale_log2, L - full_hi * kTile, G);
+      compute_tile_f8<D, kTileMax>(acc, ft, qf, a.scale_log2, L - full_hi * kTile, G);
     }
   } else {
   if (t_lo < full_hi) {
@@ -775,22 +786,22 @@ __device__ __forceinline__ void stream_segment(
     load_tile<D>(fa, tile_of(t), lane);
     for (; t + 2 < full_hi; t += 2) {
       load_tile<D>(fb, tile_of(t + 1), lane);
-      compute_tile<D>(acc, fa, qf, a.scale_log2, kTile, G);
+      compute_tile<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
       load_tile<D>(fa, tile_of(t + 2), lane);
-      compute_tile<D>(acc, fb, qf, a.scale_log2, kTile, G);
+      compute_tile<D, kTileMax>(acc, fb, qf, a.scale_log2, kTile, G);
     }
     if (t + 1 < full_hi) {
       load_tile<D>(fb, tile_of(t + 1), lane);
-      compute_tile<D>(acc, fa, qf, a.scale_log2, kTile, G);
-      compute_tile<D>(acc, fb, qf, a.scale_log2, kTile, G);
+      compute_tile<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
+      compute_tile<D, kTileMax>(acc, fb, qf, a.scale_log2, kTile, G);
     } else {
-      compute_tile<D>(acc, fa, qf, a.scale_log2, kTile, G);
+      compute_tile<D, kTileMax>(acc, fa, qf, a.scale_log2, kTile, G);
     }
   }
   if (full_hi < t_hi) {
     Frag<D> ft;
     load_tail<D>(ft, tile_of(full_hi), lane, L - full_hi * kTile, r, G);
-    compute_tile<D>(acc, ft, qf, a.scale_log2, L - full_hi * kTile, G);
+    compute_tile<D, kTileMax>(acc, ft, qf, a.scale_log2, L - full_hi * kTile, G);
   }
   }
 }
@@ -1126,7 +1137,7 @@ __device__ __forceinline__ void decode_head_block(const LdsPlan& plan, int hh, i
   const int t_hi = p_lo + (wid + 1) * (p_hi - p_lo) / kWavesPerBlock;
   Acc<D> acc;
   if (t_lo < t_hi) {
-    stream_segment<D, FP8>(acc, hh, d, t_lo, t_hi, t_hi == n, page_table, nullptr, pool, q, k_in, v_in, a);
+    stream_segment<D, FP8, true>(acc, hh, d, t_lo, t_hi, t_hi == n, page_table, nullptr, pool, q, k_in, v_in, a);
   } else {
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc.o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1492,13 +1503,13 @@ __global__ __launch_bounds__(64 * kShortWaves, 1) void decode_short_kernel(
     Acc<D> acc;
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc.o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    acc.m = -INFINITY;
+    acc.m = acc.top = -INFINITY;
     acc.l = 0.f;
     auto compute = [&](Tile& t, int at) {
       const int valid = Lnew - at * kTile;
       if (valid < kTile) mask_tail<D>(t, valid, G);
-      if constexpr (FP8) compute_tile_f8<D>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
-      else compute_tile<D>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
+      if constexpr (FP8) compute_tile_f8<D, true>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
+      else compute_tile<D, true>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
     };
     for (int t = t_lo; t < t_hi; ++t) {
       if (t > t_lo) load(fa, tile_of(t));

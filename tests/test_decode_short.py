@@ -54,3 +54,41 @@ def test_refused_step_changes_nothing(pages, maxp, err):
     assert dms.dms_status(cache.ctx) == dms.DMS_ERR_BAD_SEQ
     assert bool((out == 7.0).all())
     cache.close()
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("H,g,D,L,maxp", [
+    (2, 6, 128, 1270, 32), (8, 5, 128, 2000, 32),     # one workgroup of eleven streams per head
+    (2, 6, 128, 370, 64), (4, 7, 64, 250, 64),        # longer page tables: one workgroup of four
+    (2, 6, 128, 1270, 64)])                           # four workgroups per head
+def test_step_is_as_precise_as_one_wave_per_tile(H, g, D, L, maxp, fp8):
+    """The weights are rounded to bf16 against a reference; a head's tiles on waves of their own (dms_decode
+    over many waves: each tile's largest weight is exactly 1) are as near to 64-bit sums as it gets.  A step
+    that walks several tiles a wave must not be further off."""
+    import torch
+    from paper_2506_05345_amd import dms
+    n, w = 8, 1
+    cfg = dms.make_config(1, n, H, g, D, w, 64, n * H * (-(-(L + 1) // 64)), maxp, n * L,
+                          kv_format=dms.DMS_KV_FP8 if fp8 else dms.DMS_KV_BF16)
+    gen = torch.Generator("cuda").manual_seed(17)
+    k, v = (torch.randn((n, L + 1, H, D), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn((n, H * g, D), generator=gen, device="cuda").bfloat16()
+    if fp8:   # rows that FP8 pages hold exactly
+        k, v = (torch.cat([x.float().clamp(-1.75, 1.75).mul(4).round().div(4)[..., :-1],
+                           torch.full_like(x[..., :1], 1.75).float()], -1).bfloat16() for x in (k, v))
+    cache = dms.DmsCache(cfg)
+    sid = torch.arange(n, dtype=torch.int32, device="cuda")
+    cu = (torch.arange(n + 1, device="cuda") * L).to(torch.int32)
+    z = lambda *s: torch.zeros(s, dtype=torch.uint8, device="cuda")  # noqa: E731
+    dms.dms_append_chunk(cache.ctx, 0, n, sid, cu, n * L, L, k[:, :L].reshape(n * L, H, D),
+                         v[:, :L].reshape(n * L, H, D), z(n * L, H))
+    out = [torch.empty((n, H * g, D), device="cuda") for _ in range(2)]
+    dms.dms_decode_step(cache.ctx, 0, n, sid, q, k[:, L].contiguous(), v[:, L].contiguous(), z(n, H), out[0])
+    dms.dms_decode(cache.ctx, 0, n, sid, q, out[1])
+    assert dms.dms_status(cache.ctx) == 0
+    s = torch.einsum("nhgd,nthd->nhgt", q.double().view(n, H, g, D), k.double()) / D ** 0.5
+    ref = torch.einsum("nhgt,nthd->nhgd", s.softmax(-1), v.double()).reshape(n, H * g, D)
+    err = [float((o.double() - ref).norm() / ref.norm()) for o in out]
+    print(err)
+    assert err[0] <= 1.01 * err[1], err
+    cache.close()
