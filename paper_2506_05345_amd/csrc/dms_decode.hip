@@ -1249,14 +1249,14 @@ __global__ __launch_bounds__(256, 1) void decode_step_kernel(
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = gridDim.x;
   const int T = __builtin_amdgcn_readfirstlane(total);
-  // every workgroup takes the same decision from the same plan
-  int wide = 0, split = 0;
-  for (int hh = threadIdx.x; hh < a.NH; hh += blockDim.x) {
+  // every wave takes the same decision from the same plan
+  bool wide = false, split = false;
+  for (int hh = threadIdx.x & 63; hh < a.NH; hh += 64) {
     wide |= s_cum[hh + 1] - s_cum[hh] > kHeadBlockTiles;
     split |= s_cum[hh + 1] - s_cum[hh] > kWholeHeadTiles;
   }
-  wide = __syncthreads_or(wide);
-  split = __syncthreads_or(split);
+  wide = __builtin_amdgcn_ballot_w64(wide) != 0;
+  split = __builtin_amdgcn_ballot_w64(split) != 0;
   if (!wide && a.NH <= nb) {
     const int S = split ? min(kHeadBlockParts, nb / a.NH) : 1;
     if (static_cast<int>(blockIdx.x) < a.NH * S)
