@@ -4,7 +4,7 @@ chunk commits against the CPU oracle: bookkeeping bit-exact, outputs within
 import numpy as np
 import pytest
 
-from dms_testlib import ATOL, SeqInputs, bf16_to_f32, compare_pool, compare_state, to_dev
+from dms_testlib import ATOL, SeqInputs, bf16_to_f32, compare_pool, compare_pool_fp8, compare_state, to_dev
 from oracle import PagedKVOracle, dense_dms_attention
 
 pytestmark = pytest.mark.gpu
@@ -171,27 +171,62 @@ def test_many_heads_multi_pass_planner():
     cache.close()
 
 
+@pytest.mark.parametrize("fmt", ["bf16", "fp8"])
+@pytest.mark.parametrize("maxp", [64, 72])
 @pytest.mark.parametrize("nseq", [3, 20, 25])
-def test_short_heads_split_over_workgroups(nseq):
-    """Small calls whose heads all fit one workgroup's share: 12, 80 and 100
-    call heads are split over 4, 3 and 2 workgroups per head (one folded
-    partial each, merged by the last); heads of 1-3 tiles leave parts without
-    tiles."""
+def test_short_heads_split_over_workgroups(nseq, maxp, fmt):
+    """Small calls whose heads all fit one workgroup's share.  With page tables
+    of 72 entries (2304 slots) and one sequence of more than 32 tiles, 12, 80
+    and 100 call heads are split over 4, 3 and 2 workgroups per head (one
+    folded partial each, merged by the last), and heads of 1-3 tiles leave
+    parts without tiles; tables of 64 entries (2048 slots) take the launch
+    with one workgroup per head."""
+    import test_fp8_parity as fp8
     H, g, d, w, P = 4, 2, 64, 16, 32
     rng = np.random.default_rng(90 + nseq)
     seqs = [int(s) for s in rng.permutation(nseq)]
     lens = {s: int(rng.integers(1, 600)) for s in seqs}
     for s in seqs[:3]:
         lens[s] = int(rng.integers(1, 90))   # one to three tiles
-    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=nseq, num_kv_heads=H, group_size=g,
-                               head_dim=d, window=w, page_size=P, num_pages=4000,
-                               max_pages_per_head=64, max_chunk_tokens=nseq * 600))
-    inp = {s: SeqInputs(91, 0, s, lens[s] + 8, H, g, d, 0.7) for s in seqs}
-    orc = _oracle_for(cfg)
-    _append_chunks(dms, cache, orc, seqs, inp, {s: 0 for s in seqs}, lens, 600)
+    if maxp == 72:
+        lens[seqs[-1]] = 1300                # with few evictions: more than 32 tiles
+    kw = dict(num_layers=1, max_seqs=nseq, num_kv_heads=H, group_size=g, head_dim=d, window=w, page_size=P,
+              num_pages=4000, max_pages_per_head=maxp, max_chunk_tokens=nseq * 600)
+    if fmt == "fp8":
+        dms, cfg, cache, orc = fp8._mk(**kw)
+        append, steps, pool = fp8._append_chunks, fp8._decode_steps, lambda: compare_pool_fp8(cache, orc, seqs)
+    else:
+        dms, cfg, cache = _mk(kw)
+        orc = _oracle_for(cfg)
+        append, pool = _append_chunks, lambda: compare_pool(cache, 0, cache.export(0), seqs, inp)
+        steps = lambda *a: _decode_steps(*a, check_every=3, dense_check=False)   # noqa: E731
+    inp = {s: SeqInputs(91, 0, s, lens[s] + 8, H, g, d, 0.1 if lens[s] == 1300 else 0.7) for s in seqs}
+    append(dms, cache, orc, seqs, inp, {s: 0 for s in seqs}, lens, 600)
     compare_state(cache.export(0), orc, seqs)
-    _decode_steps(dms, cache, orc, seqs, inp, lens, 8, g, check_every=3, dense_check=False)
-    compare_pool(cache, 0, cache.export(0), seqs, inp)
+    if maxp == 72:
+        assert 1024 < cache.export(0).L.max() <= 2048
+    steps(dms, cache, orc, seqs, inp, lens, 8, g)
+    compare_state(cache.export(0), orc, seqs)
+    pool()
+    cache.close()
+
+
+@pytest.mark.parametrize("H,g,d,start", [(2, 6, 128, 1021), (64, 2, 64, 1021), (2, 4, 64, 381)])
+def test_step_that_makes_a_head_long_enough_to_split(H, g, d, start):
+    """Heads that grow from 32 to 33 tiles (and from 12 to 13, where nothing
+    changes) during the steps: from one to several workgroups per head between
+    two calls, in a workspace of NaN bytes; the other sequence stays short."""
+    torch = _torch()
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=2, num_kv_heads=H, group_size=g, head_dim=d, window=4,
+                               page_size=64, num_pages=H * 40, max_pages_per_head=34, max_chunk_tokens=2 * 1100))
+    cache.workspace.fill_(0xFF)
+    dms.dms_init_state(cache.ctx)
+    torch.cuda.synchronize()
+    seqs, lens = [1, 0], {0: start, 1: 45}
+    inp = {s: SeqInputs(92, 0, s, lens[s] + 6, H, g, d, 0.0) for s in seqs}
+    orc = _oracle_for(cfg)
+    _append_chunks(dms, cache, orc, seqs, inp, {s: 0 for s in seqs}, lens, 1100)
+    _decode_steps(dms, cache, orc, seqs, inp, lens, 6, g, dense_check=False)
     cache.close()
 
 
@@ -242,11 +277,12 @@ def test_value_variants(variant):
             assert np.abs(o[0, 0] - 2.0).max() < 1e-2  # the kept needle, nothing of -2
 
 
-def test_out_of_pages_is_sticky_and_changes_nothing():
+@pytest.mark.parametrize("maxp", [8, 66])   # the step's launch for short page tables and the one for longer ones
+def test_out_of_pages_is_sticky_and_changes_nothing(maxp):
     torch = _torch()
     dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=2, num_kv_heads=2, group_size=2,
                                head_dim=64, window=4, page_size=32, num_pages=5,
-                               max_pages_per_head=8, max_chunk_tokens=256))
+                               max_pages_per_head=maxp, max_chunk_tokens=256))
     inp = {s: SeqInputs(3, 0, s, 200, 2, 2, 64, 0.0) for s in (0, 1)}
     orc = _oracle_for(cfg)
     # 60 kept tokens: 2 pages per head, slots 60..63 still free in the last page

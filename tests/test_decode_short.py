@@ -5,7 +5,7 @@ outputs within the decode tolerance (tests/dms_testlib.py)."""
 import numpy as np
 import pytest
 
-from dms_testlib import SeqInputs, bf16_to_f32, to_dev
+from dms_testlib import SeqInputs, compare_state, to_dev
 from test_decode_parity import _append_chunks, _decode_steps, _mk, _oracle_for
 
 pytestmark = pytest.mark.gpu
@@ -31,28 +31,32 @@ def test_steps(D, P, g, w, H, starts, p):
     cache.close()
 
 
-@pytest.mark.parametrize("pages,maxp,err", [(1, 4, "DMS_ERR_OUT_OF_PAGES"), (8, 1, "DMS_ERR_CAPACITY")])
-def test_refused_step_changes_nothing(pages, maxp, err):
+@pytest.mark.parametrize("P,L,pages,maxp,err", [
+    (32, 32, 1, 4, "DMS_ERR_OUT_OF_PAGES"), (32, 32, 8, 1, "DMS_ERR_CAPACITY"),
+    # longer page tables: the launch that plans in every workgroup
+    (32, 32, 1, 65, "DMS_ERR_OUT_OF_PAGES"), (256, 2304, 10, 9, "DMS_ERR_CAPACITY")])
+def test_refused_step_changes_nothing(P, L, pages, maxp, err):
     import torch
-    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=1, num_kv_heads=1, group_size=2, head_dim=64, window=64,
-                               page_size=32, num_pages=pages, max_pages_per_head=maxp, max_chunk_tokens=32))
+    dms, cfg, cache = _mk(dict(num_layers=1, max_seqs=2, num_kv_heads=1, group_size=2, head_dim=64, window=64,
+                               page_size=P, num_pages=pages, max_pages_per_head=maxp, max_chunk_tokens=L))
     orc = _oracle_for(cfg)
-    inputs = {0: SeqInputs(12, 0, 0, 33, 1, 2, 64, 0.0)}
-    _append_chunks(dms, cache, orc, [0], inputs, {0: 0}, {0: 32}, 32)
+    inputs = {0: SeqInputs(12, 0, 0, L + 1, 1, 2, 64, 0.0)}
+    _append_chunks(dms, cache, orc, [0], inputs, {0: 0}, {0: L}, L)
     x = inputs[0]
-    sid = to_dev(np.zeros(1, np.int32))
-    out = torch.full((1, 2, 64), 7.0, device="cuda")
-    args = (to_dev(x.q[32][None]), to_dev(x.k[32][None]), to_dev(x.v[32][None]), to_dev(x.flags[32][None]), out)
+    out = torch.full((2, 2, 64), 7.0, device="cuda")
+
+    def step(*ids):
+        rep = [np.repeat(a[L][None], len(ids), 0) for a in (x.q, x.k, x.v, x.flags)]
+        dms.dms_decode_step(cache.ctx, 0, len(ids), to_dev(np.array(ids, np.int32)), *map(to_dev, rep), out[:len(ids)])
+        return dms.dms_status(cache.ctx)
+
     for _ in range(2):   # the second call finds the sticky status
-        dms.dms_decode_step(cache.ctx, 0, 1, sid, *args)
-        assert dms.dms_status(cache.ctx) == getattr(dms, err)
+        assert step(0) == getattr(dms, err)
+    for ids in ((5,), (-1,), (1, 1), (0, 2)):
+        dms.dms_clear_status(cache.ctx)
+        assert step(*ids) == dms.DMS_ERR_BAD_SEQ
     assert bool((out == 7.0).all())
-    view = cache.export(0)
-    assert view.pos[0] == 32 and view.L[0, 0] == 32
-    dms.dms_clear_status(cache.ctx)
-    dms.dms_decode_step(cache.ctx, 0, 1, to_dev(np.full(1, 5, np.int32)), *args)
-    assert dms.dms_status(cache.ctx) == dms.DMS_ERR_BAD_SEQ
-    assert bool((out == 7.0).all())
+    compare_state(cache.export(0), orc, [0, 1])
     cache.close()
 
 
