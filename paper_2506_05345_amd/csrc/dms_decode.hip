@@ -1109,12 +1109,17 @@ __device__ __forceinline__ void write_state(const FusedArgs& f, const int4* s_de
 // of the S merges them (at most four partials, one coherent round trip).
 constexpr int kHeadBlockTiles = 64;
 constexpr int kHeadBlockParts = 4;
-// Heads of at most this many tiles are not split: at 2 heads of 10 tiles the
-// launch took 14.3 us with S = 4 (publishing, counting and merging the parts
-// is three more dependent round trips) and 11 us with S = 1; at 2 or 64 heads
-// of 40 tiles S = 4 is still the faster (20.2 and 25.5 us against 22.3 and
-// 26.8).
-constexpr int kWholeHeadTiles = 12;
+// Heads of at most this many tiles are not split: publishing, counting and
+// merging the parts is three more dependent round trips, about as long as four
+// waves take for 32 tiles.  Measured on calls that reach this launch (page
+// tables of more than 2048 slots), us with S = 1 / S = 4 (2 at 128 heads):
+//                         8 tiles      24 tiles     32 tiles     40 tiles
+//   2 x 6 heads, d 128    12.4 / 17.1  13.1 / 17.8  14.5 / 18.2  15.2 / 18.6
+//   32 heads              13.8 / 18.9  17.3 / 19.9  19.8 / 21.7  22.9 / 22.1
+//   64 heads              13.7 / 19.2  18.8 / 20.9  21.2 / 21.9  23.8 / 23.4
+//   128 heads             16.1 / 20.8  20.7 / 24.1  23.5 / 26.7  26.1 / 28.9
+//   64 heads of FP8       13.6 / 19.8  17.1 / 20.9  18.8 / 21.5  20.7 / 22.2
+constexpr int kWholeHeadTiles = 32;
 
 template <int D, bool FP8>
 __device__ __forceinline__ void decode_head_block(const LdsPlan& plan, int hh, int S, int s,
