@@ -176,10 +176,11 @@ __device__ inline void tile_to_lds(const char* src, char* dst, int v, int lane, 
 }
 
 // Wait until this V wave's loads of the tile about to be computed have
-// landed, `ahead` later tiles (0 .. 2) still in flight behind them.
-__device__ inline void wait_tile(int ahead) {
-  if (ahead >= 2) __builtin_amdgcn_s_waitcnt(wait_vm(2 * kLoadsPerWave));
-  else if (ahead == 1) __builtin_amdgcn_s_waitcnt(wait_vm(kLoadsPerWave));
+// landed; `ahead`: whether a later tile's loads are in flight behind them
+// (at most one tile's are), which stay so.
+static_assert(kNBuf == 4, "two tiles ahead of the one being scored, one behind it");
+__device__ inline void wait_tile(bool ahead) {
+  if (ahead) __builtin_amdgcn_s_waitcnt(wait_vm(kLoadsPerWave));
   else __builtin_amdgcn_s_waitcnt(wait_vm(0));
 }
 
@@ -281,7 +282,7 @@ __device__ __forceinline__ void run_role(Smem& S, const MlaPtrs& P, const MlaPar
     for (int i = 0; i <= n; ++i) {
       const int t = t_lo + i;
       // i == 0: the token row was loaded before the tiles
-      if constexpr (!kScore) wait_tile(i == 0 ? 0 : min(kNBuf - 3, n - 1 - i));
+      if constexpr (!kScore) wait_tile(i > 0 && i + 1 < n);
       __syncthreads();   // tile i is in LDS, tile i - 1's probabilities too; every wave is done with tile i - 2
       if constexpr (!kScore) {
         if (i > 0 && i + kNBuf - 2 < n)

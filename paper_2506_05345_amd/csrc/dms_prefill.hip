@@ -478,7 +478,7 @@ __global__ __launch_bounds__((attn_threads<D, FP8>()), (512 / attn_threads<D, FP
              static_cast<size_t>((sb & (a.P - 1)) >> 5) * kTB;
       if (tid < 32) {
         uint32_t mt = sb + tid < L0 ? static_cast<uint32_t>(smeta[sb + tid]) : kNoKey;
-        if (a.immediate && mt != kNoKey) {
+        if (mt != kNoKey) {
           // a cached key j is hidden by the decision of position j + w, which
           // (for a live key) lies in this chunk or later
           const int kp = static_cast<int>(mt & ~kFlagBit);
@@ -1442,7 +1442,7 @@ __global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_kernel(PrefillArgs
              static_cast<size_t>((sb & (a.P - 1)) >> 5) * kMlaTileBytes;
       if (tid < 32) {
         uint32_t mt = sb + tid < L0 ? static_cast<uint32_t>(smeta[sb + tid]) : kNoKey;
-        if (a.immediate && mt != kNoKey) {
+        if (mt != kNoKey) {
           const int kp = static_cast<int>(mt & ~kFlagBit);
           const int x = kp + a.w - p0;
           mt = static_cast<uint32_t>(kp) |

@@ -317,9 +317,9 @@ __global__ __launch_bounds__(kThreads) void train_bias_kernel(TrainArgs a, bool 
 // Mask class of keys [j0, j1) for queries [q0, q1): 0 = every key older
 // than every query's window (bias log(1 - alpha)), 1 = every key inside every
 // query's window and not after any query (no bias), 2 = per element.
-__device__ inline int mask_class(int j0, int j1, int q0, int q1, int w, int T) {
+__device__ inline int mask_class(int j0, int j1, int q0, int q1, int w) {
   if (j1 - 1 <= q0 - w) return 0;
-  if (j0 > q1 - 1 - w && j1 - 1 <= q0 && q1 <= T) return 1;
+  if (j0 > q1 - 1 - w && j1 - 1 <= q0) return 1;
   return 2;
 }
 
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_fwd_kernel(TrainArgs a) {
     // tiles' products (a second tile past the last is hidden: every key is after t)
     constexpr int tl = buf * kStage;
     const int jt = 64 * st;
-    const int c0 = mask_class(jt, jt + 32, t0, t1, a.w, a.T), c1 = mask_class(jt + 32, jt + 64, t0, t1, a.w, a.T);
+    const int c0 = mask_class(jt, jt + 32, t0, t1, a.w), c1 = mask_class(jt + 32, jt + 64, t0, t1, a.w);
     f32x16 s[2] = {score_start(&bias_lds[buf][0], zero_lds, c0, hf), score_start(&bias_lds[buf][32], zero_lds, c1, hf)};
     u32x4 op[kAhead];
     // score product e: tile e % 2, k-step e / 2 (the two chains take turns)
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
       const int jt = 64 * st + 32 * sub;
       constexpr int t_buf = buf * kStage;
       const int tl = t_buf + 2 * kUnit * sub;
-      const int cls = mask_class(jt, jt + 32, t0, t1, a.w, a.T);
+      const int cls = mask_class(jt, jt + 32, t0, t1, a.w);
       f32x16 s = score_start(&bias_lds[buf][32 * sub], zero_lds, cls, hf), dp;
       u32x4 op[kAhead];
       // product e: scores (keys) and dP (values) take turns, k-step e / 2
