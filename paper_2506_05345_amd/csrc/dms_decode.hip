@@ -119,15 +119,23 @@ struct Frag {
 // fragment order (see dms_common.h), so load instruction i of the wave reads
 // the contiguous 1 KB block i and lane l takes bytes 16 l .. 16 l + 15.
 template <int D>
-__device__ inline void load_tile(Frag<D>& f, const char* tile, int lane) {
+__device__ inline void load_keys(Frag<D>& f, const char* tile, int lane, int) {
   const char* p = tile + lane * 16;
 #pragma unroll
   for (int s = 0; s < D / 32; ++s) {
     f.ka[s] = ldkv(p + s * 2048);
     f.kb[s] = ldkv(p + s * 2048 + 1024);
   }
+}
+template <int D>
+__device__ inline void load_values(Frag<D>& f, const char* tile, int lane, int) {
 #pragma unroll
-  for (int b = 0; b < D / 16; ++b) f.vt[b] = ldkv(p + D * 64 + b * 1024);
+  for (int b = 0; b < D / 16; ++b) f.vt[b] = ldkv(tile + lane * 16 + D * 64 + b * 1024);
+}
+template <int D>
+__device__ inline void load_tile(Frag<D>& f, const char* tile, int lane) {
+  load_keys<D>(f, tile, lane, 0);
+  load_values<D>(f, tile, lane, 0);
 }
 
 // Last, partial tile of a head: rows at or past L are not read and the value
@@ -190,16 +198,22 @@ __device__ __forceinline__ void set_reference(Acc<D>& acc, float mx) {
   acc.m = m_new;
 }
 
+struct Nothing {
+  __device__ void operator()() const {}
+};
+
 // Scores, online softmax and PV accumulation for one tile; `valid` live tokens.
-template <int D, bool kTileMax = false>
+// keys_done(): called once the tile's keys have been read.
+template <int D, bool kTileMax = false, class KeysDone = Nothing>
 __device__ inline void compute_tile(Acc<D>& acc, const Frag<D>& f, const u32x4* qf, float scale,
-                                    int valid, int G) {
+                                    int valid, int G, KeysDone keys_done = {}) {
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < D / 32; ++s) {
     s0 = mfma_bf16(f.ka[s], qf[s], s0);
     s1 = mfma_bf16(f.kb[s], qf[s], s1);
   }
+  keys_done();
   float sc[8];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -246,6 +260,23 @@ struct FragF8 {
   u32x4 s[4];          // key scales (s[0], s[1]) and value scales (s[2], s[3]) of slots 8G ..
 };
 
+template <int D>
+__device__ inline void load_keys(FragF8<D>& f, const char* tile, int lane, int G) {
+#pragma unroll
+  for (int p = 0; p < D / 64; ++p) {
+    f.k[p][0] = ldkv(tile + p * 2048 + lane * 16);
+    f.k[p][1] = ldkv(tile + p * 2048 + 1024 + lane * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) f.s[i] = ldkv(tile + D * 64 + G * 64 + i * 16);
+}
+template <int D>
+__device__ inline void load_values(FragF8<D>& f, const char* tile, int lane, int G) {
+#pragma unroll
+  for (int p = 0; p < D / 32; ++p) f.v[p] = ldkv(tile + D * 32 + p * 1024 + lane * 16);
+#pragma unroll
+  for (int i = 2; i < 4; ++i) f.s[i] = ldkv(tile + D * 64 + G * 64 + i * 16);
+}
 template <int D>
 __device__ inline void load_tile_f8(FragF8<D>& f, const char* tile, int lane, int G) {
 #pragma unroll
@@ -303,9 +334,9 @@ __device__ inline u32x4 f8_to_bf16x8(uint32_t w0, uint32_t w1) {
   return a;
 }
 
-template <int D, bool kTileMax = false>
+template <int D, bool kTileMax = false, class KeysDone = Nothing>
 __device__ inline void compute_tile_f8(Acc<D>& acc, const FragF8<D>& f, const u32x4* qf, float scale,
-                                       int valid, int G) {
+                                       int valid, int G, KeysDone keys_done = {}) {
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int p = 0; p < D / 64; ++p) {
@@ -321,6 +352,7 @@ __device__ inline void compute_tile_f8(Acc<D>& acc, const FragF8<D>& f, const u3
     sc[i] = s0[i] * (scale * __uint_as_float(f.s[0][i]));
     sc[4 + i] = s1[i] * (scale * __uint_as_float(f.s[1][i]));
   }
+  keys_done();
   if (valid < kTile) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
@@ -1291,10 +1323,16 @@ __global__ __launch_bounds__(256, 1) void decode_step_kernel(
 // head).  They meet once before anything is written.  The eleven results fold
 // through LDS, so nothing is merged through memory.  Taken where a head's
 // page table bounds its tiles by kShortTiles, since only the host's capacity
-// is known at launch, and the call has at most kShortHeads heads (one
-// workgroup per CU).  Measured against the launch above: 2 heads of 10 tiles
-// 14.4 -> 6.6 us, 2 heads of 40 tiles 20.2 -> 16.0 us, 64 heads of 40 tiles
-// 25.5 -> 18.6 us.  Eight waves with two tiles in flight each ran 6.7, 16.2
+// is known at launch (a cache whose page tables are sized for longer heads
+// than it holds takes the other launches), and the call has at most
+// kShortHeads heads (one workgroup per CU).  Measured, layers in turn,
+// against the launch above: 2 heads of 10 tiles 17.8 -> 7.5 us, of 41 tiles
+// 19.8 -> 16.8, of 56 tiles 21.2 both (FP8 20.3 -> 16.8); 64 heads of 41 tiles
+// 26.2 -> 19.3; and against the planned launches 256 heads of 22 tiles 34.6 ->
+// 24.2, of 56 tiles 57 -> 46.5.  Each tile's keys and values are loaded as
+// soon as the products of the tile before have read theirs: loading a whole
+// tile after the whole of the one before left 2 heads of 53 and 56 tiles 3 and
+// 5 % slower than the launch above (64 heads of 56 FP8 tiles: 20.0 -> 18.8).  Eight waves with two tiles in flight each ran 6.7, 16.2
 // and 19.0 us, sixteen waves 25 us for 40 tiles (128 registers each: the
 // stream spills).
 // ---------------------------------------------------------------------------
@@ -1510,15 +1548,19 @@ __global__ __launch_bounds__(64 * kShortWaves, 1) void decode_short_kernel(
     for (int b = 0; b < D / 16; ++b) acc.o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     acc.m = acc.top = -INFINITY;
     acc.l = 0.f;
-    auto compute = [&](Tile& t, int at) {
-      const int valid = Lnew - at * kTile;
-      if (valid < kTile) mask_tail<D>(t, valid, G);
-      if constexpr (FP8) compute_tile_f8<D, true>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
-      else compute_tile<D, true>(acc, t, qf, a.scale_log2, min(valid, kTile), G);
-    };
+    // the next tile's keys and values are loaded into the registers of this
+    // one's as soon as its products have read them
     for (int t = t_lo; t < t_hi; ++t) {
-      if (t > t_lo) load(fa, tile_of(t));
-      compute(fa, t);
+      const bool more = t + 1 < t_hi;
+      const char* next = tile_of(more ? t + 1 : t);
+      const int valid = Lnew - t * kTile;
+      if (valid < kTile) mask_tail<D>(fa, valid, G);   // the head's last tile
+      auto keys_done = [&] {
+        if (more) load_keys<D>(fa, next, lane, G);
+      };
+      if constexpr (FP8) compute_tile_f8<D, true>(acc, fa, qf, a.scale_log2, min(valid, kTile), G, keys_done);
+      else compute_tile<D, true>(acc, fa, qf, a.scale_log2, min(valid, kTile), G, keys_done);
+      if (more) load_values<D>(fa, next, lane, G);
     }
     float l = acc.l;
     l += __shfl_xor(l, 16, 64);
