@@ -99,7 +99,7 @@ struct ResetArgs {
 
 __global__ __launch_bounds__(kPlanThreads) void seq_reset_kernel(ResetArgs a) {
   __shared__ uint32_t seen[kMaxSeqs / 32];
-  __shared__ int2 head_pages[kPlanThreads];   // first stack entry, pages
+  __shared__ int head_pages[kPlanThreads][3];   // first stack entry, pages, state head
   __shared__ int lds[17];
   __shared__ int s_abort;
   if (threadIdx.x == 0) s_abort = load_status(a.status) != 0;
@@ -118,26 +118,35 @@ __global__ __launch_bounds__(kPlanThreads) void seq_reset_kernel(ResetArgs a) {
   int32_t* top = reinterpret_cast<int32_t*>(b + a.top);
   const int NH = a.n * a.H;
   const int top0 = *top;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // a lane group per head (a wave, or less where there are more heads than
+  // waves: a head is a dependent load, and a wave took 50 of 800 in turn), its
+  // lanes over the head's pages and ring entries.  One thread per head, one
+  // wave per head and so: 4 sequences of 8 heads, w = 256, 17.7, 12.8 and 12.0
+  // us; 100 x 8, w = 16, 17.5, 38.4 and 16.7; w = 256, 126, 42.8 and 22.4.
+  const int group = NH <= kPlanThreads / 64 ? 64 : NH <= kPlanThreads / 32 ? 32 : 16;
+  const int lane = threadIdx.x % group;
   int run = 0;
   for (int base = 0; base < NH; base += blockDim.x) {
     const int hh = base + threadIdx.x;
-    int np = 0;
-    if (hh < NH) np = (len[a.seq_ids[hh / a.H] * a.H + hh % a.H] + a.P - 1) / a.P;
+    int np = 0, mine = 0;
+    if (hh < NH) {
+      mine = a.seq_ids[hh / a.H] * a.H + hh % a.H;
+      np = (len[mine] + a.P - 1) / a.P;
+    }
     int tot;
     const int off = block_exclusive_scan(np, lds, &tot);
-    head_pages[threadIdx.x] = make_int2(top0 + run + off, np);
+    head_pages[threadIdx.x][0] = top0 + run + off;
+    head_pages[threadIdx.x][1] = np;
+    head_pages[threadIdx.x][2] = mine;
     __syncthreads();
-    // a wave per head, its lanes over the head's pages and ring entries (one
-    // thread per head: 15 us for 4 sequences of 8 heads, w = 256; 7 us so)
-    for (int x = wave; x < min(static_cast<int>(blockDim.x), NH - base); x += blockDim.x >> 6) {
-      const size_t sh = static_cast<size_t>(a.seq_ids[(base + x) / a.H]) * a.H + (base + x) % a.H;
-      const int2 hp = head_pages[x];
-      for (int k = lane; k < hp.y; k += 64) {
-        stack[hp.x + k] = pt[sh * a.maxp + k];
+    for (int x = threadIdx.x / group; x < min(static_cast<int>(blockDim.x), NH - base); x += blockDim.x / group) {
+      const int first = head_pages[x][0], pages = head_pages[x][1];
+      const size_t sh = head_pages[x][2];
+      for (int k = lane; k < pages; k += group) {
+        stack[first + k] = pt[sh * a.maxp + k];
         pt[sh * a.maxp + k] = -1;
       }
-      for (int e = lane; e < a.w; e += 64) ring[sh * a.w + e] = 0;
+      for (int e = lane; e < a.w; e += group) ring[sh * a.w + e] = 0;
       if (lane == 0) len[sh] = 0;
     }
     __syncthreads();
