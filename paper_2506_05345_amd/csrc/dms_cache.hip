@@ -553,6 +553,7 @@ struct ChunkArgs {
   int immediate;          // eviction timing (see chunk_reuse)
   int fp8;                // FP8 pages: rows are quantized on the way in
   int mla;                // latent-attention pages: the key row only
+  int log2_classes;       // residue classes of a block of the commit pass
 };
 
 __device__ inline int chunk_flag(const ChunkArgs& a, int tok0, int c, int h) {
@@ -707,9 +708,13 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
 // tokens, 8 heads, w = 256: 25 us against 32 us for a walk through memory by
 // one block per head and 31 us for a copy launch with a thread group per
 // token, most of which had nothing to do.
-constexpr int kClasses = 16, kMembers = 64;
+// A block takes fewer classes, and more members of each at a time, where the
+// heads are too few to fill the chip (launch_chunk_commit): with 16 classes
+// always, one latent head of 4096 tokens took 195 us at w = 16 and 54 at w = 64,
+// 4 such heads at w = 256 (64 blocks) 7 us more than now.
+constexpr int kClasses = 16, kSlots = 1024;   // classes of a block at most; tokens gathered at a time
 __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
-  __shared__ int slot_l[kClasses * kMembers], live_l[kClasses * kMembers];
+  __shared__ int slot_l[kSlots], live_l[kSlots];
   __shared__ int live_cnt;
   if (load_status(a.status) != 0) return;
   const int hh = blockIdx.y;
@@ -725,20 +730,21 @@ __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
   const int first_new_page = (L0 + a.P - 1) / a.P;
   if (blockIdx.x == 0)
     for (int k = threadIdx.x; k < a.need[hh]; k += blockDim.x) a.st.page_table[pt_base + first_new_page + k] = popped[-k];
-  const int r0 = blockIdx.x * kClasses;
-  const int nr = min(kClasses, min(a.w, C) - r0);   // classes of this block
+  const int lc = a.log2_classes;
+  const int r0 = blockIdx.x << lc, members = kSlots >> lc;
+  const int nr = min(1 << lc, min(a.w, C) - r0);    // classes of this block
   if (nr <= 0) return;
   const int kq = a.D / 8;                           // 16-byte pieces of a row
   const int log2P = 31 - __clz(a.P);
   int carried = -1;
-  const int rr = threadIdx.x % kClasses;
-  for (int64_t m0 = 0; m0 * a.w + r0 < C; m0 += kMembers) {
+  const int rr = threadIdx.x & ((1 << lc) - 1);
+  for (int64_t m0 = 0; m0 * a.w + r0 < C; m0 += members) {
     if (threadIdx.x == 0) live_cnt = 0;
-    bool lives[kClasses * kMembers / 256];
+    bool lives[kSlots / 256];
 #pragma unroll
-    for (int u = 0; u < kClasses * kMembers / 256; ++u) {
+    for (int u = 0; u < kSlots / 256; ++u) {
       const int e = threadIdx.x + 256 * u;
-      const int64_t c = r0 + rr + (m0 + e / kClasses) * a.w;
+      const int64_t c = r0 + rr + (m0 + (e >> lc)) * a.w;
       int v = -2;                                   // no such token
       lives[u] = false;
       if (rr < nr && c < C) {
@@ -754,20 +760,20 @@ __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
         const int32_t e = a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + r0 + rr) % a.w];
         carried = static_cast<int>(static_cast<uint32_t>(e) & ~kFlagBit);
       }
-      for (int m = 0; m < kMembers; ++m) {
-        const int v = slot_l[m * kClasses + rr];
+      for (int m = 0; m < members; ++m) {
+        const int v = slot_l[(m << lc) + rr];
         if (v == -2) break;
-        if (v == -1) slot_l[m * kClasses + rr] = carried;
+        if (v == -1) slot_l[(m << lc) + rr] = carried;
         else carried = v;
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kClasses * kMembers / 256; ++u) {
+    for (int u = 0; u < kSlots / 256; ++u) {
       const int e = threadIdx.x + 256 * u;
       const int slot = slot_l[e];
       if (slot < 0) continue;
-      const int c = static_cast<int>(r0 + rr + (m0 + e / kClasses) * a.w);
+      const int c = static_cast<int>(r0 + rr + (m0 + (e >> lc)) * a.w);
       const uint32_t fb = chunk_flag(a, tok0, c, h) ? kFlagBit : 0u;
       if (C - c <= a.w)
         a.st.ring[static_cast<size_t>(sh) * a.w + (pos0 + c) % a.w] = static_cast<int32_t>(static_cast<uint32_t>(slot) | fb);
@@ -782,7 +788,7 @@ __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
     // quantizer: it takes every branch together)
     for (int x = threadIdx.x; x < live_cnt * kq; x += blockDim.x) {
       const int e = live_l[x / kq], part = x % kq;
-      const int c = static_cast<int>(r0 + e % kClasses + (m0 + e / kClasses) * a.w);
+      const int c = static_cast<int>(r0 + (e & ((1 << lc) - 1)) + (m0 + (e >> lc)) * a.w);
       const int slot = slot_l[e], row = slot & (a.P - 1), j = row & 31;
       const int pi = slot >> log2P;
       const int page = pi >= first_new_page ? popped[first_new_page - pi] : a.st.page_table[pt_base + pi];
@@ -1010,8 +1016,11 @@ hipError_t launch_chunk_commit(const dms_config& c, const Layout& lo, void* meta
   a.pool = static_cast<char*>(pool);
   hipLaunchKernelGGL(chunk_pages_kernel, dim3(1), dim3(kPlanThreads), 0, st, a);
   const int classes = std::max(1, std::min(c.window, max_len));
-  hipLaunchKernelGGL(chunk_commit_kernel, dim3((classes + kClasses - 1) / kClasses, n * c.num_kv_heads), dim3(256), 0,
-                     st, a);
+  // fewer classes a block until there is about a block per CU
+  int lc = 31 - __builtin_clz(kClasses);
+  while (lc > 0 && static_cast<int64_t>((classes - 1) >> lc) * n * c.num_kv_heads < 256) --lc;
+  a.log2_classes = lc;
+  hipLaunchKernelGGL(chunk_commit_kernel, dim3(((classes - 1) >> lc) + 1, n * c.num_kv_heads), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

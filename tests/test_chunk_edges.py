@@ -1,6 +1,7 @@
-"""Chunk commits where their passes' rounds end: 16 residue classes per block,
-64 members of a class per round, 4096 tokens per scan round; sequence release
-with more heads than waves.  Bookkeeping and stored rows are bit-exact."""
+"""Chunk commits where their passes' rounds end: 1 to 16 residue classes per
+block (fewer for fewer heads), 1024 tokens of them per round, 4096 tokens per
+scan round; sequence release with more heads than lane groups.  Bookkeeping and
+stored rows are bit-exact."""
 import numpy as np
 import pytest
 
@@ -33,6 +34,15 @@ def test_chunk_then_release(w, lens, chunk, H):
         orc.seq_reset(seqs)
         compare_state(cache.export(0), orc, seqs)
     cache.close()
+
+
+@pytest.mark.parametrize("w,lens,chunk,H", [
+    (1, (1100,), 1100, 1),           # one class a block, more members than a round
+    (70, (150,) * 8, 150, 2),        # four classes a block, the last one short
+    (40, (90,) * 16, 90, 8),         # sixteen
+    (9, (35,) * 12, 35, 2)])         # release: half a wave per head
+def test_classes_per_block(w, lens, chunk, H):
+    test_chunk_then_release(w, lens, chunk, H)
 
 
 def test_release_of_many_heads():
