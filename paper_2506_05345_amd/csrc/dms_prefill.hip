@@ -31,8 +31,8 @@
 // registers.  A tile is masked per element only when some query of the block
 // does not see one of its keys; the online softmax works in the exp2 domain
 // with a lazy rescale.  Pass 0 also counts the kept chunk tokens before every
-// 32-aligned position and a one-block pass ranks the call's (sequence, head)
-// rows by work; the attention launch keeps as many workgroups as fit on the
+// 32-aligned position and the first block of pass 1 ranks the call's (sequence,
+// head) rows by work; the attention launch keeps as many workgroups as fit on the
 // chip, each taking (row, query block) items in that order.
 #include <type_traits>
 
@@ -121,6 +121,7 @@ struct PrefillArgs {
   float* out;             // [T, Hq, D]
   size_t page_bytes;
   int n, H, g, w, P, log2P, maxp, max_slots, max_seqs, total, max_len, PB, tph;
+  int order;        // 1: the first blocks of pass 1 order the rows
   int immediate;    // eviction timing: key j is hidden by the decision of j + w
   int zero_neuron;  // element 0 of each group's first query head is read as 0
   float scale_log2;
@@ -160,20 +161,24 @@ __device__ inline size_t ws_kb(const PrefillArgs& a, int h, int i, int j) {
 // attends to, and the mean of its kept-prefix keys); ties keep row order, and
 // calls of more than kOrderMax rows keep theirs.  It also writes each row's
 // descriptor (which saves a work item three dependent loads) and first work
-// item, so that rows of shorter chunks have no empty items.
+// item, so that rows of shorter chunks have no empty items.  Like pass 1 it
+// needs nothing but pass 0's results, so it runs as the first blocks of that
+// launch (`part`: one of every 256 unranked rows, one in all of ranked ones): a
+// launch of its own took 3.4 to 6.2 us a chunk.
 constexpr int kOrderMax = 512;
-__global__ __launch_bounds__(kThreads) void prefill_order_kernel(PrefillArgs a) {
+__device__ __forceinline__ void order_rows(const PrefillArgs& a, int part) {
   __shared__ int work[kOrderMax], blocks[kOrderMax], lds[17];
-  if (load_status(a.status) != 0) return;
   const int NH = a.n * a.H;
   const bool ranked = NH <= kOrderMax;
+  if (ranked && part > 0) return;
   if (ranked)
     for (int x = threadIdx.x; x < kOrderMax; x += kThreads) {
       work[x] = x < NH ? a.len[a.seq_ids[x / a.H] * a.H + x % a.H] + a.list_cnt[x] / 2 : 0;
       blocks[x] = 0;
     }
   __syncthreads();
-  for (int x = blockIdx.x * kThreads + threadIdx.x; x < NH; x += gridDim.x * kThreads) {
+  const int end = ranked ? NH : min(NH, (part + 1) * kThreads);
+  for (int x = part * kThreads + threadIdx.x; x < end; x += kThreads) {
     int rank = x;
     if (ranked) {
       rank = 0;
@@ -211,7 +216,8 @@ __global__ __launch_bounds__(kThreads) void prefill_order_kernel(PrefillArgs a) 
   if (threadIdx.x == 0) a.first_item[NH] = total;
 }
 
-// Pass 1 (one block per (32-token tile, sequence x head, region)): copy the
+// Pass 1 (one block per (32-token tile, sequence x head, region), after those
+// that order the rows): copy the
 // chunk's keys and values -- region 0: in chunk order; region 1: the kept
 // tokens in list order -- into workspace tiles in the pool's tile layout
 // (fragment order, values transposed); rows past the end are 0.
@@ -219,7 +225,11 @@ template <int D, bool FP8>
 __global__ __launch_bounds__(kThreads) void prefill_tile_kernel(PrefillArgs a) {
   __shared__ uint16_t vrows[32][D + 2];
   if (load_status(a.status) != 0) return;
-  const int k = blockIdx.x, hh = blockIdx.y, region = blockIdx.z;
+  const int k = blockIdx.x - a.order, hh = blockIdx.y, region = blockIdx.z;
+  if (k < 0) {
+    if (region == 0) order_rows(a, hh);
+    return;
+  }
   if (!FP8 && k == 0 && hh == 0 && region == 1)
     for (int x = threadIdx.x; x < D * 4; x += kThreads) reinterpret_cast<u32x4*>(a.zeros)[x] = u32x4{0u, 0u, 0u, 0u};
   const int i = hh / a.H, h = hh % a.H;
@@ -688,7 +698,7 @@ __global__ __launch_bounds__((attn_threads<D, FP8>()), (512 / attn_threads<D, FP
   }
 };
 
-  // items as in the bf16 pass: grid position first, then the counter
+  // items: grid position first, then the counter
   int item = blockIdx.x, buf = 0;
   if (threadIdx.x == 0) item_lds[0] = gridDim.x + atomicAdd(a.work_ctr, 1);
   while (item < a.items) {
@@ -926,7 +936,7 @@ void prefill_delayed_kernel(PrefillArgs a) {
     for (int x = tid; x <= NH; x += 64 * NW) first_lds[x] = a.first_item[x];
   __syncthreads();
   const int items = ranked ? __builtin_amdgcn_readfirstlane(first_lds[NH]) : a.items;
-  // ranked: first_lds holds the rows' first items (see prefill_order_kernel)
+  // ranked: first_lds holds the rows' first items (see order_rows)
   auto load_item = [&](int item) { return prefill_item(a, first_lds, item, lane); };
   auto page_of = [&](const Item& it, int k) { return pool_page(a, it, k); };
   auto source = [&](const Item& it, int k, int page, const char*& tile, const uint32_t*& mt) {
@@ -1276,11 +1286,8 @@ hipError_t launch_prefill_d(const dms_config& c, const Layout& lo, void* meta, v
   if (ev_start) (void)hipEventRecord(ev_start, st);
   hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prefill_order_kernel, dim3(NH <= kOrderMax ? 1 : (NH + kThreads - 1) / kThreads), dim3(kThreads),
-                     0, st, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((prefill_tile_kernel<D, FP8>), dim3((max_len + 31) / 32, NH, 2), dim3(kThreads), 0,
+  a.order = 1;
+  hipLaunchKernelGGL((prefill_tile_kernel<D, FP8>), dim3(a.order + (max_len + 31) / 32, NH, 2), dim3(kThreads), 0,
                      st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1337,7 +1344,11 @@ __device__ inline u32x2 tr_read16(const char* p) {
 // are 0.
 __global__ __launch_bounds__(kThreads) void prefill_tile_mla_kernel(PrefillArgs a) {
   if (load_status(a.status) != 0) return;
-  const int k = blockIdx.x, i = blockIdx.y, region = blockIdx.z;
+  const int k = blockIdx.x - a.order, i = blockIdx.y, region = blockIdx.z;
+  if (k < 0) {
+    if (region == 0) order_rows(a, i);
+    return;
+  }
   const int tok0 = a.cu[i], C = a.cu[i + 1] - a.cu[i];
   const int cnt = region ? a.list_cnt[i] : C;
   if (k * 32 >= cnt) return;
@@ -1867,13 +1878,8 @@ hipError_t launch_prefill_mla(const dms_config& c, const Layout& lo, void* meta,
   if (ev_start) (void)hipEventRecord(ev_start, st);
   hipError_t e = launch_chunk_scan(c, lo, meta, ws, layer, n, seq_ids, cu, total_tokens, max_len, flags, true, st);
   if (e != hipSuccess) return e;
-  if (!a.immediate) {
-    hipLaunchKernelGGL(prefill_order_kernel, dim3(n <= kOrderMax ? 1 : (n + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                       st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(prefill_tile_mla_kernel, dim3((max_len + 31) / 32, n, 2), dim3(kThreads), 0, st, a);
+  a.order = !a.immediate;
+  hipLaunchKernelGGL(prefill_tile_mla_kernel, dim3(a.order + (max_len + 31) / 32, n, 2), dim3(kThreads), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!a.immediate) {
