@@ -88,7 +88,11 @@ typedef struct dms_config {
   int32_t window;             /* w >= 1: eviction delay = sliding window */
   int32_t page_size;          /* P tokens per page: 32, 64, 128 or 256 */
   int32_t num_pages;          /* pages in each layer's pool */
-  int32_t max_pages_per_head; /* page-table length of one (seq, head) */
+  int32_t max_pages_per_head; /* page-table length of one (seq, head).  Size it to
+                                 the heads' retained slots, not to the context:
+                                 where it bounds a head by 2048 slots (times
+                                 page_size), decode steps of at most 256 KV heads
+                                 take the launch with the least latency */
   int32_t max_chunk_tokens;   /* largest total token count of one chunk call */
   float softmax_scale;        /* <= 0 selects 1 / sqrt(head_dim) */
   int32_t eviction;           /* DMS_EVICT_DELAYED (0, the method) or
@@ -422,7 +426,8 @@ const char* dms_strerror(int code);
  *   dalpha    f32  [B, T, Hkv]
  * Query head q reads KV head q / g.  Gradients are of sum(out * dout) and
  * overwrite their buffers.  The workspace (dms_train_workspace bytes) holds
- * tiled copies of the inputs; it and every buffer belong to the caller, and
+ * key biases, per-row sums, aligned copies of inputs that are not 16-byte
+ * aligned and partial gradients; it and every buffer belong to the caller, and
  * one workspace serves one stream at a time.  Errors: DMS_ERR_INVALID /
  * DMS_ERR_UNSUPPORTED (host checks, nothing launched) or DMS_ERR_HIP.
  */

@@ -23,10 +23,12 @@
 // core (about half busy in each).  32x32 products take half the MFMA and LDS
 // read instructions per key of 16x16 ones.  One layer of 8 x 5 heads, 2 x
 // 8192 tokens, w = 256, before (16x16 products on tiles re-laid in memory by a
-// pass of their own) and now: forward 1836 -> 1400 us (980 TFLOP/s), dQ 4005
-// -> 1820 us (1130 of its three products), dK / dV 5160 -> 2570 us (1070 of
-// its four), tiling and row sums 380 us -> none; operands read ahead in pinned
-// order are 2 to 4 % of each pass here, 6 to 14 % with 1777 tokens of 2 heads.
+// pass of their own) and now: forward 1836 -> 1390 us (990 TFLOP/s), dQ 4005
+// -> 1800 us (1150 of its three products), dK / dV 5160 -> 2540 us (1080 of
+// its four), tiling and row sums 380 us -> none; the clock drops under the
+// matrix core, so that single runs lie within 4 % of these.  Operands read
+// ahead in pinned order are 2 to 4 % of each pass here, 6 to 14 % with 1777
+// tokens of 2 heads.
 // Pairing each tile's weights with the next tile's scores and the last tile's
 // value products in one scheduled stretch ran 1540 to 1700 us forward: the
 // second wave of a SIMD already fills the gaps, and the tile-by-tile barriers
@@ -645,7 +647,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_dq_kernel(TrainArgs a) {
 // When the call has too few blocks to fill the chip, each block's steps are
 // split over `splits` workgroups whose sums train_sum_kernel adds in order:
 // 1777 tokens of 2 x 6 heads, 518 us with one workgroup of 64 keys per block,
-// 83 + 8 us with six of 128.  Both loops hold 256 registers without a spill
+// 75 + 8 us with six of 128.  Both loops hold 256 registers without a spill
 // only when a step's products and its element-wise part are kept apart and not
 // unrolled over the two steps; a reload from scratch waits for every copy in
 // flight (4400 us against 2600 us).
