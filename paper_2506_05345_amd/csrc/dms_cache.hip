@@ -696,22 +696,21 @@ __global__ __launch_bounds__(kPlanThreads) void chunk_pages_kernel(ChunkArgs a) 
   }
 }
 
-// Pass 3 (one block per (head, 16 residue classes modulo w)): slots of the
+// Pass 3 (one block per (head, up to 16 residue classes modulo w)): slots of the
 // reusing tokens, ring, slot metadata, and the K rows and V columns of the
 // surviving tokens.  A token that reuses takes the slot of the token w before
 // it, so along one class c = r, r + w, r + 2w, ... every token holds the slot
 // of the latest fresh token of the class before it, or, for the first ones,
 // the slot the ring gives for position pos0 + r - w; the class reads and
-// writes no other ring entry than that one, so classes are independent.  Up to
-// 64 members of each class are gathered in LDS at a time, walked there, and
+// writes no other ring entry than that one, so classes are independent.  1024
+// tokens of the block's classes are gathered in LDS at a time, walked there, and
 // the survivors (one in eight at 7/8 evicted) listed for the copy.  4 x 4096
 // tokens, 8 heads, w = 256: 25 us against 32 us for a walk through memory by
 // one block per head and 31 us for a copy launch with a thread group per
 // token, most of which had nothing to do.
 // A block takes fewer classes, and more members of each at a time, where the
-// heads are too few to fill the chip (launch_chunk_commit): with 16 classes
-// always, one latent head of 4096 tokens took 195 us at w = 16 and 54 at w = 64,
-// 4 such heads at w = 256 (64 blocks) 7 us more than now.
+// heads are too few to fill the chip (launch_chunk_commit): one latent head of
+// 4096 tokens, w = 16, 195 us in one block of 16 classes, about 40 in 16 of one.
 constexpr int kClasses = 16, kSlots = 1024;   // classes of a block at most; tokens gathered at a time
 __global__ __launch_bounds__(256) void chunk_commit_kernel(ChunkArgs a) {
   __shared__ int slot_l[kSlots], live_l[kSlots];

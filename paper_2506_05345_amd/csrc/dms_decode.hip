@@ -1332,9 +1332,10 @@ __global__ __launch_bounds__(256, 1) void decode_step_kernel(
 // 24.2, of 56 tiles 57 -> 46.5.  Each tile's keys and values are loaded as
 // soon as the products of the tile before have read theirs: loading a whole
 // tile after the whole of the one before left 2 heads of 53 and 56 tiles 3 and
-// 5 % slower than the launch above (64 heads of 56 FP8 tiles: 20.0 -> 18.8).  Eight waves with two tiles in flight each ran 6.7, 16.2
-// and 19.0 us, sixteen waves 25 us for 40 tiles (128 registers each: the
-// stream spills).
+// 5 % slower than the launch above (64 heads of 56 FP8 tiles: 20.0 -> 18.8).
+// Of eight, eleven and sixteen streaming waves loading whole tiles (eight: two
+// of them in flight) 64 heads of 40 tiles took 19.0, 18.6 and 25 us (sixteen:
+// 128 registers each, the stream spills).
 // ---------------------------------------------------------------------------
 constexpr int kShortTiles = 64;     // 32-slot tiles of one head (one page-table entry per lane)
 constexpr int kShortHeads = 256;
