@@ -1634,8 +1634,8 @@ __global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_kernel(PrefillArgs
 // read fall into different banks.  16x16 products read every operand for 16
 // columns and were bound by those reads; now the matrix core is the bound,
 // and, with one wave per SIMD, the softmax between its two products.  Four
-// prompts of 4096 to 8192 tokens in chunks of 4096, 16 heads: 988 us with
-// every pass, from 1703 us (attention 844 -> 477 us a call).
+// prompts of 4096 to 8192 tokens in chunks of 4096, 16 heads: 933 us with
+// every pass, from 1703 us.
 __global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_delayed_kernel(PrefillArgs a) {
   constexpr int NW = kMlaThreads / 64;
   constexpr int KS = kMlaDim / 16, OB = kMlaLatent / 32;
@@ -1768,7 +1768,14 @@ __global__ __launch_bounds__(kMlaThreads, 1) void prefill_mla_delayed_kernel(Pre
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
       mx = col_max32(mx);
       const bool raise = mx > m_ref + thr;   // false while the column has seen no key
-      if (__builtin_amdgcn_ballot_w64(raise)) {
+      uint64_t rescale = __builtin_amdgcn_ballot_w64(raise);
+      if (rescale) {
+        // not where no raised column has a sum yet, as in an item's first tile: 256 accumulators
+        // through the vector registers are about 2 us (4 prompts of 4096 to 8192 tokens 959 -> 933 us)
+        rescale = __builtin_amdgcn_ballot_w64(raise && col_sum32(l_run) > 0.f);
+        if (!rescale) m_ref = raise ? mx : m_ref;
+      }
+      if (rescale) {
         const float m_new = raise ? mx : m_ref;
         const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
         l_run *= alpha;
